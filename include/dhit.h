@@ -93,8 +93,9 @@ typedef struct dhit_params {
                            so that the round fills the device;
                            0 = chosen at create_box for the current device:
                            among the chunks ceil(n/k) >= min(n, 8), plain or
-                           cut, the one that minimises the launch's estimated
-                           plane iterations per block.  Every setting gives
+                           cut, and the shorter ones whose blocks the device
+                           holds at once, the one that minimises the launch's
+                           estimated plane iterations per block.  Every setting gives
                            the same populations; the global sums agree to
                            rounding (the work split groups the cells' sums) */
     double nu;          /* kinematic viscosity, > 0 */

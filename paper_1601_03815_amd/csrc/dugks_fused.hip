@@ -1223,9 +1223,11 @@ int fused_dugks_items(int n, int w, int chunk, int *tiles_x, int *tiles_y) {
   return tx * ty * ((n + chunk - 1) / chunk);
 }
 
-// Shortest z-chunk the balanced choice below takes (shorter chunks re-read
-// the two halo planes too often).
+// Shortest z-chunk the balanced choice below takes for a launch that fills
+// the device (shorter chunks re-read the two halo planes too often), and the
+// most items a launch of shorter chunks has.
 constexpr int kMinAutoChunk = 8;
+constexpr int kMaxShortItems = 1024;
 
 // Parts each chunk of a launch's last round is cut into: `chunks` items of
 // `chunk` planes run in rounds of `slots` blocks; when at least one round
@@ -1248,7 +1250,7 @@ FusedPlan fused_plan_for(const dhit_params &p, int slots) {
   const int n = p.n;
   f.width = p.tile_width ? p.tile_width : fused_tile_width(p.precision);
   // an unresolved setting (0) gets the shortest automatic chunk: an upper
-  // bound on the items, for sizing buffers
+  // an unresolved setting (0) is taken as kMinAutoChunk planes
   f.chunk = p.z_chunk > 0 ? p.z_chunk : (p.z_chunk < 0 ? -p.z_chunk : std::min(n, kMinAutoChunk));
   const int chunks = fused_dugks_items(n, f.width, f.chunk, &f.tiles_x, &f.tiles_y);
   f.items = f.tail_from = f.grid = chunks;
@@ -1287,15 +1289,18 @@ void fused_item_planes(const FusedPlan &f, int n, int item, int *tile, int *z0, 
 
 // Work items of a box's fused launch (and its tiling).  With z_chunk = 0
 // (not yet resolved) an upper bound for sizing buffers: twice the items of
-// the shortest automatic chunk and 8 (a cut last round adds at most a
-// round's items, rounded up to a multiple of 8, to at least one full round).
+// an automatic chunk of kMinAutoChunk planes and 8 (a cut last round adds at
+// most a round's items, rounded up to a multiple of 8, to at least one full
+// round), or what shorter chunks may have (kMaxShortItems, at most one item
+// per tile-plane).
 int fused_dugks_blocks(const dhit_params &p, int *width, int *tiles_x, int *tiles_y, int *nz_chunk) {
   const FusedPlan f = fused_plan(p);
   if (width) *width = f.width;
   if (tiles_x) *tiles_x = f.tiles_x;
   if (tiles_y) *tiles_y = f.tiles_y;
   if (nz_chunk) *nz_chunk = f.chunk;
-  return p.z_chunk == 0 ? 2 * f.items + 8 : f.items;
+  if (p.z_chunk != 0) return f.items;
+  return std::max(2 * f.items + 8, std::min(f.tiles_x * f.tiles_y * p.n, kMaxShortItems));
 }
 
 // FP64 tiles use the split-population march (two thread groups per
@@ -1434,14 +1439,23 @@ static int fused_slots(int precision, int w) {
 // 37 planes cost 11 rounds of 39 iterations (the last round 58% full: 429);
 // chunks of 128 planes, 3 full rounds of 130 and 6 chunks left over that
 // are cut into 32 parts of 4 planes, 396.
+// A small box does not fill one round even with chunks of kMinAutoChunk
+// planes; its launch lasts as long as one block's march, so the shorter
+// chunks whose items still fit one round are taken into the choice: at 32^3
+// (12 column tiles) FP64 chunks of 2 planes (192 items) ran 22.6 us a step
+// against 44.6 with 8 planes (48 items), at 48^3 3 planes (256 items) 26.9
+// against 42.6, at 64^3 in FP32 (512 slots) 6 planes 37.0 against 42.9.  Two
+// rounds of the shortest chunks lose again (32^3, 1 plane, 384 items: 30.7).
 int fused_balanced_chunk(int n, int tiles_xy, int slots) {
   const int cmin = std::min(n, kMinAutoChunk);
+  const int one_round = std::min(slots, kMaxShortItems);
   int best = n;
   int64_t best_cost = INT64_MAX;
-  for (int k = 1; (n + k - 1) / k >= cmin; ++k) {
-    const int c = (n + k - 1) / k;
-    if (k > 1 && c == (n + k - 2) / (k - 1)) continue;  // same chunk as k - 1
-    const int64_t blocks = (int64_t)tiles_xy * ((n + c - 1) / c);
+  for (int c = n; c >= 1; --c) {
+    const int k = (n + c - 1) / c;
+    if ((n + k - 1) / k != c) continue;  // k chunks can be shorter
+    const int64_t blocks = (int64_t)tiles_xy * k;
+    if (c < cmin && blocks > one_round) break;
     const int64_t cost = (blocks + slots - 1) / slots * (c + 2);
     if (cost < best_cost) {
       best_cost = cost;

@@ -113,3 +113,39 @@ def test_work_split_errors():
         dhit.fused_work_item(_params(32), 256, 10 ** 6)
     with pytest.raises(dhit.DhitError):
         dhit.fused_work_items(_params(32, chunk=-33), 256)
+
+
+@pytest.mark.parametrize("n", [4, 7, 9, 16, 24, 32, 33, 40, 48, 49, 64, 80])
+@pytest.mark.parametrize("tile", [16, 32])
+@pytest.mark.parametrize("slots", [64, 256, 512, 1024, 4096])
+def test_automatic_choice_of_small_boxes(n, tile, slots):
+    """The automatic chunk is the cheapest of its candidates, re-derived here:
+    chunks ceil(n/k) of at least min(n, 8) planes in as many rounds as they
+    need, and shorter ones that fit one round (at most 1024 items); a launch's
+    cost is its rounds times the planes a block visits (chunk + 2)."""
+    tiles = math.ceil(n / (tile - 2)) * math.ceil(n / 6)
+    items, zc, _ = _cover(_params(n, tile=tile), slots)
+    assert items <= max(2 * tiles * math.ceil(n / min(n, 8)) + 8, min(tiles * n, 1024))
+    cost = {}
+    for k in range(1, n + 1):
+        c = math.ceil(n / k)
+        blocks = tiles * math.ceil(n / c)
+        if c >= min(n, 8) or blocks <= min(slots, 1024):
+            cost[c] = math.ceil(blocks / slots) * (c + 2)
+    if zc > 0:
+        assert items == tiles * math.ceil(n / zc)
+        assert cost[zc] == min(cost.values())
+    else:
+        assert -zc >= min(n, 8) and items > slots
+
+
+def test_small_boxes_get_short_chunks():
+    """32^3: 12 tiles; FP64 on 256 slots takes 2 planes (192 items, one
+    round), FP32 on 512 slots one plane (384 items)."""
+    assert fused_choice(32, "fp64", 256) == (192, 2)
+    assert fused_choice(32, "fp32", 512) == (384, 1)
+    assert fused_choice(48, "fp64", 256) == (256, 3)
+
+
+def fused_choice(n, precision, slots):
+    return dhit.fused_work_items(_params(n, precision), slots)
