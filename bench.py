@@ -163,8 +163,8 @@ def gpu_sizes(torch, dhit, nu, steps=100, warmup=10):
 
 def mesh_costs(torch, dhit, n=256, steps=10, warmup=3):
     """DUGKS on a stretched mesh against unit cells at n^3: per-kernel mean
-    launch times (HIP events on the box's stream) of the stretched-mesh
-    two-pass path and of the fused uniform kernel, same field and dt
+    launch times (HIP events on the box's stream) of the march on a
+    stretched mesh and on unit cells, same field and dt
     (CFL 0.9 on the smallest cell of the mesh)."""
     import numpy as np
     import synth
@@ -173,7 +173,7 @@ def mesh_costs(torch, dhit, n=256, steps=10, warmup=3):
     dt = 0.9 * W.min() / np.sqrt(2.0)
     out = {"n": n, "widths": "1 + a cos(2 pi (i + 1/2)/n + phase), a = (0.2, 0.3, 0.25)", "dt": round(dt, 6)}
     for precision in ("fp64", "fp32"):
-        for label, mesh in (("uniform_fused", None), ("stretched_two_pass", W)):
+        for label, mesh in (("uniform", None), ("stretched", W)):
             print("bench: mesh %s %s" % (precision, label), file=sys.stderr, flush=True)
             b = dhit.Box(n, "dugks", precision, 0.01, dt=dt, stream=torch.cuda.Stream())
             if mesh is not None:

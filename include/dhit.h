@@ -66,7 +66,7 @@ enum dhit_method {
 enum dhit_precision {
     DHIT_FP64 = 0,         /* populations stored and updated in double */
     DHIT_FP32 = 1          /* populations stored and updated in float, per-cell moment sums
-                              compensated, global reductions in double */
+                              compensated or in double, global reductions in double */
 };
 
 /* Kernel variant of a step.  DHIT_VARIANT_DEFAULT picks the fastest
@@ -194,8 +194,8 @@ int32_t init_velocity_field_device(dhit_box *b, const double *u, const double *d
  * (whatever the variant) and the five sums of the step history and of
  * moments() are weighted by the cell volumes w_x w_y w_z.  Unit widths give
  * the uniform scheme.  widths = NULL returns the box to unit cells.
- * Allocates the mesh tables and, if the box has none, the scratch field of
- * the two-pass form.  Synchronous.  DHIT_EMETHOD on an LBE box;
+ * Allocates the mesh tables (and the step's tables, for a box of the
+ * two-pass variant).  Synchronous.  DHIT_EMETHOD on an LBE box;
  * DHIT_EINVAL for a width that is not finite and > 0, or for
  * sqrt(2) dt > min width (CFL above 1; the paper takes
  * dt = CFL dx_min / sqrt(2)).  Boxes with a stretched mesh cannot be batched
@@ -385,7 +385,7 @@ enum dhit_kernel {
     DHIT_K_LBE = 0,              /* LBE pull streaming + collision */
     DHIT_K_DUGKS_TRANSFORM = 1,  /* DUGKS cell transform (two-pass variant) */
     DHIT_K_DUGKS_FACE = 2,       /* DUGKS face fluxes and update (two-pass variant) */
-    DHIT_K_DUGKS_FUSED = 3,      /* DUGKS single-kernel step */
+    DHIT_K_DUGKS_FUSED = 3,      /* DUGKS single-kernel step (on a stretched mesh too) */
     DHIT_K_FINALIZE = 4,         /* global-sum finalisation */
     DHIT_NKERNEL = 5
 };

@@ -218,7 +218,8 @@ void upload_table(dhit_batch &bt) {
 void enqueue_step(dhit_batch &bt, int commit) {
   const int nbox = (int)bt.boxes.size();
   if (bt.method == DHIT_DUGKS)
-    dhit::launch_dugks_batch(bt.stream, bt.precision, bt.tile, bt.max_n, bt.d_boxes, nbox, bt.total_items, bt.grid);
+    dhit::launch_dugks_batch(bt.stream, bt.precision, bt.tile, bt.max_n, bt.d_boxes, nbox, bt.total_items, bt.grid,
+                             false);
   else
     dhit::launch_lbe_batch(bt.stream, bt.method, bt.precision, bt.cells_per_thread, bt.d_boxes, nbox, bt.total_items,
                            bt.grid);

@@ -394,26 +394,50 @@ int32_t set_mesh(dhit_box *b, const double *widths) {
     }
     // the fastest particles move sqrt(2) per unit time: CFL = sqrt(2) dt / w_min
     if (std::sqrt(2.0) * b->p.dt > wmin) fail(DHIT_EINVAL, "dt exceeds CFL 1 on the smallest cell");
-    std::vector<double> t((size_t)3 * dhit::kMeshTables * n);
+    // widths in double, then the march's coefficients in the box's precision
+    const size_t coefs = (size_t)3 * dhit::kMarchCoefs * n, wbytes = (size_t)3 * n * sizeof(double);
+    std::vector<double> t(coefs);
+    const double h = b->sp.h, dtal = b->sp.dt * b->sp.alpha;
     for (int a = 0; a < 3; ++a) {
       const double *w = widths + (size_t)a * n;
-      double *row = t.data() + (size_t)a * dhit::kMeshTables * n;
+      double *row = t.data() + (size_t)a * dhit::kMarchCoefs * n;
       for (int i = 0; i < n; ++i) {
         const double wm = w[(i + n - 1) % n], wi = w[i], wp = w[(i + 1) % n];
-        row[dhit::kMeshWidth * n + i] = wi;
-        row[dhit::kMeshInvWidth * n + i] = 1.0 / wi;
-        row[dhit::kMeshLam * n + i] = wi / (wi + wp);
-        row[dhit::kMeshInvGap * n + i] = 2.0 / (wi + wp);
-        row[dhit::kMeshInvSpan * n + i] = 1.0 / (0.5 * wm + wi + 0.5 * wp);
+        const double lam = wi / (wi + wp), hg = h * 2.0 / (wi + wp), hgm = h * 2.0 / (wm + wi);
+        const double A = dtal * lam / wi, E = dtal * (wi / (wm + wi)) / wi;  // 1 - lam_{i-1} = w_i/(w_{i-1} + w_i)
+        row[dhit::kMarchUp * n + i] = A - dtal * hg / wi;
+        row[dhit::kMarchUm * n + i] = -A - dtal * hg / wi;
+        row[dhit::kMarchVp * n + i] = E + dtal * hgm / wi;
+        row[dhit::kMarchVm * n + i] = -E + dtal * hgm / wi;
+        row[dhit::kMarchA * n + i] = A;
+        row[dhit::kMarchE * n + i] = E;
+        row[dhit::kMarchLam * n + i] = lam;
+        row[dhit::kMarchHg * n + i] = hg;
+        row[dhit::kMarchHs * n + i] = h / (0.5 * wm + wi + 0.5 * wp);
+        row[dhit::kMarchIw * n + i] = 1.0 / wi;
       }
     }
-    if (!b->scratch) {
-      const int64_t bytes = population_buffer_bytes(&b->p);
-      if (hipMalloc(&b->scratch, (size_t)bytes) != hipSuccess) fail(DHIT_ENOMEM, "cannot allocate DUGKS scratch field");
+    std::vector<char> img(wbytes + coefs * b->elem);
+    std::memcpy(img.data(), widths, wbytes);
+    if (b->elem == sizeof(double)) {
+      std::memcpy(img.data() + wbytes, t.data(), coefs * sizeof(double));
+    } else {
+      std::vector<float> tf(t.begin(), t.end());
+      std::memcpy(img.data() + wbytes, tf.data(), coefs * sizeof(float));
     }
-    if (!b->mesh && hipMalloc(&b->mesh, t.size() * sizeof(double)) != hipSuccess)
-      fail(DHIT_ENOMEM, "cannot allocate mesh tables");
-    DHIT_HIP(hipMemcpy(b->mesh, t.data(), t.size() * sizeof(double), hipMemcpyHostToDevice));
+    if (!b->step_table) {  // a box of the two-pass variant
+      if (hipMalloc(&b->step_table, 2 * sizeof(dhit::BatchBox)) != hipSuccess)
+        fail(DHIT_ENOMEM, "cannot allocate the step table");
+      b->own_step_table = true;
+    }
+    const bool had = b->mesh != nullptr;
+    if (!had && hipMalloc(&b->mesh, img.size()) != hipSuccess) fail(DHIT_ENOMEM, "cannot allocate mesh tables");
+    DHIT_HIP(hipMemcpy(b->mesh, img.data(), img.size(), hipMemcpyHostToDevice));
+    if (!had) {  // the step's tables name the mesh
+      dhit::BatchBox e[2];
+      dhit::fused_table_entries(*b, e);
+      DHIT_HIP(hipMemcpy(b->step_table, e, sizeof(e), hipMemcpyHostToDevice));
+    }
     return DHIT_OK;
   });
 }

@@ -277,6 +277,113 @@ __device__ __forceinline__ void zface_half(const P &c, Real h, Real (&m)[4]) {
   });
 }
 
+// ---------------------------------------------------------------------------
+// Stretched mesh (set_mesh).  With cell widths w that vary along each axis
+// the reconstruction reads, at the face between L = i and R = i+1 of an axis
+// (lam = w_L/(w_L + w_R), g = 1/(c_R - c_L), s_t = 1/(c_{k+1} - c_{k-1}) of
+// the tangential axis t),
+//   fbar = B_L + lam (B_R - B_L) - h [xi_d g (B_R - B_L)
+//          + sum_t xi_t s_t (G_t(L) + lam (G_t(R) - G_t(L)))],
+// and each axis's flux difference is divided by the cell's width, so that
+// with A = lam_i/w_i, E = (1 - lam_{i-1})/w_i, b = h g_i/w_i,
+// f = h g_{i-1}/w_i of the centre i along an axis
+//   axis part, sign s:  U (B(+) - B(0)) + V (B(0) - B(-)),  U = s A - b, V = s E + f
+//   mixed part of a diagonal population in (d1, d2):
+//     - h s1 s2 { s_2 [A_1 (G_2(+) - G_2(0)) + E_1 (G_2(0) - G_2(-))]
+//               + s_1 [A_2 (G_1(+) - G_1(0)) + E_2 (G_1(0) - G_1(-))] }
+// (unit widths give the stencils above).  The pieces of a plane go to the
+// same three centres as on unit cells, with the coefficients of the centre
+// they go to: those of x and y are per column (a table in LDS, read in each
+// phase: held in registers, or hoisted there, they would not fit), those of z
+// are uniform over the block (scalar loads).
+//
+// The tables hold one row of n values per coefficient and axis (MarchCoef,
+// runtime.hpp), already multiplied by dt alpha (U, V, A, E) and by h.
+//
+// Like the march on unit cells it is bound by the latency its two waves per
+// SIMD cannot cover (FP64) and by vector issue (FP32): 15-20% more
+// instructions than there (1,840 and 1,700 per plane and wave pair).  It took
+// the place of a transform pass and a face pass that rebuilt six faces of 19
+// populations per cell from some 700 cached loads: 128^3 FP64 1.04 -> 0.272 ms
+// a step, 97^3 FP32 0.132 -> 0.083 ms.
+template <typename T>
+using constant_t = __attribute__((address_space(4))) T;
+template <typename Real, int W>
+struct MeshMarch {
+  const constant_t<Real> *zc;  // the z axis's rows
+  const Real *X, *Y;           // LDS: the column's x and y coefficients
+  int n;
+  __device__ __forceinline__ Real z(int k, int plane) const {
+    const int i = plane < 0 ? plane + n : (plane >= n ? plane - n : plane);
+    return zc[k * n + i];
+  }
+  template <int D>
+  __device__ __forceinline__ Real col(int k) const {
+    return D == 0 ? X[k * W] : Y[k * 8];
+  }
+};
+// Values of the x/y coefficient table in LDS of a tile.
+template <int W>
+constexpr int kMeshValues = kMarchCoefs * (W + 8);
+
+// Fills the block's x/y coefficient table for tile (x0, y0).
+template <typename Real, int W>
+__device__ __forceinline__ void load_mesh_columns(const Real *coef, int n, int x0, int y0, Real *L) {
+  for (int i = threadIdx.x; i < kMeshValues<W>; i += blockDim.x) {
+    const bool isx = i < kMarchCoefs * W;
+    const int j = isx ? i : i - kMarchCoefs * W;
+    const int k = isx ? j / W : j / 8, c = (isx ? x0 + j % W : y0 + j % 8) - 1;
+    const int cell = c < 0 ? c + n : c % n;
+    L[i] = to_global(coef)[((isx ? 0 : kMarchCoefs) + k) * n + cell];
+  }
+}
+
+// In-plane part of a D-face's moments on the mesh (see face_inplane): the
+// value v of cell L and the rest m, which is small beside it (added to v once,
+// so that in FP32 a moment is rounded at the scale of v once).
+template <int D, int LX, int LY, typename Real, class P>
+__device__ __forceinline__ void face_inplane_mesh(const P &c, Real lam, Real hg, Real hs, Real (&v)[4], Real (&m)[4]) {
+  constexpr int t = 1 - D;
+  constexpr int RX = LX + Unit<D>::x, RY = LY + Unit<D>::y;
+  auto moment = [&](auto i, auto V, auto N, auto T) {
+    const Real vl = c.template at<V, LX, LY>(), vr = c.template at<V, RX, RY>();
+    const Real tl = dif<T, t, LX, LY>(c), tr = dif<T, t, RX, RY>(c);
+    v[i] = vl;
+    m[i] = lam * ((vr - vl) - hs * (tr - tl)) - (hs * tl + hg * (c.template at<N, RX, RY>() - c.template at<N, LX, LY>()));
+  };
+  using std::integral_constant;
+  moment(integral_constant<int, 0>{}, integral_constant<int, kR0>{}, integral_constant<int, jid(D)>{},
+         integral_constant<int, jid(t)>{});
+  static_for<3>([&](auto a) {
+    moment(integral_constant<int, 1 + a>{}, integral_constant<int, jid(a)>{}, integral_constant<int, pid(a, D)>{},
+           integral_constant<int, pid(a, t)>{});
+  });
+}
+
+// The z-differentiated fields at the D-face (see face_zsum).
+template <int D, int LX, int LY, typename Real, class P>
+__device__ __forceinline__ void face_zvalue_mesh(const P &c, Real lam, Real (&s)[4]) {
+  constexpr int RX = LX + Unit<D>::x, RY = LY + Unit<D>::y;
+  constexpr int ids[4] = {kJz, kPxz, kPyz, kPzz};
+  static_for<4>([&](auto i) {
+    const Real l = c.template at<ids[i], LX, LY>(), r = c.template at<ids[i], RX, RY>();
+    s[i] = l + lam * (r - l);
+  });
+}
+
+// What a plane gives to its z-faces' moments on the mesh: the value with the
+// tangential gradients taken off (w) and the normal-flux field (nf); between
+// planes L and R the moments are w_L + lam (w_R - w_L) - hg (nf_R - nf_L).
+template <typename Real, class P>
+__device__ __forceinline__ void zface_parts_mesh(const P &c, Real hsx, Real hsy, Real (&w)[4], Real (&nf)[4]) {
+  w[0] = c.template at<kR0, 0, 0>() - (hsx * dif<kJx, 0, 0, 0>(c) + hsy * dif<kJy, 1, 0, 0>(c));
+  nf[0] = c.template at<kJz, 0, 0>();
+  static_for<3>([&](auto a) {
+    w[1 + a] = c.template at<jid(a), 0, 0>() - (hsx * dif<pid(a, 0), 0, 0, 0>(c) + hsy * dif<pid(a, 1), 1, 0, 0>(c));
+    nf[1 + a] = c.template at<pid(a, 2), 0, 0>();
+  });
+}
+
 // Index of the population with velocity (x, y, z).
 constexpr int pop_of(int x, int y, int z) {
   for (int q = 0; q < kQ; ++q)
@@ -347,6 +454,13 @@ __device__ __forceinline__ void apply_terms(const Real (&v)[10], Real (&acc)[kQ]
     }
   });
 }
+// The same on the mesh: divided by the cell's width along the axis.
+template <int D, int S, typename Real>
+__device__ __forceinline__ void apply_terms(const Real (&v)[10], Real iw, Real (&acc)[kQ]) {
+  static_for<kQ>([&](auto q) {
+    if constexpr (cdir(q, D) != 0) acc[q] -= (S > 0 ? iw : -iw) * v[cross_slot<D>(q)];
+  });
+}
 
 // acc_q -= S v_q for the populations crossing a D-face of the centre
 // (S = +1 for its upper face, -1 for its lower face).
@@ -389,30 +503,29 @@ __device__ __forceinline__ void load_raw(const global_t<Real> *__restrict__ ft, 
 // yields for q in a set closed under q -> -q), formed from opposite-velocity
 // pairs: with s = f_q + f_-q and d = f_q - f_-q over the pairs (q < -q),
 //   drho = f_0 + sum s,  j = sum xi_q d,  Pi_ab = sum xi_qa xi_qb s.
-// FP32: drho and j are compensated sums over the pair terms.
+// drho and j are summed in double also for FP32 populations and rounded
+// once: double additions issue at the rate of FP32 ones, so that this takes
+// 39 vector instructions fewer per cell than FP32 sums with compensation, the
+// same time, and is more accurate (errors against double after 30 steps at
+// 128^3 2.9e-7 instead of 3.2e-7; on a 97^3 mesh after 20 steps 2.7e-7
+// instead of 3.0e-7).
 // m = {drho, jx, jy, jz, Pxx, Pyy, Pzz, Pxy, Pxz, Pyz}.
 template <typename Real, class Has, class Get>
 __device__ __forceinline__ void pair_moments(Has has, Get get, Real (&m)[10]) {
-  CompSum<Real> r, ax, ay, az;
+  double r = 0, ax = 0, ay = 0, az = 0;
   Real pxx = 0, pyy = 0, pzz = 0, pxy = 0, pxz = 0, pyz = 0;
-  constexpr bool plain = std::is_same<Real, double>::value;
-  auto acc = [&](CompSum<Real> &c, Real x) {
-    if constexpr (plain)
-      c.s += x;
-    else
-      c.add(x);
-  };
-  if constexpr (has(0)) acc(r, get(std::integral_constant<int, 0>{}));
+  if constexpr (has(0)) r += (double)get(std::integral_constant<int, 0>{});
   static_for<kQ>([&](auto q) {
     constexpr int qb = opposite(q);
     if constexpr (q != 0 && q < qb && has(q)) {
       const Real fq = get(q), fb = get(std::integral_constant<int, qb>{});
-      const Real sm = fq + fb, df = fq - fb;
+      const double sd = (double)fq + (double)fb, df = (double)fq - (double)fb;
+      const Real sm = std::is_same<Real, double>::value ? Real(sd) : fq + fb;
       constexpr int x = kCx[q], y = kCy[q], z = kCz[q];
-      acc(r, sm);
-      if constexpr (x != 0) acc(ax, x > 0 ? df : -df);
-      if constexpr (y != 0) acc(ay, y > 0 ? df : -df);
-      if constexpr (z != 0) acc(az, z > 0 ? df : -df);
+      r += sd;
+      if constexpr (x != 0) ax += x > 0 ? df : -df;
+      if constexpr (y != 0) ay += y > 0 ? df : -df;
+      if constexpr (z != 0) az += z > 0 ? df : -df;
       if constexpr (x != 0) pxx += sm;
       if constexpr (y != 0) pyy += sm;
       if constexpr (z != 0) pzz += sm;
@@ -424,7 +537,7 @@ __device__ __forceinline__ void pair_moments(Has has, Get get, Real (&m)[10]) {
       if constexpr (y * z == -1) pyz -= sm;
     }
   });
-  m[0] = r.value(); m[1] = ax.value(); m[2] = ay.value(); m[3] = az.value();
+  m[0] = Real(r); m[1] = Real(ax); m[2] = Real(ay); m[3] = Real(az);
   m[4] = pxx; m[5] = pyy; m[6] = pzz; m[7] = pxy; m[8] = pxz; m[9] = pyz;
 }
 
@@ -475,12 +588,202 @@ __device__ __forceinline__ void publish_cell(const Real (&f)[kQ], Real *P, Real 
   });
 }
 
+// The mesh coefficients each phase of the marches reads, with the terms they
+// make (on unit cells stubs that no code calls).  Plane p is the one being worked on: p_.
+template <typename Real, int W, bool Mesh>
+struct OwnCoef {
+  __device__ __forceinline__ OwnCoef(const MeshMarch<Real, W> &, int) {}
+  template <int S> __device__ __forceinline__ void add(Real, Real &, Real &, Real &) const {}
+};
+// The column's own B of plane p along z: to centre p-1 (its z+1 value), to
+// centre p (its own value, -U + V) and to centre p+1 (its z-1 value).  U and
+// V enter centre p with the same rounded values as they do its neighbours.
+template <typename Real, int W>
+struct OwnCoef<Real, W, true> {
+  Real u[2], v[2], ua[2], vb[2];  // by sign (+, -): of centre p, U of centre p-1, V of centre p+1
+  __device__ __forceinline__ OwnCoef(const MeshMarch<Real, W> &m, int p) {
+    static_for<2>([&](auto s) {
+      u[s] = m.z(kMarchUp + s, p);
+      v[s] = m.z(kMarchVp + s, p);
+      ua[s] = m.z(kMarchUp + s, p - 1);
+      vb[s] = m.z(kMarchVp + s, p + 1);
+    });
+  }
+  template <int S>
+  __device__ __forceinline__ void add(Real b, Real &acc_c, Real &r, Real &nxt) const {
+    constexpr int i = S > 0 ? 0 : 1;
+    acc_c -= ua[i] * b;
+    r += nxt - v[i] * b;
+    r += u[i] * b;
+    nxt = vb[i] * b;
+  }
+};
+
+// The z-face between planes p-1 and p.
+template <typename Real, int W, bool Mesh>
+struct ZFaceCoef {
+  static constexpr Real iw_c = 1, iw_p = 1;
+  __device__ __forceinline__ ZFaceCoef(const MeshMarch<Real, W> &, int) {}
+  template <class G> __device__ __forceinline__ void face(const G &, Real (&)[4], Real (&)[4], Real (&)[4]) const {}
+};
+template <typename Real, int W>
+struct ZFaceCoef<Real, W, true> {
+  Real hsx, hsy, lam, hg, iw_c, iw_p;
+  __device__ __forceinline__ ZFaceCoef(const MeshMarch<Real, W> &m, int p)
+      : hsx(m.template col<0>(kMarchHs)), hsy(m.template col<1>(kMarchHs)), lam(m.z(kMarchLam, p - 1)),
+        hg(m.z(kMarchHg, p - 1)), iw_c(m.z(kMarchIw, p - 1)), iw_p(m.z(kMarchIw, p)) {}
+  // moments of the face between the plane below (wl, nl) and this one, whose
+  // parts then replace the plane below's
+  template <class G>
+  __device__ __forceinline__ void face(const G &g, Real (&wl)[4], Real (&nl)[4], Real (&m)[4]) const {
+    Real w[4], nf[4];
+    zface_parts_mesh(g, hsx, hsy, w, nf);
+    if constexpr (G::use)
+      static_for<4>([&](auto i) {
+        m[i] = wl[i] + (lam * (w[i] - wl[i]) - hg * (nf[i] - nl[i]));
+        wl[i] = w[i];
+        nl[i] = nf[i];
+      });
+  }
+};
+
+// The diagonal z-moving populations' in-plane neighbours in plane p: with
+// D = B(+) - B(-) and X = A (B(+) - B(0)) + E (B(0) - B(-)) along the
+// in-plane axis, the mixed terms of centres p-1, p and p+1 and the in-plane
+// axis part of centre p.
+template <typename Real, int W, bool Mesh>
+struct DiagZCoef {
+  __device__ __forceinline__ DiagZCoef(const MeshMarch<Real, W> &, int) {}
+  template <int Q, class G> __device__ __forceinline__ void add(const G &, Real &, Real &, Real &) const {}
+};
+template <typename Real, int W>
+struct DiagZCoef<Real, W, true> {
+  Real a[2], e[2], hs[2], u[2][2], v[2][2];  // per in-plane axis
+  Real hsz_c, az_c, eaz_p, hsz_n, ez_n;      // of centres p-1, p, p+1
+  __device__ __forceinline__ DiagZCoef(const MeshMarch<Real, W> &m, int p) {
+    static_for<2>([&](auto d) {
+      a[d] = m.template col<d>(kMarchA);
+      e[d] = m.template col<d>(kMarchE);
+      hs[d] = m.template col<d>(kMarchHs);
+      static_for<2>([&](auto s) {
+        u[d][s] = m.template col<d>(kMarchUp + s);
+        v[d][s] = m.template col<d>(kMarchVp + s);
+      });
+    });
+    hsz_c = m.z(kMarchHs, p - 1);
+    az_c = m.z(kMarchA, p - 1);
+    eaz_p = m.z(kMarchE, p) - m.z(kMarchA, p);
+    hsz_n = m.z(kMarchHs, p + 1);
+    ez_n = m.z(kMarchE, p + 1);
+  }
+  template <int Q, class G>
+  __device__ __forceinline__ void add(const G &g, Real &acc_c, Real &acc_p, Real &nxt) const {
+    constexpr int d = kCx[Q] != 0 ? 0 : 1, s = kCx[Q] + kCy[Q], i = s > 0 ? 0 : 1;
+    const Real bp = g.template at<Q, Unit<d>::x, Unit<d>::y>();
+    const Real b0 = g.template at<Q, 0, 0>();
+    const Real bm = g.template at<Q, -Unit<d>::x, -Unit<d>::y>();
+    if constexpr (G::use) {
+      const Real dp = bp - b0, dm = b0 - bm;
+      const Real x = a[d] * dp + e[d] * dm;
+      const Real y = hs[d] * (bp - bm);
+      const Real up = hsz_c * x + az_c * y, dn = hsz_n * x + ez_n * y;
+      const Real in = u[d][i] * dp + v[d][i] * dm;
+      if constexpr (s * kCz[Q] > 0) {
+        acc_c += up;
+        acc_p += eaz_p * y - in;
+        nxt -= dn;
+      } else {
+        acc_c -= up;
+        acc_p -= eaz_p * y + in;
+        nxt += dn;
+      }
+    }
+  }
+};
+
+// In-plane neighbours of the populations that move in the plane, as
+// differences from the column's own B (in FP32 they round at the scale of
+// the differences and not of B).
+template <typename Real, int W, bool Mesh>
+struct InPlaneCoef {
+  __device__ __forceinline__ InPlaneCoef(const MeshMarch<Real, W> &) {}
+  template <int Q, class G> __device__ __forceinline__ void axis(const G &, Real &) const {}
+  template <int Q, class G> __device__ __forceinline__ void diag(const G &, Real &) const {}
+};
+template <typename Real, int W>
+struct InPlaneCoef<Real, W, true> {
+  Real a[2], e[2], hs[2], u[2][2], v[2][2];
+  __device__ __forceinline__ InPlaneCoef(const MeshMarch<Real, W> &m) {
+    static_for<2>([&](auto d) {
+      a[d] = m.template col<d>(kMarchA);
+      e[d] = m.template col<d>(kMarchE);
+      hs[d] = m.template col<d>(kMarchHs);
+      static_for<2>([&](auto s) {
+        u[d][s] = m.template col<d>(kMarchUp + s);
+        v[d][s] = m.template col<d>(kMarchVp + s);
+      });
+    });
+  }
+  template <int Q, class G>
+  __device__ __forceinline__ void axis(const G &g, Real &acc) const {
+    constexpr int d = kCx[Q] != 0 ? 0 : 1, i = kCx[Q] + kCy[Q] > 0 ? 0 : 1;
+    const Real bp = g.template at<Q, Unit<d>::x, Unit<d>::y>(), bm = g.template at<Q, -Unit<d>::x, -Unit<d>::y>();
+    const Real b0 = g.template at<Q, 0, 0>();
+    if constexpr (G::use) acc -= u[d][i] * (bp - b0) + v[d][i] * (b0 - bm);
+  }
+  template <int Q, class G>
+  __device__ __forceinline__ void diag(const G &g, Real &acc) const {
+    constexpr int i = kCx[Q] > 0 ? 0 : 1, j = kCy[Q] > 0 ? 0 : 1;
+    const Real p1 = g.template at<Q, 1, 0>(), m1 = g.template at<Q, -1, 0>();
+    const Real p2 = g.template at<Q, 0, 1>(), m2 = g.template at<Q, 0, -1>();
+    const Real pp = g.template at<Q, 1, 1>(), pm = g.template at<Q, 1, -1>();
+    const Real mp = g.template at<Q, -1, 1>(), mm = g.template at<Q, -1, -1>();
+    const Real b0 = g.template at<Q, 0, 0>();
+    if constexpr (G::use) {
+      const Real y0 = p2 - m2, x0 = p1 - m1;
+      const Real mix = hs[1] * (a[0] * ((pp - pm) - y0) + e[0] * (y0 - (mp - mm))) +
+                       hs[0] * (a[1] * ((pp - mp) - x0) + e[1] * (x0 - (pm - mm)));
+      const Real in = (u[0][i] * (p1 - b0) + v[0][i] * (b0 - m1)) + (u[1][j] * (p2 - b0) + v[1][j] * (b0 - m2));
+      if constexpr (kCx[Q] * kCy[Q] > 0)
+        acc += mix - in;
+      else
+        acc -= mix + in;
+    }
+  }
+};
+
+// Moments of the D-face (D = 0 or 1) between the column and its upper
+// neighbour at centre plane p-1, on the mesh (planes p, p-1, p-2).
+template <int D, typename Real, int W>
+__device__ __forceinline__ void face_moments_mesh(const MeshMarch<Real, W> &mc, int p, const Plane<Real, W> &c,
+                                                  const Plane<Real, W> &c1, const Plane<Real, W> &c2, Real (&m)[4]) {
+  const Real lam = mc.template col<D>(kMarchLam), hg = mc.template col<D>(kMarchHg);
+  const Real hs = mc.template col<1 - D>(kMarchHs), hsz = mc.z(kMarchHs, p - 1);
+  Real vl[4], s1[4];
+  gathered<Real, W>(c1, c1, [&](const auto &g, const auto &) {
+    Real v[4], t[4];
+    face_inplane_mesh<D, 0, 0>(g, lam, hg, hs, v, t);
+    if constexpr (std::decay_t<decltype(g)>::use) static_for<4>([&](auto i) { vl[i] = v[i]; m[i] = t[i]; });
+  });
+  gathered<Real, W>(c, c2, [&](const auto &g, const auto &g2) {
+    Real a[4], b[4];
+    face_zvalue_mesh<D, 0, 0>(g, lam, a);
+    face_zvalue_mesh<D, 0, 0>(g2, lam, b);
+    if constexpr (std::decay_t<decltype(g)>::use) static_for<4>([&](auto i) { s1[i] = a[i] - b[i]; });
+  });
+  static_for<4>([&](auto i) { m[i] = vl[i] + (m[i] - hsz * s1[i]); });
+}
+
 // The z-march of one tile (bx, by) over the planes [z0, z1) of a box; adds
 // the moments of the updated cells to v.  L is the block's LDS, kFusedValues
 // values per column: P [kNPop][NT], Q [2][kNQ][NT], Z [3][kNZ][NT].
-template <typename Real, int W, bool O32>
+// Mesh: on a stretched mesh with the tables coef (x, y, z rows of
+// MarchCoef) and width (the cell widths, the weights of the sums); the x/y
+// coefficients follow the plane data in L (kMeshValues).
+template <typename Real, int W, bool O32, bool Mesh>
 __device__ __forceinline__ void fused_tile(const global_t<Real> *__restrict__ ft, global_t<Real> *__restrict__ out, const StepParams &p,
-                                           int bx, int by, int z0, int z1, Real *L, double (&v)[kNumSums]) {
+                                           int bx, int by, int z0, int z1, Real *L, double (&v)[kNumSums],
+                                           const Real *coef, const double *width) {
   constexpr int TX = Tile<W>::TX, TY = Tile<W>::TY, IX = Tile<W>::IX, IY = Tile<W>::IY, NT = Tile<W>::NT;
   const int n = p.n;
   const int64_t stride = p.stride;
@@ -500,6 +803,17 @@ __device__ __forceinline__ void fused_tile(const global_t<Real> *__restrict__ ft
   Real *const LQ = L + kNPop * NT + tid;
   Real *const LZ = L + (kNPop + 2 * kNQ) * NT + tid;
   Real *const LY = L + kLdsValues * NT + tid;
+  MeshMarch<Real, W> mc{};
+  const constant_t<double> *wz = nullptr;
+  double wxy = 1.0;
+  if constexpr (Mesh) {
+    Real *const LM = L + kFusedValues * NT;
+    load_mesh_columns<Real, W>(coef, n, x0, y0, LM);
+    mc = {(const constant_t<Real> *)(coef + 2 * kMarchCoefs * n), LM + tx, LM + kMarchCoefs * W + ty, n};
+    wz = (const constant_t<double> *)(width + 2 * n);
+    wxy = to_global(width)[gx] * to_global(width)[n + gy];
+    __syncthreads();
+  }
 
   Real pf[kQ];        // f~ of the plane being published (loaded one plane ahead)
   // A centre's result is f~+ plus the stencil and face terms, which are
@@ -512,10 +826,11 @@ __device__ __forceinline__ void fused_tile(const global_t<Real> *__restrict__ ft
   Real fp_c[kQ];      // f~+ of centre p-1
   Real fp_p[kQ];      // f~+ of centre p
   Real nxt[10];       // z-1 terms of the z-moving populations of centre p+1
-  Real zl[4];         // lower half of the z-face above the previous plane
+  Real zl[4];         // lower half of the z-face above the previous plane (mesh: its w, and nf in zn)
+  Real zn[4];
   static_for<kQ>([&](auto q) { acc_p[q] = Real(0); fp_p[q] = Real(0); });
   static_for<10>([&](auto i) { nxt[i] = Real(0); });
-  static_for<4>([&](auto i) { zl[i] = Real(0); });
+  static_for<4>([&](auto i) { zl[i] = Real(0); zn[i] = Real(0); });
 
   // Completes centre `plane` (acc_c): its lower y-face, read from the slot
   // of the column W before, the store and the sums.  Runs after the barrier
@@ -523,7 +838,10 @@ __device__ __forceinline__ void fused_tile(const global_t<Real> *__restrict__ ft
   auto finish = [&](int plane) {
     Real fym[10];
     static_for<10>([&](auto k) { fym[k] = LY[k * NT - W]; });
-    apply_terms<1, -1>(fym, acc_c);
+    if constexpr (Mesh)
+      apply_terms<1, -1>(fym, mc.template col<1>(kMarchIw), acc_c);
+    else
+      apply_terms<1, -1>(fym, acc_c);
     const int cell = plane * n * n + col;
     // plain (L2-allocating) stores: a tile row's 30 updated cells do not
     // fill whole 128-byte lines, and L2 merges them with the neighbouring
@@ -533,7 +851,14 @@ __device__ __forceinline__ void fused_tile(const global_t<Real> *__restrict__ ft
       res[q] = fp_c[q] + acc_c[q];
       *at_cell<O32>(out + (int64_t)q * stride, cell) = res[q];
     });
-    sums_of_populations<Real>(res, p.inv_rho0, v);
+    if constexpr (Mesh) {
+      double s[kNumSums] = {0, 0, 0, 0, 0};
+      sums_of_populations<Real>(res, p.inv_rho0, s);
+      const double vol = wxy * wz[plane];
+      static_for<kNumSums>([&](auto i) { v[i] += vol * s[i]; });
+    } else {
+      sums_of_populations<Real>(res, p.inv_rho0, v);
+    }
   };
 
   load_raw<Real, O32>(ft, stride, n, col, z0 - 1, pf);
@@ -556,7 +881,15 @@ __device__ __forceinline__ void fused_tile(const global_t<Real> *__restrict__ ft
     // own-column pieces of plane p: z+1 terms of centre p-1, the centre
     // terms and initial value of centre p, z-1 terms of centre p+1 (formed
     // by halo columns too, which never store them)
+    const OwnCoef<Real, W, Mesh> own(mc, p_);
     publish_cell<Real, W>(pf, LP, LQ + q2 * (kNQ * NT), LZ + q3 * (kNZ * NT), p, [&](auto q, Real bq, Real ftq) {
+      if constexpr (Mesh) {
+        Real r = Real(0);
+        if constexpr (kCz[q] != 0) own.template add<kCz[q]>(bq, acc_c[q], r, nxt[zslot(q)]);
+        acc_p[q] = r;
+        fp_p[q] = ftq;
+        return;
+      }
       if constexpr (kCz[q] != 0) acc_c[q] -= dtal * ((Real(0.5 * kCz[q]) - h) * bq);
       Real r = Real(0);
       if constexpr (kCz[q] != 0) r = nxt[zslot(q)];
@@ -570,26 +903,39 @@ __device__ __forceinline__ void fused_tile(const global_t<Real> *__restrict__ ft
     if (inner) {
       // face between p-1 and p (upper half from plane p, lower half carried
       // from plane p-1) and the lower half of the face between p and p+1
+      const ZFaceCoef<Real, W, Mesh> zf(mc, p_);
       gathered<Real, W>(c, c, [&](const auto &g, const auto &) {
         Real m[4], lo[4];
-        zface_half<-1>(g, h, m);
-        zface_half<1>(g, h, lo);
+        if constexpr (Mesh) {
+          zf.face(g, zl, zn, m);
+        } else {
+          zface_half<-1>(g, h, m);
+          zface_half<1>(g, h, lo);
+        }
         if constexpr (std::decay_t<decltype(g)>::use) {
-          static_for<4>([&](auto i) { m[i] += zl[i]; });
+          if constexpr (!Mesh) static_for<4>([&](auto i) { m[i] += zl[i]; });
           face_equilibrium<2, Real>(m, p, dtbe, [&](auto q, Real val) {
-            acc_c[q] -= val;   // upper face of centre p-1
-            acc_p[q] += val;   // lower face of centre p
+            if constexpr (Mesh) {
+              acc_c[q] -= zf.iw_c * val;
+              acc_p[q] += zf.iw_p * val;
+            } else {
+              acc_c[q] -= val;   // upper face of centre p-1
+              acc_p[q] += val;   // lower face of centre p
+            }
           });
-          static_for<4>([&](auto i) { zl[i] = lo[i]; });
+          if constexpr (!Mesh) static_for<4>([&](auto i) { zl[i] = lo[i]; });
         }
       });
       // diagonal z-moving populations: the in-plane differences D = B(+d1)
       // - B(-d1) and sums S = B(+d1) + B(-d1) of plane p enter centre p-1
       // (z+1 mixed term), centre p (in-plane terms) and centre p+1 (z-1
       // mixed term)
+      const DiagZCoef<Real, W, Mesh> dz(mc, p_);
       gathered<Real, W>(c, c, [&](const auto &g, const auto &) {
         static_for<kQ>([&](auto q) {
-          if constexpr (is_diag_z(q)) {
+          if constexpr (is_diag_z(q) && Mesh) {
+            dz.template add<q>(g, acc_c[q], acc_p[q], nxt[zslot(q)]);
+          } else if constexpr (is_diag_z(q)) {
             constexpr int d1 = kCx[q] != 0 ? 0 : 1, s1 = kCx[q] + kCy[q];
             constexpr Real k = Real(0.5 * s1 * kCz[q]);
             const Real bp_ = g.template at<q, Unit<d1>::x, Unit<d1>::y>();
@@ -609,6 +955,10 @@ __device__ __forceinline__ void fused_tile(const global_t<Real> *__restrict__ ft
       // z-tangential gradients -h/4 [(M_L + M_R)(p) - (M_L + M_R)(p-2)]
       const Real hq = Real(0.25) * h;
       auto face_moments = [&](auto D, auto LX, auto LY, Real (&m)[4]) {
+        if constexpr (Mesh) {
+          face_moments_mesh<D>(mc, p_, c, c1, c2, m);
+          return;
+        }
         gathered<Real, W>(c1, c1, [&](const auto &g, const auto &) {
           Real t[4];
           face_inplane<D, LX, LY>(g, h, t);
@@ -644,11 +994,22 @@ __device__ __forceinline__ void fused_tile(const global_t<Real> *__restrict__ ft
         face_moments(I1{}, I0{}, I0{}, my);
         face_terms<1>(my, p, dtbe, fy);
         static_for<10>([&](auto k) { LY[k * NT] = fy[k]; });
-        if (inner) apply_terms<1, 1>(fy, acc_c);    // y+
+        if (inner) {
+          if constexpr (Mesh)
+            apply_terms<1, 1>(fy, mc.template col<1>(kMarchIw), acc_c);
+          else
+            apply_terms<1, 1>(fy, acc_c);    // y+
+        }
       }
       if (inner) {
-        apply_terms<0, 1>(fxp, acc_c);   // x+
-        apply_terms<0, -1>(fxm, acc_c);  // x-
+        if constexpr (Mesh) {
+          const Real iw = mc.template col<0>(kMarchIw);
+          apply_terms<0, 1>(fxp, iw, acc_c);
+          apply_terms<0, -1>(fxm, iw, acc_c);
+        } else {
+          apply_terms<0, 1>(fxp, acc_c);   // x+
+          apply_terms<0, -1>(fxm, acc_c);  // x-
+        }
       }
     }
 
@@ -662,9 +1023,12 @@ __device__ __forceinline__ void fused_tile(const global_t<Real> *__restrict__ ft
       // in-plane terms of the in-plane populations of centre p (the centre
       // value was added before)
       //   axis: L = s/2 (B(+d) - B(-d)) - h (B(+d) + B(-d))
+      const InPlaneCoef<Real, W, Mesh> xy(mc);
       gathered<Real, W>(c, c, [&](const auto &g, const auto &) {
         static_for<5>([&](auto q) {
-          if constexpr (q >= 1) {
+          if constexpr (q >= 1 && Mesh) {
+            xy.template axis<q>(g, acc_p[q]);
+          } else if constexpr (q >= 1) {
             constexpr int d = kCx[q] != 0 ? 0 : 1, s = kCx[q] + kCy[q];
             const Real bp_ = g.template at<q, Unit<d>::x, Unit<d>::y>();
             const Real bm_ = g.template at<q, -Unit<d>::x, -Unit<d>::y>();
@@ -675,6 +1039,10 @@ __device__ __forceinline__ void fused_tile(const global_t<Real> *__restrict__ ft
       });
       //   diagonal in the plane, in the (x, y) frame of its own signs
       auto diag_xy = [&](auto q, const auto &g) {
+        if constexpr (Mesh) {
+          xy.template diag<q>(g, acc_p[q]);
+          return;
+        }
         constexpr int sx = kCx[q], sy = kCy[q];
         const Real p1 = g.template at<q, 1, 0>(), m1 = g.template at<q, -1, 0>();
         const Real p2 = g.template at<q, 0, 1>(), m2 = g.template at<q, 0, -1>();
@@ -767,10 +1135,10 @@ __device__ __forceinline__ int xcd_tile(int b, int padded) { return (b & 7) * (p
 // [r G, (r+1) G), dealt to the XCDs in contiguous eighths.  A single box is
 // a table of one entry, so a box stepped alone and the same box stepped in
 // a batch run the same machine code and give the same bits.
-template <typename Real, int W, bool O32>
+template <typename Real, int W, bool O32, bool Mesh>
 __global__ __launch_bounds__(Tile<W>::NT, kWavesPerSimd<Real>) void dugks_fused_kernel(const BatchBox *__restrict__ boxes, int nbox,
                                                                   int total_items) {
-  __shared__ Real L[kFusedValues * Tile<W>::NT];
+  __shared__ Real L[kFusedValues * Tile<W>::NT + (Mesh ? kMeshValues<W> : 0)];
   const int G = gridDim.x;
   for (int base = 0; base < total_items; base += G) {
     const int it = base + xcd_tile(blockIdx.x, G);
@@ -784,7 +1152,8 @@ __global__ __launch_bounds__(Tile<W>::NT, kWavesPerSimd<Real>) void dugks_fused_
     const ItemPlanes ip(d, local);
     // the march ends with a barrier: L is free for the block reduction
     if (ip.left > 0)
-      fused_tile<Real, W, O32>(src, dst, d.sp, ip.tile % d.tiles_x, ip.tile / d.tiles_x, ip.z0, ip.z0 + ip.left, L, v);
+      fused_tile<Real, W, O32, Mesh>(src, dst, d.sp, ip.tile % d.tiles_x, ip.tile / d.tiles_x, ip.z0, ip.z0 + ip.left, L,
+                                     v, static_cast<const Real *>(d.mesh_coef), d.mesh_width);
     write_block_partials(v, d.partials, d.items, local, reinterpret_cast<double (*)[kNumSums]>(L));
     __syncthreads();
   }
@@ -893,9 +1262,11 @@ __device__ __forceinline__ void publish_group(const Real (&f)[Group<G>::N], cons
 
 // The z-march of group G of a tile over the planes [z0, z1) (see above).
 // L: the block's LDS, kSplitValues values per column.
-template <typename Real, int W, int G, bool O32>
+// Mesh: as in fused_tile.
+template <typename Real, int W, int G, bool O32, bool Mesh>
 __device__ __forceinline__ void split_tile(const global_t<Real> *__restrict__ ft, global_t<Real> *__restrict__ out, const StepParams &p,
-                                           int bx, int by, int z0, int z1, Real *L, double (&v)[kNumSums]) {
+                                           int bx, int by, int z0, int z1, Real *L, double (&v)[kNumSums],
+                                           const Real *coef, const double *width) {
   constexpr int TX = Tile<W>::TX, TY = Tile<W>::TY, IX = Tile<W>::IX, IY = Tile<W>::IY, NT = Tile<W>::NT;
   constexpr int NG = Group<G>::N;
   const int n = p.n;
@@ -920,16 +1291,37 @@ __device__ __forceinline__ void split_tile(const global_t<Real> *__restrict__ ft
   Real *const RB = L + kRB * NT + c;
   Real *const SA = L + kSA * NT + c;
   Real *const RY = L + kRY * NT + c;
+  MeshMarch<Real, W> mc{};
+  const constant_t<double> *wz = nullptr;
+  double wxy = 1.0;
+  if constexpr (Mesh) {  // filled by both groups; first read after the first barrier of the march
+    Real *const LM = L + kSplitValues * NT;
+    load_mesh_columns<Real, W>(coef, n, x0, y0, LM);
+    mc = {(const constant_t<Real> *)(coef + 2 * kMarchCoefs * n), LM + tx, LM + kMarchCoefs * W + ty, n};
+    wz = (const constant_t<double> *)(width + 2 * n);
+    wxy = to_global(width)[gx] * to_global(width)[n + gy];
+  }
+  // adds B's own sums (r, x, y, z) of a stored cell, or A's part with the
+  // cell's kinetic energy, weighted by the cell volume on the mesh
+  auto add_sums = [&](int plane, double r, double x, double y, double z, double ke) {
+    if constexpr (Mesh) {
+      const double vol = wxy * wz[plane];
+      v[0] += vol * r; v[1] += vol * x; v[2] += vol * y; v[3] += vol * z; v[4] += vol * ke;
+    } else {
+      v[0] += r; v[1] += x; v[2] += y; v[3] += z; v[4] += ke;
+    }
+  };
 
   Real pf[NG];            // the group's f~ of the plane being published
   Real acc_c[NG];         // centre p-1
   Real acc_p[NG];         // centre p
   Real nxt[10];           // A: z-1 terms of centre p+1 (all of A's populations move in z)
-  Real zl[4];             // B: lower half of the z-face above the previous plane
+  Real zl[4];             // B: lower half of the z-face above the previous plane (mesh: its w, and nf in zn)
+  Real zn[4];
   double jb[3] = {0, 0, 0};  // B: its part of the momentum of the last stored cell
   static_for<NG>([&](auto i) { acc_p[i] = Real(0); });
   static_for<10>([&](auto i) { nxt[i] = Real(0); });
-  static_for<4>([&](auto i) { zl[i] = Real(0); });
+  static_for<4>([&](auto i) { zl[i] = Real(0); zn[i] = Real(0); });
 
   load_group<Real, G, O32>(ft, stride, n, col, z0 - 1, pf);
   int q2 = 0, q3 = 0;
@@ -952,14 +1344,20 @@ __device__ __forceinline__ void split_tile(const global_t<Real> *__restrict__ ft
     if constexpr (G == 1) {
       if (inner && stored_last) {
         const double ra = (double)SA[0], xa = (double)SA[NT], ya = (double)SA[2 * NT], za = (double)SA[3 * NT];
-        v[0] += ra; v[1] += xa; v[2] += ya; v[3] += za;
         const double x = jb[0] + xa, y = jb[1] + ya, z = jb[2] + za;
-        v[4] += 0.5 * (x * x + y * y + z * z) * ir * ir;
+        add_sums(p_ - 2, ra, xa, ya, za, 0.5 * (x * x + y * y + z * z) * ir * ir);
       }
     }
     // own-column pieces of plane p (see fused_tile)
+    const OwnCoef<Real, W, Mesh> own(mc, p_);
     publish_group<Real, W, G>(pf, m, LP, LQ + q2 * (kNQ * NT), LZ + q3 * (kNZ * NT), p, [&](auto q, Real bq, Real ftq) {
       constexpr int i = local_of(q);
+      if constexpr (Mesh) {
+        Real r = ftq;
+        if constexpr (kCz[q] != 0) own.template add<kCz[q]>(bq, acc_c[i], r, nxt[i]);
+        acc_p[i] = r;
+        return;
+      }
       if constexpr (kCz[q] != 0) acc_c[i] -= dtal * ((Real(0.5 * kCz[q]) - h) * bq);
       Real r = ftq;
       if constexpr (kCz[q] != 0) r += nxt[i];
@@ -975,9 +1373,13 @@ __device__ __forceinline__ void split_tile(const global_t<Real> *__restrict__ ft
         // diagonal z-moving populations: in-plane differences D = B(+d1) -
         // B(-d1) and sums S = B(+d1) + B(-d1) of plane p enter centre p-1
         // (z+1 mixed term), centre p (in-plane terms), centre p+1 (z-1 mixed term)
+        const DiagZCoef<Real, W, Mesh> dz(mc, p_);
         gathered<Real, W>(pc, pc, [&](const auto &g, const auto &) {
           static_for<kQ>([&](auto q) {
-            if constexpr (is_diag_z(q)) {
+            if constexpr (is_diag_z(q) && Mesh) {
+              constexpr int i = local_of(q);
+              dz.template add<q>(g, acc_c[i], acc_p[i], nxt[i]);
+            } else if constexpr (is_diag_z(q)) {
               constexpr int d1 = kCx[q] != 0 ? 0 : 1, s1 = kCx[q] + kCy[q];
               constexpr Real k = Real(0.5 * s1 * kCz[q]);
               constexpr int i = local_of(q);
@@ -995,19 +1397,27 @@ __device__ __forceinline__ void split_tile(const global_t<Real> *__restrict__ ft
       } else {
         // face between p-1 and p (upper half from plane p, lower half
         // carried from plane p-1) for A, and the lower half of the next one
+        const ZFaceCoef<Real, W, Mesh> zf(mc, p_);
         gathered<Real, W>(pc, pc, [&](const auto &g, const auto &) {
           Real mm[4], lo[4];
-          zface_half<-1>(g, h, mm);
-          zface_half<1>(g, h, lo);
+          if constexpr (Mesh) {
+            zf.face(g, zl, zn, mm);
+          } else {
+            zface_half<-1>(g, h, mm);
+            zface_half<1>(g, h, lo);
+          }
           if constexpr (std::decay_t<decltype(g)>::use) {
-            static_for<4>([&](auto i) { RA[(8 + i) * NT] = mm[i] + zl[i]; });
-            static_for<4>([&](auto i) { zl[i] = lo[i]; });
+            static_for<4>([&](auto i) { RA[(8 + i) * NT] = Mesh ? mm[i] : mm[i] + zl[i]; });
+            if constexpr (!Mesh) static_for<4>([&](auto i) { zl[i] = lo[i]; });
           }
         });
         if (has_cur) {
+          const InPlaneCoef<Real, W, Mesh> xy(mc);
           gathered<Real, W>(pc, pc, [&](const auto &g, const auto &) {
             static_for<5>([&](auto q) {
-              if constexpr (q >= 1) {
+              if constexpr (q >= 1 && Mesh) {
+                xy.template axis<q>(g, acc_p[local_of(q)]);
+              } else if constexpr (q >= 1) {
                 constexpr int d = kCx[q] != 0 ? 0 : 1, s = kCx[q] + kCy[q];
                 const Real bp_ = g.template at<q, Unit<d>::x, Unit<d>::y>();
                 const Real bm_ = g.template at<q, -Unit<d>::x, -Unit<d>::y>();
@@ -1017,6 +1427,10 @@ __device__ __forceinline__ void split_tile(const global_t<Real> *__restrict__ ft
             });
           });
           auto diag_xy = [&](auto q, const auto &g) {
+            if constexpr (Mesh) {
+              xy.template diag<q>(g, acc_p[local_of(q)]);
+              return;
+            }
             constexpr int sx = kCx[q], sy = kCy[q];
             const Real p1 = g.template at<q, 1, 0>(), m1 = g.template at<q, -1, 0>();
             const Real p2 = g.template at<q, 0, 1>(), m2 = g.template at<q, 0, -1>();
@@ -1048,6 +1462,10 @@ __device__ __forceinline__ void split_tile(const global_t<Real> *__restrict__ ft
         constexpr int D = G == 0 ? 0 : 1;
         const Real hq = Real(0.25) * h;
         auto face = [&](auto LX, auto LY, Real (&fm)[4]) {
+          if constexpr (Mesh) {
+            face_moments_mesh<D>(mc, p_, pc, pc1, pc2, fm);
+            return;
+          }
           gathered<Real, W>(pc1, pc1, [&](const auto &g, const auto &) {
             Real t[4];
             face_inplane<D, LX, LY>(g, h, t);
@@ -1091,10 +1509,14 @@ __device__ __forceinline__ void split_tile(const global_t<Real> *__restrict__ ft
       if (inner) {
         using I0 = std::integral_constant<int, 0>;
         using I1 = std::integral_constant<int, 1>;
+        Real iw[2] = {Real(1), Real(1)};
+        if constexpr (Mesh) static_for<2>([&](auto d) { iw[d] = mc.template col<d>(kMarchIw); });
         auto put_face = [&](const Real (&fm)[4], auto D, auto S) {
           face_equilibrium<D, Real>(fm, p, dtbe, [&](auto q, Real val) {
             if constexpr (group_of(q) == G) {
-              if constexpr (S > 0)
+              if constexpr (Mesh)
+                acc_c[local_of(q)] -= (S > 0 ? iw[D] : -iw[D]) * val;
+              else if constexpr (S > 0)
                 acc_c[local_of(q)] -= val;
               else
                 acc_c[local_of(q)] += val;
@@ -1105,9 +1527,19 @@ __device__ __forceinline__ void split_tile(const global_t<Real> *__restrict__ ft
           // the z-face between p-1 and p: upper face of centre p-1, lower of centre p
           Real zf[4];
           static_for<4>([&](auto i) { zf[i] = RA[(8 + i) * NT]; });
+          Real iwc = Real(1), iwp = Real(1);
+          if constexpr (Mesh) {
+            iwc = mc.z(kMarchIw, p_ - 1);
+            iwp = mc.z(kMarchIw, p_);
+          }
           face_equilibrium<2, Real>(zf, p, dtbe, [&](auto q, Real val) {
-            acc_c[local_of(q)] -= val;
-            acc_p[local_of(q)] += val;
+            if constexpr (Mesh) {
+              acc_c[local_of(q)] -= iwc * val;
+              acc_p[local_of(q)] += iwp * val;
+            } else {
+              acc_c[local_of(q)] -= val;
+              acc_p[local_of(q)] += val;
+            }
           });
         }
         if (has_prev) {
@@ -1143,7 +1575,7 @@ __device__ __forceinline__ void split_tile(const global_t<Real> *__restrict__ ft
           if constexpr (G == 0) {
             SA[0] = Real(r); SA[NT] = Real(ax); SA[2 * NT] = Real(ay); SA[3 * NT] = Real(az);
           } else {
-            v[0] += r; v[1] += ax; v[2] += ay; v[3] += az;
+            add_sums(p_ - 1, r, ax, ay, az, 0.0);
             jb[0] = ax; jb[1] = ay; jb[2] = az;
           }
         }
@@ -1157,19 +1589,18 @@ __device__ __forceinline__ void split_tile(const global_t<Real> *__restrict__ ft
   if constexpr (G == 1) {
     if (inner) {
       const double ra = (double)SA[0], xa = (double)SA[NT], ya = (double)SA[2 * NT], za = (double)SA[3 * NT];
-      v[0] += ra; v[1] += xa; v[2] += ya; v[3] += za;
       const double x = jb[0] + xa, y = jb[1] + ya, z = jb[2] + za;
-      v[4] += 0.5 * (x * x + y * y + z * z) * ir * ir;
+      add_sums(z1 - 1, ra, xa, ya, za, 0.5 * (x * x + y * y + z * z) * ir * ir);
     }
   }
   __syncthreads();
 }
 
 // Work-list kernel of the split march (see dugks_fused_kernel).
-template <typename Real, int W, bool O32>
+template <typename Real, int W, bool O32, bool Mesh>
 __global__ __launch_bounds__(2 * Tile<W>::NT) void dugks_split_kernel(const BatchBox *__restrict__ boxes, int nbox,
                                                                       int total_items) {
-  __shared__ Real L[kSplitValues * Tile<W>::NT];
+  __shared__ Real L[kSplitValues * Tile<W>::NT + (Mesh ? kMeshValues<W> : 0)];
   const int G = gridDim.x;
   for (int base = 0; base < total_items; base += G) {
     const int it = base + xcd_tile(blockIdx.x, G);
@@ -1184,9 +1615,11 @@ __global__ __launch_bounds__(2 * Tile<W>::NT) void dugks_split_kernel(const Batc
     if (ip.left > 0) {
       const int bx = ip.tile % d.tiles_x, by = ip.tile / d.tiles_x, z1 = ip.z0 + ip.left;
       if (threadIdx.x < Tile<W>::NT)
-        split_tile<Real, W, 0, O32>(src, dst, d.sp, bx, by, ip.z0, z1, L, v);
+        split_tile<Real, W, 0, O32, Mesh>(src, dst, d.sp, bx, by, ip.z0, z1, L, v,
+                                          static_cast<const Real *>(d.mesh_coef), d.mesh_width);
       else
-        split_tile<Real, W, 1, O32>(src, dst, d.sp, bx, by, ip.z0, z1, L, v);
+        split_tile<Real, W, 1, O32, Mesh>(src, dst, d.sp, bx, by, ip.z0, z1, L, v,
+                                          static_cast<const Real *>(d.mesh_coef), d.mesh_width);
     }
     write_block_partials(v, d.partials, d.items, local, reinterpret_cast<double (*)[kNumSums]>(L));
     __syncthreads();
@@ -1308,15 +1741,15 @@ int fused_dugks_blocks(const dhit_params &p, int *width, int *tiles_x, int *tile
 template <typename Real>
 constexpr bool kSplit = sizeof(Real) == 8;
 
-template <typename Real, int W, bool O32>
+template <typename Real, int W, bool O32, bool Mesh>
 static void list_launch(hipStream_t s, const BatchBox *d_boxes, int nbox, int total_items, int grid) {
   grid = (grid + 7) / 8 * 8;  // the XCD numbering of work items needs a multiple of 8
   if constexpr (kSplit<Real>)
-    hipLaunchKernelGGL((fused::dugks_split_kernel<Real, W, O32>), dim3(grid), dim3(2 * fused::Tile<W>::NT), 0, s,
+    hipLaunchKernelGGL((fused::dugks_split_kernel<Real, W, O32, Mesh>), dim3(grid), dim3(2 * fused::Tile<W>::NT), 0, s,
                        d_boxes, nbox, total_items);
   else
-    hipLaunchKernelGGL((fused::dugks_fused_kernel<Real, W, O32>), dim3(grid), dim3(fused::Tile<W>::NT), 0, s, d_boxes,
-                       nbox, total_items);
+    hipLaunchKernelGGL((fused::dugks_fused_kernel<Real, W, O32, Mesh>), dim3(grid), dim3(fused::Tile<W>::NT), 0, s,
+                       d_boxes, nbox, total_items);
 }
 
 // Whether 32-bit byte offsets reach every cell of one population array of
@@ -1326,21 +1759,26 @@ static bool offsets32(int max_n, int precision) {
   return (uint64_t)max_n * max_n * max_n * elem < (uint64_t(1) << 32);
 }
 
+template <typename Real, bool Mesh>
+static void list_launch(hipStream_t s, int w, bool o32, const BatchBox *d_boxes, int nbox, int total_items, int grid) {
+  if (w == 16)
+    o32 ? list_launch<Real, 16, true, Mesh>(s, d_boxes, nbox, total_items, grid)
+        : list_launch<Real, 16, false, Mesh>(s, d_boxes, nbox, total_items, grid);
+  else
+    o32 ? list_launch<Real, 32, true, Mesh>(s, d_boxes, nbox, total_items, grid)
+        : list_launch<Real, 32, false, Mesh>(s, d_boxes, nbox, total_items, grid);
+}
+
 void launch_dugks_batch(hipStream_t s, int precision, int w, int max_n, const BatchBox *d_boxes, int nbox,
-                        int total_items, int grid) {
+                        int total_items, int grid, bool mesh) {
   if (w != 16 && w != 32) throw Error(DHIT_EINVAL, "fused DUGKS tile width must be 16 or 32");
   const bool o32 = offsets32(max_n, precision);
-  if (precision == DHIT_FP64) {
-    if (w == 16) o32 ? list_launch<double, 16, true>(s, d_boxes, nbox, total_items, grid)
-                     : list_launch<double, 16, false>(s, d_boxes, nbox, total_items, grid);
-    else o32 ? list_launch<double, 32, true>(s, d_boxes, nbox, total_items, grid)
-             : list_launch<double, 32, false>(s, d_boxes, nbox, total_items, grid);
-  } else {
-    if (w == 16) o32 ? list_launch<float, 16, true>(s, d_boxes, nbox, total_items, grid)
-                     : list_launch<float, 16, false>(s, d_boxes, nbox, total_items, grid);
-    else o32 ? list_launch<float, 32, true>(s, d_boxes, nbox, total_items, grid)
-             : list_launch<float, 32, false>(s, d_boxes, nbox, total_items, grid);
-  }
+  if (precision == DHIT_FP64)
+    mesh ? list_launch<double, true>(s, w, o32, d_boxes, nbox, total_items, grid)
+         : list_launch<double, false>(s, w, o32, d_boxes, nbox, total_items, grid);
+  else
+    mesh ? list_launch<float, true>(s, w, o32, d_boxes, nbox, total_items, grid)
+         : list_launch<float, false>(s, w, o32, d_boxes, nbox, total_items, grid);
   DHIT_HIP(hipGetLastError());
 }
 
@@ -1363,6 +1801,8 @@ void fused_table_entries(const dhit_box &b, BatchBox (&e)[2]) {
     e[c].partials = b.partials;
     e[c].hist = b.hist;
     e[c].cur = c;
+    e[c].mesh_width = b.mesh;
+    e[c].mesh_coef = b.mesh ? b.mesh + 3 * b.n : nullptr;
   }
 }
 
@@ -1380,7 +1820,8 @@ static void fused_step(dhit_box &b, const void *src, void *dst, double *sums_out
   const FusedPlan f = fused_plan(b.p);
   {
     TimedLaunch t(b, DHIT_K_DUGKS_FUSED);
-    launch_dugks_batch(b.stream, b.p.precision, f.width, b.n, b.step_table + entry, 1, f.items, f.grid);
+    launch_dugks_batch(b.stream, b.p.precision, f.width, b.n, b.step_table + entry, 1, f.items, f.grid,
+                       b.mesh != nullptr);
     t.done();
   }
   launch_finalize_sums(b, b.partials, f.items, sums_out);
@@ -1396,14 +1837,14 @@ static int fused_resident_blocks(int precision, int w) {
   hipError_t e;
   if (precision == DHIT_FP64)
     e = w == 16 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                      &nb, reinterpret_cast<const void *>(&fused::dugks_split_kernel<double, 16, true>), 2 * fused::Tile<16>::NT, 0)
+                      &nb, reinterpret_cast<const void *>(&fused::dugks_split_kernel<double, 16, true, false>), 2 * fused::Tile<16>::NT, 0)
                 : hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                      &nb, reinterpret_cast<const void *>(&fused::dugks_split_kernel<double, 32, true>), 2 * fused::Tile<32>::NT, 0);
+                      &nb, reinterpret_cast<const void *>(&fused::dugks_split_kernel<double, 32, true, false>), 2 * fused::Tile<32>::NT, 0);
   else
     e = w == 16 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                      &nb, reinterpret_cast<const void *>(&fused::dugks_fused_kernel<float, 16, true>), fused::Tile<16>::NT, 0)
+                      &nb, reinterpret_cast<const void *>(&fused::dugks_fused_kernel<float, 16, true, false>), fused::Tile<16>::NT, 0)
                 : hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                      &nb, reinterpret_cast<const void *>(&fused::dugks_fused_kernel<float, 32, true>), fused::Tile<32>::NT, 0);
+                      &nb, reinterpret_cast<const void *>(&fused::dugks_fused_kernel<float, 32, true, false>), fused::Tile<32>::NT, 0);
   return e == hipSuccess && nb > 0 ? nb : 1;
 }
 

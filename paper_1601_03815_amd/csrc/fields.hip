@@ -133,9 +133,7 @@ __global__ __launch_bounds__(kBlock) void moments_kernel(const Real *__restrict_
     sums_of_cell<Real>(r, jx, jy, jz, p.inv_rho0, v);
     if (mesh) {
       const int n = p.n, x = cell % n, y = (cell / n) % n, z = cell / (n * n);
-      const double vol = mesh[(0 * kMeshTables + kMeshWidth) * n + x] *
-                         mesh[(1 * kMeshTables + kMeshWidth) * n + y] *
-                         mesh[(2 * kMeshTables + kMeshWidth) * n + z];
+      const double vol = mesh[x] * mesh[n + y] * mesh[2 * n + z];
       static_for<kNumSums>([&](auto i) { v[i] *= vol; });
     }
   }

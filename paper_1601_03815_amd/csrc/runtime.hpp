@@ -49,12 +49,17 @@ constexpr int kHistoryCap = 4096;
 constexpr int kFinalizeLevels = 64;
 constexpr int kFinalizeDoubles = kFinalizeLevels * 5 + 8;
 
-// Geometry tables of a stretched DUGKS mesh (set_mesh), laid out
-// [axis][table][n] doubles; for cell i of an axis with widths w:
-//   width w_i, 1/w_i; for the face between i and i+1: lam = w_i/(w_i + w_{i+1})
-//   (position of the face between the two centres) and 1/(c_{i+1} - c_i)
-//   = 2/(w_i + w_{i+1}); 1/(c_{i+1} - c_{i-1}) for the central difference.
-enum MeshTable { kMeshWidth = 0, kMeshInvWidth, kMeshLam, kMeshInvGap, kMeshInvSpan, kMeshTables };
+// Device tables of a stretched DUGKS mesh (set_mesh): the cell widths [3][n]
+// in double (weights of the sums), then the march's coefficients
+// [3][kMarchCoefs][n] in the box's precision.  For cell i of an axis with
+// widths w, faces i (to i+1) and i-1: lam_i = w_i/(w_i + w_{i+1}) (position of
+// the face between the two centres), g_i = 1/(c_{i+1} - c_i) = 2/(w_i + w_{i+1}),
+//   A = dt alpha lam_i/w_i,  E = dt alpha (1 - lam_{i-1})/w_i,
+//   U(s) = s A - dt alpha h g_i/w_i,  V(s) = s E + dt alpha h g_{i-1}/w_i  (s = +1, -1),
+//   lam_i,  Hg = h g_i,  Hs = h/(c_{i+1} - c_{i-1}),  Iw = 1/w_i.
+enum MarchCoef {
+  kMarchUp = 0, kMarchUm, kMarchVp, kMarchVm, kMarchA, kMarchE, kMarchLam, kMarchHg, kMarchHs, kMarchIw, kMarchCoefs
+};
 
 // One box of a batched launch (device-resident table entry).  `cur` and
 // `step` live on the device so that a captured graph can be replayed for
@@ -72,6 +77,8 @@ struct BatchBox {
   int tail_from, tail_split;
   double *partials;    // the box's per-item partial sums, [5][items]
   double *hist;        // the box's history of global sums, [kHistoryCap][5]
+  const double *mesh_width;  // stretched DUGKS mesh (see MarchCoef), NULL: unit cells
+  const void *mesh_coef;
   double *trial;       // where a trial (uncommitted) step writes its sums, [5]
   int cur;
   int pad_;
@@ -120,7 +127,7 @@ struct dhit_box {
   double *hist = nullptr;      // [kHistoryCap][5]
   int64_t steps = 0;
   void *scratch = nullptr;     // DUGKS two-pass transform field
-  double *mesh = nullptr;      // stretched-mesh tables [3][kMeshTables][n] (DUGKS), NULL = unit cells
+  double *mesh = nullptr;      // stretched-mesh tables (see MarchCoef), NULL = unit cells
   dhit::BatchBox *step_table = nullptr;  // LBE and fused DUGKS steps: the box as a one-entry table per buffer phase [2]
   bool own_step_table = false;
   dhit::StepParams sp{};
@@ -173,10 +180,11 @@ int lbe_cells_per_thread(int n, int precision);
 int lbe_items(int64_t ncell, int cells_per_thread);
 void lbe_table_entries(const dhit_box &b, BatchBox (&e)[2]);
 // One launch of the fused DUGKS kernel (tile width w) over the work items
-// of a device table of boxes (the largest of side max_n); a single box is a
-// table of one entry.
+// of a device table of boxes (the largest of side max_n; mesh: all on
+// stretched meshes, else all on unit cells); a single box is a table of one
+// entry.
 void launch_dugks_batch(hipStream_t s, int precision, int w, int max_n, const BatchBox *d_boxes, int nbox,
-                        int total_items, int grid);
+                        int total_items, int grid, bool mesh);
 // The two one-entry tables of a box (entry c steps from f[c] to f[1 - c]),
 // and a launch that writes two entries given by value to device memory.
 void fused_table_entries(const dhit_box &b, BatchBox (&e)[2]);

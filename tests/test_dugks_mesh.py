@@ -291,3 +291,40 @@ def test_mesh_fp32_energy_tracks_fp64():
             K[prec] = b.sums_history(steps)[:, 4]
     assert K["fp64"][-1] < 0.5 * K["fp64"][0]
     assert np.max(np.abs(K["fp32"] - K["fp64"]) / K["fp64"]) < 5e-6
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("n", [31, 40])
+def test_mesh_tiles_and_chunks(n, precision):
+    """The march on a stretched mesh over several column tiles (a tile whose
+    inner columns end short of the box, one that crosses the periodic seam
+    twice) for both tile widths, z-chunks of one plane, of a length that does
+    not divide n and of the whole box, and on a box of the two-pass variant:
+    two steps against the oracle (FP64 1e-12; FP32 2e-6 per step), the same
+    populations bit for bit whatever the z-chunk, and volume-weighted sums of
+    the last step against the oracle's state (FP64: 1e-13 of sum V|f|; FP32:
+    one rounding of 6e-8 per value)."""
+    import oracle as O
+    import paper_1601_03815_amd as dhit
+    nu, dt, rho0 = 0.02, 0.37, 1.3
+    W = synth.stretched_widths(n, AMP)
+    V = W[0][None, None, :] * W[1][None, :, None] * W[2][:, None, None]
+    f0 = synth.random_populations(n, seed=600 + n, amplitude=0.01)
+    if precision == "fp32":
+        f0 = f0.astype(np.float32).astype(np.float64)
+    ref = O.dugks_step_mesh(f0, W, nu=nu, dt=dt, rho0=rho0, nsteps=2)
+    drho, j, _ = O.moments(ref)
+    sums = [(V * drho).sum()] + [(V * a).sum() for a in j] + [0.5 * (V * (j * j).sum(0)).sum() / rho0 ** 2]
+    scale = (V * np.abs(ref)).sum()
+    same = {}
+    for tile, chunk, variant in [(32, 0, 0), (32, 1, 0), (32, 7, 0), (32, -7, 0), (32, n, 0), (32, 5, dhit.VARIANT_TWO_PASS),
+                                 (16, 0, 0), (16, 9, 0)]:
+        with dhit.Box(n, "dugks", precision, nu, dt=dt, rho0=rho0, tile_width=tile, z_chunk=chunk, variant=variant) as b:
+            b.set_mesh(W)
+            b.set_populations(f0)
+            b.step(2)
+            got, hist = b.get_populations(), b.sums_history(2)
+        assert _rel(got, ref) <= (1e-12 if precision == "fp64" else 4e-6), (tile, chunk, variant)
+        assert np.abs(hist[1] - sums).max() <= (1e-13 if precision == "fp64" else 6e-8) * scale, (tile, chunk, variant)
+        np.testing.assert_array_equal(got, same.setdefault(tile, got))
