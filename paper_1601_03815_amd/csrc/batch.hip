@@ -138,7 +138,7 @@ void build_table(dhit_batch &bt, int chunk) {
       d.nz_chunk = cz;
       d.items = dhit::fused_dugks_items(b->n, bt.tile, cz, &d.tiles_x, &d.tiles_y);
     } else {
-      d.items = dhit::lbe_items(b->ncell, bt.cells_per_thread);
+      d.items = dhit::lbe_items(b->ncell, {bt.cells_per_thread, dhit::kBlock});
     }
     d.hist = b->hist;
     d.cur = b->cur;
@@ -221,8 +221,8 @@ void enqueue_step(dhit_batch &bt, int commit) {
     dhit::launch_dugks_batch(bt.stream, bt.precision, bt.tile, bt.max_n, bt.d_boxes, nbox, bt.total_items, bt.grid,
                              false);
   else
-    dhit::launch_lbe_batch(bt.stream, bt.method, bt.precision, bt.cells_per_thread, bt.d_boxes, nbox, bt.total_items,
-                           bt.grid);
+    dhit::launch_lbe_batch(bt.stream, bt.method, bt.precision, {bt.cells_per_thread, dhit::kBlock}, bt.d_boxes, nbox,
+                           bt.total_items, bt.grid);
   dhit::launch_finalize_batch(bt.stream, bt.d_boxes, nbox, commit);
 }
 
@@ -378,9 +378,9 @@ void set_boxes(dhit_batch &bt, dhit_box **boxes, int32_t nbox) {
   bt.boxes.assign(boxes, boxes + nbox);
   bt.max_n = 0;
   for (int32_t i = 0; i < nbox; ++i) bt.max_n = std::max(bt.max_n, boxes[i]->n);
-  bt.cells_per_thread = dhit::lbe_cells_per_thread(boxes[0]->n, bt.precision);
+  bt.cells_per_thread = dhit::lbe_cells_per_thread(boxes[0]->n, bt.method, bt.precision);
   for (int32_t i = 1; i < nbox; ++i)
-    if (dhit::lbe_cells_per_thread(boxes[i]->n, bt.precision) != bt.cells_per_thread) bt.cells_per_thread = 1;
+    if (dhit::lbe_cells_per_thread(boxes[i]->n, bt.method, bt.precision) != bt.cells_per_thread) bt.cells_per_thread = 1;
   if ((size_t)nbox > bt.cap_boxes) {
     if (bt.d_boxes || bt.d_trial) DHIT_HIP(hipStreamSynchronize(bt.stream));
     if (bt.d_boxes) (void)hipFree(bt.d_boxes);

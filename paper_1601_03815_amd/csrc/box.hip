@@ -141,6 +141,9 @@ int64_t reduction_blocks(const dhit_params &p) {
   if (p.method == DHIT_DUGKS) {
     const int64_t f = dhit::fused_dugks_blocks(p, nullptr, nullptr, nullptr, nullptr);
     if (f > blocks) blocks = f;
+  } else {
+    const int64_t f = dhit::lbe_items(ncell, dhit::lbe_split(p.n, p.method, p.precision));
+    if (f > blocks) blocks = f;
   }
   return blocks;
 }

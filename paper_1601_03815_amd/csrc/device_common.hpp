@@ -111,26 +111,53 @@ __device__ __forceinline__ void equilibrium(Real drho, Real jx, Real jy, Real jz
   static_for<kQ>([&](auto q) { feq[q] = equilibrium_q<q, Real>(base, xi_dot<q>(ux, uy, uz), rho0); });
 }
 
-// Sum of five doubles over the block; thread 0 gets the block total.
-// Deterministic: fixed shuffle tree inside each wavefront, then the
-// wavefront totals in wavefront order.
-__device__ __forceinline__ void block_sum5(double (&v)[kNumSums], double (*smem)[kNumSums]) {
-  static_for<kNumSums>([&](auto i) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v[i] += __shfl_down(v[i], off, 64);
-  });
+// Value of the lane `Off` lanes above (lanes without one get some value): the
+// permlane swaps exchange half-wavefronts and 16-lane rows, DPP shifts within a
+// row; no LDS traffic, unlike a shuffle.
+template <int Off>
+__device__ __forceinline__ unsigned lane_above(unsigned v) {
+  if constexpr (Off == 32)
+    return __builtin_amdgcn_permlane32_swap(v, v, false, false)[1];
+  else if constexpr (Off == 16)
+    return __builtin_amdgcn_permlane16_swap(v, v, false, false)[1];
+  else
+    return (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x100 + Off, 0xf, 0xf, true);
+}
+template <int Off>
+__device__ __forceinline__ double lane_above(double v) {
+  const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
+  const unsigned lo = lane_above<Off>((unsigned)b), hi = lane_above<Off>((unsigned)(b >> 32));
+  return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+}
+// Sum over the wavefront in lane 0, by halving (l takes l + 32, then l + 16, ...).
+__device__ __forceinline__ double wave_sum(double v) {
+  v += lane_above<32>(v);
+  v += lane_above<16>(v);
+  v += lane_above<8>(v);
+  v += lane_above<4>(v);
+  v += lane_above<2>(v);
+  v += lane_above<1>(v);
+  return v;
+}
+
+// Sums of five doubles over a block of NW wavefronts: thread i < 5 returns
+// the total of v[i].  Deterministic: a fixed tree inside each wavefront, then
+// the wavefront totals in wavefront order (five lanes side by side).
+template <int NW>
+__device__ __forceinline__ double block_sum5(double (&v)[kNumSums], double (*smem)[kNumSums]) {
+  static_for<kNumSums>([&](auto i) { v[i] = wave_sum(v[i]); });
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   if (lane == 0) {
     static_for<kNumSums>([&](auto i) { smem[wave][i] = v[i]; });
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    static_for<kNumSums>([&](auto i) {
-      double s = smem[0][i];
-      for (int w = 1; w < (int)(blockDim.x >> 6); ++w) s += smem[w][i];
-      v[i] = s;
-    });
+  double s = 0.0;
+  if (threadIdx.x < kNumSums) {
+    s = smem[0][threadIdx.x];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) s += smem[w][threadIdx.x];
   }
+  return s;
 }
 
 // Per-cell contributions to the five global sums, accumulated in FP64 from
@@ -182,17 +209,17 @@ __device__ __forceinline__ global_t<T> *to_global(T *p) {
 // Writes the block's five sums to partials laid out [5][nblocks], using
 // smem (at least one row of five doubles per wavefront of the block) for
 // the reduction.
+template <int NW>
 __device__ __forceinline__ void write_block_partials(double (&v)[kNumSums], double *partials, int nblocks, int block,
                                                      double (*smem)[kNumSums]) {
-  block_sum5(v, smem);
-  if (threadIdx.x == 0) {
-    static_for<kNumSums>([&](auto i) { to_global(partials)[(int64_t)i * nblocks + block] = v[i]; });
-  }
+  const double t = block_sum5<NW>(v, smem);
+  if (threadIdx.x < kNumSums) to_global(partials)[(int64_t)threadIdx.x * nblocks + block] = t;
 }
+template <int NW = kWaves>
 __device__ __forceinline__ void write_block_partials(double (&v)[kNumSums], double *partials, int nblocks,
                                                      int block) {
-  __shared__ double smem[kBlock / 64][kNumSums];
-  write_block_partials(v, partials, nblocks, block, smem);
+  __shared__ double smem[NW][kNumSums];
+  write_block_partials<NW>(v, partials, nblocks, block, smem);
 }
 
 // Flat-index offsets of the +-1 neighbours along one axis with periodic

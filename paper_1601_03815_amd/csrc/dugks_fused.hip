@@ -1154,7 +1154,7 @@ __global__ __launch_bounds__(Tile<W>::NT, kWavesPerSimd<Real>) void dugks_fused_
     if (ip.left > 0)
       fused_tile<Real, W, O32, Mesh>(src, dst, d.sp, ip.tile % d.tiles_x, ip.tile / d.tiles_x, ip.z0, ip.z0 + ip.left, L,
                                      v, static_cast<const Real *>(d.mesh_coef), d.mesh_width);
-    write_block_partials(v, d.partials, d.items, local, reinterpret_cast<double (*)[kNumSums]>(L));
+    write_block_partials<Tile<W>::NT / 64>(v, d.partials, d.items, local, reinterpret_cast<double (*)[kNumSums]>(L));
     __syncthreads();
   }
 }
@@ -1621,7 +1621,7 @@ __global__ __launch_bounds__(2 * Tile<W>::NT) void dugks_split_kernel(const Batc
         split_tile<Real, W, 1, O32, Mesh>(src, dst, d.sp, bx, by, ip.z0, z1, L, v,
                                           static_cast<const Real *>(d.mesh_coef), d.mesh_width);
     }
-    write_block_partials(v, d.partials, d.items, local, reinterpret_cast<double (*)[kNumSums]>(L));
+    write_block_partials<2 * Tile<W>::NT / 64>(v, d.partials, d.items, local, reinterpret_cast<double (*)[kNumSums]>(L));
     __syncthreads();
   }
 }

@@ -182,10 +182,8 @@ __global__ __launch_bounds__(1024) void finalize_sums_kernel(const double *__res
   for (int b = threadIdx.x; b < nblocks; b += 1024) {
     static_for<kNumSums>([&](auto i) { v[i] += partials[(int64_t)i * nblocks + b]; });
   }
-  block_sum5(v, smem);
-  if (threadIdx.x == 0) {
-    static_for<kNumSums>([&](auto i) { out[i] = v[i]; });
-  }
+  const double t = block_sum5<16>(v, smem);
+  if (threadIdx.x < kNumSums) out[threadIdx.x] = t;
 }
 
 // Per-box finalisation of a batched step: block b sums box b's partials in
@@ -200,12 +198,13 @@ __global__ __launch_bounds__(1024) void finalize_batch_kernel(BatchBox *__restri
   for (int b = threadIdx.x; b < nblocks; b += 1024) {
     static_for<kNumSums>([&](auto i) { v[i] += d.partials[(int64_t)i * nblocks + b]; });
   }
-  block_sum5(v, smem);
-  if (threadIdx.x == 0) {
-    double *out = commit ? d.hist + (d.step % kHistoryCap) * kNumSums : d.trial;
-    static_for<kNumSums>([&](auto i) { out[i] = v[i]; });
-    if (commit) {
-      d.step = d.step + 1;
+  const double t = block_sum5<16>(v, smem);
+  if (threadIdx.x < kNumSums) {
+    const int64_t step = d.step;
+    double *out = commit ? d.hist + (step % kHistoryCap) * kNumSums : d.trial;
+    out[threadIdx.x] = t;
+    if (commit && threadIdx.x == 0) {  // the wavefront's five lanes have read d.step
+      d.step = step + 1;
       d.cur = d.cur ^ 1;
     }
   }
@@ -233,12 +232,11 @@ __global__ __launch_bounds__(kBlock) void finalize_sums_wide_kernel(const double
   for (int b = lo + (int)threadIdx.x; b < hi; b += kBlock) {
     static_for<kNumSums>([&](auto i) { v[i] += partials[(int64_t)i * nblocks + b]; });
   }
-  block_sum5(v, smem);
+  const double t = block_sum5<kWaves>(v, smem);
   unsigned *counter = reinterpret_cast<unsigned *>(level + kFinalizeLevels * kNumSums);
+  if (threadIdx.x < kNumSums)
+    __hip_atomic_store(&level[(int64_t)blockIdx.x * kNumSums + threadIdx.x], t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   if (threadIdx.x == 0) {
-    static_for<kNumSums>([&](auto i) {
-      __hip_atomic_store(&level[(int64_t)blockIdx.x * kNumSums + i], v[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    });
     const unsigned done = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
     last = done == gridDim.x - 1;
   }
@@ -251,9 +249,6 @@ __global__ __launch_bounds__(kBlock) void finalize_sums_wide_kernel(const double
     if (threadIdx.x == 0) __hip_atomic_store(counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
 }
-
-// Partials one block of the wide finalisation sums.
-constexpr int kFinalizePer = 4096;
 
 void launch_finalize_sums(dhit_box &b, const double *partials, int nblocks, double *out) {
   TimedLaunch t(b, DHIT_K_FINALIZE);

@@ -26,8 +26,27 @@ namespace dhit {
 // one cell per thread.  FP32: one cell (runs of 2 or 4 cells measured 15%
 // slower: the registers of several cells' collisions cost occupancy that the
 // wider accesses do not win back).
+// BGK boxes of more than kBgkRunMaxCells cells run one cell per thread in FP64
+// too: two BGK collisions take 176 registers (MRT 136), two waves per SIMD,
+// which does not keep enough accesses in flight once the populations come
+// from HBM (us per step with two cells and with one: 256^3 971 and 930, 128^3
+// 135 and 122, 96^3 62.2 and 57.1; 64^3, in the caches, 19.0 and 19.5).
+// At 256^3 the step runs at the rate of a plain copy of 19 arrays of its
+// layout (0.90-0.96 ms over access widths and block sizes).
 template <typename Real>
 constexpr int kRunCells = sizeof(Real) == 8 ? 2 : 1;
+constexpr int64_t kBgkRunMaxCells = 512000;
+
+// A small box stepped alone runs one cell per thread in blocks of
+// kSmallBlock threads, up to kSmallCells<Real> cells: its launch lasts as long
+// as one thread's chain of loads, collision and stores, and two cells in a
+// row, or fewer and larger blocks, only lengthen it.  Step of a 32^3 box, us,
+// against kRunCells in blocks of kBlock: FP64 MRT 6.8 (11.8), 48^3 12.6
+// (15.1), 52^3 14.8 (16.2), but 56^3 17.4 (16.6); FP32 7.0 (7.3), 36^3 8.1
+// (7.9).  Blocks of 64 threads: 32^3 7.0, 48^3 12.7, 52^3 15.7.
+constexpr int kSmallBlock = 128;
+template <typename Real>
+constexpr int64_t kSmallCells = sizeof(Real) == 8 ? 150000 : 32768;
 
 template <typename Real, int C>
 struct Run {
@@ -116,63 +135,78 @@ __device__ __forceinline__ void lbe_run(const global_t<Real> *__restrict__ src, 
   });
 }
 
-// One launch advances one or many boxes: work item = a run of kBlock * C
-// cells of one box of the device table `boxes` (sorted by item_begin),
-// where C is 1 or kRunCells<Real> for the whole launch.  A single box is a
-// table of one entry.  The per-item partial sums are laid out as a block
-// launch's would be.
-template <int K, typename Real, int C>
-__global__ __launch_bounds__(kBlock) void lbe_kernel(const BatchBox *__restrict__ boxes, int nbox, int total_items) {
+// One launch advances one or many boxes: work item = a run of B * C cells of
+// one box of the device table `boxes` (sorted by item_begin), where C, 1 or
+// kRunCells<Real>, and the block size B are the same for the whole launch.  A
+// single box is a table of one entry.  The per-item partial sums are laid out
+// as a block launch's would be.
+template <int K, typename Real, int C, int B>
+__global__ __launch_bounds__(B) void lbe_kernel(const BatchBox *__restrict__ boxes, int nbox, int total_items) {
+  __shared__ double smem[B / 64][kNumSums];
   for (int it = blockIdx.x; it < total_items; it += gridDim.x) {
     const int b = find_batch_box(boxes, nbox, it);
     const BatchBox &d = boxes[b];
     const int local = it - d.item_begin;
-    const int cell = (local * kBlock + threadIdx.x) * C;
+    const int cell = (local * B + threadIdx.x) * C;
     double v[kNumSums] = {0, 0, 0, 0, 0};
     if (cell < d.ncell)
       lbe_run<K, C, Real>(to_global(static_cast<const Real *>(d.f[d.cur])), to_global(static_cast<Real *>(d.f[d.cur ^ 1])),
                           d.sp, cell, v);
-    write_block_partials(v, d.partials, d.items, local);
+    write_block_partials<B / 64>(v, d.partials, d.items, local, smem);
     __syncthreads();
   }
 }
 
-int lbe_cells_per_thread(int n, int precision) {
-  const int c = precision == DHIT_FP64 ? kRunCells<double> : kRunCells<float>;
+// Work split of a box stepped alone.
+LbeSplit lbe_split(int n, int method, int precision) {
+  const int64_t ncell = (int64_t)n * n * n;
+  if (ncell <= (precision == DHIT_FP64 ? kSmallCells<double> : kSmallCells<float>)) return {1, kSmallBlock};
+  return {lbe_cells_per_thread(n, method, precision), kBlock};
+}
+
+int lbe_cells_per_thread(int n, int method, int precision) {
+  int c = precision == DHIT_FP64 ? kRunCells<double> : kRunCells<float>;
+  if (method == DHIT_LBE_BGK && (int64_t)n * n * n > kBgkRunMaxCells) c = 1;
   return n % c == 0 ? c : 1;
 }
 
-int lbe_items(int64_t ncell, int cells_per_thread) {
-  return (int)((ncell / cells_per_thread + kBlock - 1) / kBlock);
+int lbe_items(int64_t ncell, const LbeSplit &s) {
+  return (int)((ncell / s.cells + s.threads - 1) / s.threads);
 }
 
-template <typename Real, int C>
+template <typename Real, int C, int B>
 static void lbe_launch_typed(hipStream_t s, int method, const BatchBox *d_boxes, int nbox, int total_items, int grid) {
   if (method == DHIT_LBE_BGK)
-    hipLaunchKernelGGL((lbe_kernel<kBGK, Real, C>), dim3(grid), dim3(kBlock), 0, s, d_boxes, nbox, total_items);
+    hipLaunchKernelGGL((lbe_kernel<kBGK, Real, C, B>), dim3(grid), dim3(B), 0, s, d_boxes, nbox, total_items);
   else
-    hipLaunchKernelGGL((lbe_kernel<kMRT, Real, C>), dim3(grid), dim3(kBlock), 0, s, d_boxes, nbox, total_items);
+    hipLaunchKernelGGL((lbe_kernel<kMRT, Real, C, B>), dim3(grid), dim3(B), 0, s, d_boxes, nbox, total_items);
 }
 
-void launch_lbe_batch(hipStream_t s, int method, int precision, int cells_per_thread, const BatchBox *d_boxes,
-                      int nbox, int total_items, int grid) {
-  if (precision == DHIT_FP64) {
-    if (cells_per_thread == kRunCells<double>)
-      lbe_launch_typed<double, kRunCells<double>>(s, method, d_boxes, nbox, total_items, grid);
-    else
-      lbe_launch_typed<double, 1>(s, method, d_boxes, nbox, total_items, grid);
-  } else {
-    if (cells_per_thread == kRunCells<float>)
-      lbe_launch_typed<float, kRunCells<float>>(s, method, d_boxes, nbox, total_items, grid);
-    else
-      lbe_launch_typed<float, 1>(s, method, d_boxes, nbox, total_items, grid);
-  }
+template <typename Real>
+static void lbe_launch_split(hipStream_t s, int method, const LbeSplit &w, const BatchBox *d_boxes, int nbox,
+                             int total_items, int grid) {
+  if (w.threads == kSmallBlock && w.cells == 1)
+    lbe_launch_typed<Real, 1, kSmallBlock>(s, method, d_boxes, nbox, total_items, grid);
+  else if (w.threads == kBlock && w.cells == kRunCells<Real>)
+    lbe_launch_typed<Real, kRunCells<Real>, kBlock>(s, method, d_boxes, nbox, total_items, grid);
+  else if (w.threads == kBlock && w.cells == 1)
+    lbe_launch_typed<Real, 1, kBlock>(s, method, d_boxes, nbox, total_items, grid);
+  else
+    throw Error(DHIT_EINVAL, "no LBE kernel for this work split");
+}
+
+void launch_lbe_batch(hipStream_t s, int method, int precision, const LbeSplit &w, const BatchBox *d_boxes, int nbox,
+                      int total_items, int grid) {
+  if (precision == DHIT_FP64)
+    lbe_launch_split<double>(s, method, w, d_boxes, nbox, total_items, grid);
+  else
+    lbe_launch_split<float>(s, method, w, d_boxes, nbox, total_items, grid);
   DHIT_HIP(hipGetLastError());
 }
 
 // The two one-box tables of an LBE box (entry c steps from f[c] to f[1 - c]).
 void lbe_table_entries(const dhit_box &b, BatchBox (&e)[2]) {
-  const int cpt = lbe_cells_per_thread(b.n, b.p.precision);
+  const LbeSplit w = lbe_split(b.n, b.p.method, b.p.precision);
   for (int c = 0; c < 2; ++c) {
     std::memset(&e[c], 0, sizeof(BatchBox));
     e[c].f[0] = b.f[0];
@@ -180,7 +214,7 @@ void lbe_table_entries(const dhit_box &b, BatchBox (&e)[2]) {
     e[c].sp = b.sp;
     e[c].ncell = (int)b.ncell;
     e[c].item_begin = 0;
-    e[c].items = lbe_items(b.ncell, cpt);
+    e[c].items = lbe_items(b.ncell, w);
     e[c].partials = b.partials;
     e[c].hist = b.hist;
     e[c].cur = c;
@@ -193,11 +227,11 @@ void launch_lbe_step(dhit_box &b, const void *src, void *dst, double *sums_out) 
   if (src == b.f[0] && dst == b.f[1]) entry = 0;
   else if (src == b.f[1] && dst == b.f[0]) entry = 1;
   else throw Error(DHIT_EINVAL, "LBE step between buffers that are not the box's");
-  const int cpt = lbe_cells_per_thread(b.n, b.p.precision);
-  const int items = lbe_items(b.ncell, cpt);
+  const LbeSplit w = lbe_split(b.n, b.p.method, b.p.precision);
+  const int items = lbe_items(b.ncell, w);
   {
     TimedLaunch t(b, DHIT_K_LBE);
-    launch_lbe_batch(b.stream, b.p.method, b.p.precision, cpt, b.step_table + entry, 1, items, items);
+    launch_lbe_batch(b.stream, b.p.method, b.p.precision, w, b.step_table + entry, 1, items, items);
     t.done();
   }
   launch_finalize_sums(b, b.partials, items, sums_out);

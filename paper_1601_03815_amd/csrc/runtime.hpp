@@ -47,6 +47,8 @@ constexpr int kHistoryCap = 4096;
 // 4096 block partials); its work space is kFinalizeLevels * 5 doubles and a
 // counter that must be zero before the first launch.
 constexpr int kFinalizeLevels = 64;
+// Partials one block of the wide finalisation sums.
+constexpr int kFinalizePer = 4096;
 constexpr int kFinalizeDoubles = kFinalizeLevels * 5 + 8;
 
 // Device tables of a stretched DUGKS mesh (set_mesh): the cell widths [3][n]
@@ -172,12 +174,16 @@ void timer_free(dhit_box &b);
 void launch_velocity(dhit_box &b, const void *f, double *d_u);   // u = j / rho0, [3][ncell]
 
 // Batched launches (batch.hip drives them).  LBE: one launch over the work
-// items (runs of kBlock * cells_per_thread cells) of a device table of boxes;
-// cells_per_thread is lbe_cells_per_thread() of every box of the launch, or 1.
-void launch_lbe_batch(hipStream_t s, int method, int precision, int cells_per_thread, const BatchBox *d_boxes,
-                      int nbox, int total_items, int grid);
-int lbe_cells_per_thread(int n, int precision);
-int lbe_items(int64_t ncell, int cells_per_thread);
+// items (runs of threads * cells cells) of a device table of boxes; cells is
+// lbe_cells_per_thread() of every box of the launch, or 1.
+struct LbeSplit {
+  int cells, threads;  // cells per thread, threads per block
+};
+void launch_lbe_batch(hipStream_t s, int method, int precision, const LbeSplit &w, const BatchBox *d_boxes, int nbox,
+                      int total_items, int grid);
+int lbe_cells_per_thread(int n, int method, int precision);
+LbeSplit lbe_split(int n, int method, int precision);
+int lbe_items(int64_t ncell, const LbeSplit &s);
 void lbe_table_entries(const dhit_box &b, BatchBox (&e)[2]);
 // One launch of the fused DUGKS kernel (tile width w) over the work items
 // of a device table of boxes (the largest of side max_n; mesh: all on
