@@ -263,6 +263,7 @@ int32_t create_box(const dhit_params *pp, dhit_box **out) {
     *out = nullptr;
     validate(*pp);
     dhit_box *b = new dhit_box();
+    dhit::box_made();
     try {
       b->p = *pp;
       if (b->p.method == DHIT_DUGKS && b->p.z_chunk == 0) b->p.z_chunk = dhit::fused_auto_chunk(b->p);
@@ -338,6 +339,7 @@ int32_t destroy_box(dhit_box *b) {
   if (b->own_step_table && b->step_table) (void)hipFree(b->step_table);
   if (b->own_stream && b->stream) (void)hipStreamDestroy(b->stream);
   delete b;
+  dhit::box_gone();
   return DHIT_OK;
 }
 
@@ -577,9 +579,7 @@ int32_t moments(dhit_box *b, double *drho, double *j, double *sums) {
       dhit::launch_moments(*b, b->f[b->cur], dd, dj, ds);
       double hs[5];
       DHIT_HIP(hipMemcpyAsync(hs, ds, sizeof(hs), hipMemcpyDeviceToHost, b->stream));
-      if (drho) DHIT_HIP(hipMemcpyAsync(drho, dd, bytes, hipMemcpyDeviceToHost, b->stream));
-      if (j) DHIT_HIP(hipMemcpyAsync(j, dj, 3 * bytes, hipMemcpyDeviceToHost, b->stream));
-      DHIT_HIP(hipStreamSynchronize(b->stream));
+      dhit::copy_to_host({{drho, dd, drho ? bytes : 0}, {j, dj, j ? 3 * bytes : 0}}, b->stream);
       if (sums) std::memcpy(sums, hs, sizeof(hs));
       cleanup();
       check_finite(hs, 5);
@@ -597,12 +597,15 @@ int32_t sums_history(dhit_box *b, double *out, int32_t count) {
     require_box(b);
     if (count < 0 || (count > 0 && !out)) fail(DHIT_EINVAL, "bad output");
     if (count > b->steps || count > dhit::kHistoryCap) fail(DHIT_EINVAL, "count exceeds the recorded history");
+    // the history is a ring: one copy, or two where the range wraps around
+    const int32_t first = (int32_t)((b->steps - count) % dhit::kHistoryCap);
+    const int32_t run = std::min(count, (int32_t)dhit::kHistoryCap - first);
+    if (run > 0)
+      DHIT_HIP(hipMemcpyAsync(out, b->hist + 5 * first, (size_t)run * 5 * sizeof(double), hipMemcpyDeviceToHost, b->stream));
+    if (count > run)
+      DHIT_HIP(hipMemcpyAsync(out + 5 * run, b->hist, (size_t)(count - run) * 5 * sizeof(double), hipMemcpyDeviceToHost,
+                              b->stream));
     DHIT_HIP(hipStreamSynchronize(b->stream));
-    for (int32_t i = 0; i < count; ++i) {
-      const int64_t step = b->steps - count + i;
-      DHIT_HIP(hipMemcpy(out + 5 * i, b->hist + (step % dhit::kHistoryCap) * 5, 5 * sizeof(double),
-                         hipMemcpyDeviceToHost));
-    }
     check_finite(out, 5 * count);
     return DHIT_OK;
   });
@@ -646,8 +649,7 @@ int32_t get_populations(dhit_box *b, double *f) {
     if (hipMalloc(&d, bytes) != hipSuccess) fail(DHIT_ENOMEM, "cannot allocate download buffer");
     try {
       dhit::launch_pack(*b, b->f[b->cur], d);
-      DHIT_HIP(hipMemcpyAsync(f, d, bytes, hipMemcpyDeviceToHost, b->stream));
-      DHIT_HIP(hipStreamSynchronize(b->stream));
+      dhit::copy_to_host({{f, d, bytes}}, b->stream);
     } catch (...) {
       (void)hipStreamSynchronize(b->stream);
       (void)hipFree(d);

@@ -1,0 +1,156 @@
+// Large copies of results to the caller's (pageable) host arrays.
+//
+// A plain hipMemcpy to pageable memory moves it through one staging buffer with
+// one thread, copy after copy, and that thread also takes the page faults of
+// a result array that nobody has touched yet: 11 GB/s for the moments of a
+// 128^3 box, where the link gives 56 GB/s.  Here several threads take chunks
+// in turn: a chunk goes over the link to the thread's pinned buffer while the
+// other threads copy theirs on: the moments of that box 6.0 -> 2.5 ms, its
+// vorticity 5.0 -> 1.8 ms (8 and 14 threads, and 4 MiB chunks, the same).  (Uploads stay plain copies: their source is
+// resident, they already run at 26 GB/s, and the same scheme gave no more.)
+#include <algorithm>
+#include <atomic>
+#include <cstring>
+#include <memory>
+#include <mutex>
+#include <system_error>
+#include <thread>
+#include <vector>
+
+#include "runtime.hpp"
+
+namespace dhit {
+namespace {
+
+// Threads (and pinned buffers) of one copy at most.  Chunks end on 2 MiB
+// boundaries of the host address: a fresh array is made of 2 MiB pages, and
+// two threads that fault on one wait for each other.
+constexpr int kCopyThreads = 4;
+constexpr size_t kChunk = size_t(2) << 20;
+// Below this a plain copy is as fast as starting the threads.
+constexpr size_t kPlainBytes = size_t(4) << 20;
+
+struct Staging {
+  void *buf = nullptr;  // kCopyThreads chunks of pinned memory
+  hipEvent_t done[kCopyThreads] = {};
+  ~Staging() {
+    for (hipEvent_t e : done)
+      if (e) (void)hipEventDestroy(e);
+    if (buf) (void)hipHostFree(buf);
+  }
+};
+
+// One idle set of buffers is kept for the next copy while boxes exist;
+// copies that run at the same time make sets of their own.
+std::mutex g_mu;
+std::unique_ptr<Staging> g_idle;
+int g_boxes = 0;
+
+std::unique_ptr<Staging> take_staging() {
+  {
+    std::lock_guard<std::mutex> lock(g_mu);
+    if (g_idle) return std::move(g_idle);
+  }
+  std::unique_ptr<Staging> s(new Staging());
+  if (hipHostMalloc(&s->buf, kCopyThreads * kChunk, hipHostMallocPortable) != hipSuccess) {
+    (void)hipGetLastError();
+    return nullptr;
+  }
+  for (hipEvent_t &e : s->done)
+    if (hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) {
+      (void)hipGetLastError();
+      e = nullptr;
+      return nullptr;
+    }
+  return s;
+}
+
+void give_staging(std::unique_ptr<Staging> s) {
+  std::lock_guard<std::mutex> lock(g_mu);
+  if (g_boxes > 0 && !g_idle) g_idle = std::move(s);
+}
+
+// Whether the host pointer is memory the runtime already has pinned (a plain
+// copy is then one transfer).
+bool is_pinned(const void *p) {
+  hipPointerAttribute_t a;
+  if (hipPointerGetAttributes(&a, p) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return a.type == hipMemoryTypeHost || a.type == hipMemoryTypeManaged;
+}
+
+}  // namespace
+
+void copy_to_host(std::initializer_list<HostCopy> copies, hipStream_t s) {
+  std::vector<HostCopy> chunks;
+  size_t total = 0;
+  bool pinned = false;
+  for (const HostCopy &c : copies) {
+    if (c.bytes == 0) continue;
+    total += c.bytes;
+    pinned = pinned || is_pinned(c.dst);
+    char *dst = static_cast<char *>(c.dst);
+    const char *src = static_cast<const char *>(c.src);
+    const size_t lead = reinterpret_cast<uintptr_t>(dst) % kChunk;
+    for (size_t from = 0; from < c.bytes;) {
+      const size_t to = std::min(c.bytes, (from + lead) / kChunk * kChunk + kChunk - lead);
+      chunks.push_back({dst + from, src + from, to - from});
+      from = to;
+    }
+  }
+  const unsigned cpus = std::thread::hardware_concurrency();
+  const int threads = (int)std::min<size_t>(std::min<size_t>(kCopyThreads, cpus ? cpus : 1), chunks.size());
+  std::unique_ptr<Staging> st;
+  int dev = 0;
+  if (total <= kPlainBytes || threads < 2 || pinned || hipGetDevice(&dev) != hipSuccess || !(st = take_staging())) {
+    for (const HostCopy &c : copies)
+      if (c.bytes) DHIT_HIP(hipMemcpyAsync(c.dst, c.src, c.bytes, hipMemcpyDeviceToHost, s));
+    DHIT_HIP(hipStreamSynchronize(s));
+    return;
+  }
+  std::atomic<size_t> next{0};
+  std::atomic<int> error{(int)hipSuccess};
+  auto work = [&](int w) {
+    hipError_t e = hipSetDevice(dev);
+    char *buf = static_cast<char *>(st->buf) + w * kChunk;
+    while (e == hipSuccess && error.load() == (int)hipSuccess) {
+      const size_t k = next.fetch_add(1);
+      if (k >= chunks.size()) break;
+      const HostCopy &c = chunks[k];
+      e = hipMemcpyAsync(buf, c.src, c.bytes, hipMemcpyDeviceToHost, s);
+      if (e == hipSuccess) e = hipEventRecord(st->done[w], s);
+      if (e == hipSuccess) e = hipEventSynchronize(st->done[w]);
+      if (e == hipSuccess) std::memcpy(c.dst, buf, c.bytes);
+    }
+    if (e != hipSuccess) error.store((int)e);
+  };
+  std::vector<std::thread> pool;
+  pool.reserve(threads - 1);
+  try {
+    for (int w = 1; w < threads; ++w) pool.emplace_back(work, w);
+  } catch (const std::system_error &) {
+    // fewer threads: those that started, and this one, take every chunk
+  }
+  work(0);
+  for (std::thread &t : pool) t.join();
+  const hipError_t sync = hipStreamSynchronize(s);  // no transfer uses the buffers after this
+  const hipError_t e = (hipError_t)error.load();
+  if (sync == hipSuccess) give_staging(std::move(st));
+  DHIT_HIP(e);
+  DHIT_HIP(sync);
+}
+
+void box_made() {
+  std::lock_guard<std::mutex> lock(g_mu);
+  ++g_boxes;
+}
+
+void box_gone() {
+  std::unique_ptr<Staging> last;
+  std::lock_guard<std::mutex> lock(g_mu);
+  if (--g_boxes == 0) last = std::move(g_idle);
+}
+
+}  // namespace dhit

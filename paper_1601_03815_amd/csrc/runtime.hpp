@@ -6,6 +6,7 @@
 #include <hipfft/hipfft.h>
 
 #include <cstdint>
+#include <initializer_list>
 #include <stdexcept>
 #include <string>
 
@@ -138,6 +139,18 @@ struct dhit_box {
 };
 
 namespace dhit {
+
+// Copies device memory to the caller's host memory, after the work queued on
+// s; done on return (hostcopy.hip).
+struct HostCopy {
+  void *dst;
+  const void *src;
+  size_t bytes;
+};
+void copy_to_host(std::initializer_list<HostCopy> copies, hipStream_t s);
+// Counts the live boxes: the copies' idle pinned buffers go with the last one.
+void box_made();
+void box_gone();
 
 // Sets the thread's message returned by dhit_last_error().
 void set_last_error(const std::string &m);

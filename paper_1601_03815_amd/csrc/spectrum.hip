@@ -407,8 +407,7 @@ void pressure_compute(dhit_box &b, const double *u_host, double *drho_host) {
     hipLaunchKernelGGL(inverse_laplacian_kernel, dim3(mb), dim3(256), 0, b.stream, w.tmp, n, w.nhalf, scale);
     DHIT_HIP(hipGetLastError());
     DHIT_FFT(hipfftExecZ2D(w.inv, w.tmp, w.u));
-    DHIT_HIP(hipMemcpyAsync(drho_host, w.u, b.ncell * sizeof(double), hipMemcpyDeviceToHost, b.stream));
-    DHIT_HIP(hipStreamSynchronize(b.stream));
+    copy_to_host({{drho_host, w.u, b.ncell * sizeof(double)}}, b.stream);
   } catch (...) {
     (void)hipStreamSynchronize(b.stream);
     (void)hipFree(du);
@@ -451,8 +450,7 @@ void vorticity_compute(dhit_box &b, double *omega_host) {
     DHIT_HIP(hipGetLastError());
     DHIT_FFT(hipfftExecZ2D(w.inv, w.tmp, w.u + (int64_t)a * b.ncell));
   }
-  DHIT_HIP(hipMemcpyAsync(omega_host, w.u, 3 * b.ncell * sizeof(double), hipMemcpyDeviceToHost, b.stream));
-  DHIT_HIP(hipStreamSynchronize(b.stream));
+  copy_to_host({{omega_host, w.u, 3 * b.ncell * sizeof(double)}}, b.stream);
 }
 
 }  // namespace dhit
