@@ -17,16 +17,21 @@ struct SpectrumWork {
   int n = 0;
   int nshell = 0;
   int64_t nhalf = 0;  // modes of one real-to-complex transform, n*n*(n/2+1)
-  double *u = nullptr;
-  hipfftDoubleComplex *uh = nullptr;
-  hipfftDoubleComplex *tmp = nullptr;
-  unsigned long long *shells = nullptr;  // [2][kShellParts][nshell]: digit sums of E and kappa^2-weighted E
-  int *overflow = nullptr;               // set when a shell term is out of range or not finite
-  double *partials = nullptr;  // [5][blocks]
-  double *dstats = nullptr;    // [3][5]
-  hipfftHandle fwd = 0, inv = 0;
-  bool have_fwd = false, have_inv = false;
+  double *u = nullptr;                   // three fields
+  hipfftDoubleComplex *uh = nullptr;     // their transforms
+  hipfftDoubleComplex *tmp = nullptr;    // one more half spectrum (pressure, gradient; made when first needed)
+  // what energy_spectrum brings to the host, in one piece: the shells' digit
+  // sums [2][kShellParts][nshell] of E and kappa^2-weighted E, the power sums
+  // of the three derivatives [3][5] (doubles), and a word that is set when a
+  // shell term is out of range or not finite
+  unsigned long long *result = nullptr;
+  double *partials = nullptr;  // [3][5][kPowerBlocks]
+  // real-to-complex of three fields; complex-to-real of three, and of one
+  // (each made when first needed)
+  hipfftHandle fwd = 0, inv3 = 0, inv1 = 0;
+  bool have_fwd = false, have_inv3 = false, have_inv1 = false;
 };
+constexpr int kPowerBlocks = 1024;
 
 #define DHIT_FFT(expr)                                                                               \
   do {                                                                                               \
@@ -65,13 +70,20 @@ __device__ __forceinline__ void shell_digits(double e, unsigned long long (&d)[k
   d[0] = (unsigned long long)lo;
 }
 
+// Wavenumber of a derivative: the Nyquist component is dropped.
+__device__ __forceinline__ int derivative_k(int k, int n) { return (2 * k == n || 2 * k == -n) ? 0 : k; }
+
 // One thread per mode of the half spectrum; block histogram of the digits
 // in LDS, then one integer atomic add per digit, shell and block.  Modes
 // 0 < kx < n/2 stand for their Hermitian partners too (weight 2).
-// shells: [2][kShellParts][nshell] digit sums of E and of kappa^2 E.
-__global__ __launch_bounds__(256) void bin_kernel(const hipfftDoubleComplex *__restrict__ uh, int n, int64_t nhalf,
+// shells: [2][kShellParts][nshell] digit sums of E and of kappa^2 E.  The modes
+// are then replaced by those of d_a u_a (i kappa_a u_hat_a, each thread its
+// own), so that the three derivatives go back in one batched transform
+// (three passes of deriv, transform and sums took 160 us of a 128^3
+// spectrum's 330).
+__global__ __launch_bounds__(256) void bin_kernel(hipfftDoubleComplex *__restrict__ uh, int n, int64_t nhalf,
                                                   int nshell, double inv_n6, unsigned long long *__restrict__ shells,
-                                                  int *__restrict__ overflow) {
+                                                  unsigned long long *__restrict__ overflow) {
   extern __shared__ unsigned long long hist[];  // [2][kShellParts][nshell]
   const int nh = 2 * kShellParts * nshell;
   for (int i = threadIdx.x; i < nh; i += blockDim.x) hist[i] = 0ull;
@@ -84,11 +96,14 @@ __global__ __launch_bounds__(256) void bin_kernel(const hipfftDoubleComplex *__r
     const int64_t r = m / nxh;
     const int iy = (int)(r % n), iz = (int)(r / n);
     const int kx = kxh, ky = signed_k(iy, n), kz = signed_k(iz, n);
+    const int kd[3] = {derivative_k(kx, n), derivative_k(ky, n), derivative_k(kz, n)};
     double e = 0.0;
-    for (int c = 0; c < 3; ++c) {
+    static_for<3>([&](auto c) {
       const hipfftDoubleComplex v = uh[(int64_t)c * nhalf + m];
       e += v.x * v.x + v.y * v.y;
-    }
+      const double kap = kfac * kd[c];
+      uh[(int64_t)c * nhalf + m] = make_double2(-kap * v.y, kap * v.x);
+    });
     const bool self = (kx == 0) || (2 * kx == n);
     e *= 0.5 * inv_n6 * (self ? 1.0 : 2.0);
     const int k2 = kx * kx + ky * ky + kz * kz;
@@ -101,61 +116,36 @@ __global__ __launch_bounds__(256) void bin_kernel(const hipfftDoubleComplex *__r
       if (dk[j]) atomicAdd(&hist[(kShellParts + j) * nshell + s], dk[j]);
     }
   }
-  if (over) atomicOr(overflow, 1);
+  if (over) atomicOr(overflow, 1ull);
   __syncthreads();
   for (int i = threadIdx.x; i < nh; i += blockDim.x)
     if (hist[i] != 0ull) atomicAdd(&shells[i], hist[i]);
 }
 
-// tmp = i kappa_a u_hat_a on the half spectrum; the Nyquist wavenumber of
-// the derivative direction is set to zero.
-__global__ __launch_bounds__(256) void deriv_kernel(const hipfftDoubleComplex *__restrict__ uha,
-                                                    hipfftDoubleComplex *__restrict__ out, int n, int64_t nhalf,
-                                                    int axis) {
-  const int64_t m = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (m >= nhalf) return;
-  const int nxh = n / 2 + 1;
-  const int kxh = (int)(m % nxh);
-  const int64_t r = m / nxh;
-  const int iy = (int)(r % n), iz = (int)(r / n);
-  int k = axis == 0 ? kxh : (axis == 1 ? signed_k(iy, n) : signed_k(iz, n));
-  if ((n % 2 == 0) && (2 * k == n || 2 * k == -n)) k = 0;
-  const double kap = 2.0 * M_PI / n * k;
-  const hipfftDoubleComplex v = uha[m];
-  hipfftDoubleComplex o;
-  o.x = -kap * v.y;
-  o.y = kap * v.x;
-  out[m] = o;
-}
-
-// Component a of the vorticity on the half spectrum, scaled by `scale`:
-// out = scale i (kappa_b u_hat_c - kappa_c u_hat_b), (a, b, c) cyclic; the
-// Nyquist wavenumber of each derivative direction is set to zero, as in
-// deriv_kernel.
-__global__ __launch_bounds__(256) void curl_kernel(const hipfftDoubleComplex *__restrict__ uh,
-                                                   hipfftDoubleComplex *__restrict__ out, int n, int64_t nhalf,
-                                                   int a, double scale) {
+// u_hat -> spectrum of the vorticity, in place and scaled by `scale`:
+// component a becomes scale i (kappa_b u_hat_c - kappa_c u_hat_b), (a, b, c)
+// cyclic, the Nyquist wavenumber of each derivative direction dropped.
+__global__ __launch_bounds__(256) void curl_kernel(hipfftDoubleComplex *__restrict__ uh, int n, int64_t nhalf,
+                                                   double scale) {
   const int64_t m = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (m >= nhalf) return;
   const int nxh = n / 2 + 1;
   const int64_t r = m / nxh;
-  int k[3] = {(int)(m % nxh), signed_k((int)(r % n), n), signed_k((int)(r / n), n)};
-  for (int i = 0; i < 3; ++i)
-    if ((n % 2 == 0) && (2 * k[i] == n || 2 * k[i] == -n)) k[i] = 0;
-  const int b = (a + 1) % 3, c = (a + 2) % 3;
-  const double kb = 2.0 * M_PI / n * k[b], kc = 2.0 * M_PI / n * k[c];
-  const hipfftDoubleComplex ub = uh[(int64_t)b * nhalf + m], uc = uh[(int64_t)c * nhalf + m];
-  // i (kb uc - kc ub)
-  const double re = kb * uc.x - kc * ub.x, im = kb * uc.y - kc * ub.y;
-  hipfftDoubleComplex o;
-  o.x = -im * scale;
-  o.y = re * scale;
-  out[m] = o;
+  const double kfac = 2.0 * M_PI / n;
+  const double k[3] = {kfac * derivative_k((int)(m % nxh), n), kfac * derivative_k(signed_k((int)(r % n), n), n),
+                       kfac * derivative_k(signed_k((int)(r / n), n), n)};
+  hipfftDoubleComplex v[3];
+  static_for<3>([&](auto c) { v[c] = uh[(int64_t)c * nhalf + m]; });
+  static_for<3>([&](auto a) {
+    constexpr int b = (a + 1) % 3, c = (a + 2) % 3;
+    const double re = k[b] * v[c].x - k[c] * v[b].x, im = k[b] * v[c].y - k[c] * v[b].y;
+    uh[(int64_t)a * nhalf + m] = make_double2(-im * scale, re * scale);
+  });
 }
 
 // Spectrum of the velocity-gradient component d_a u_b, scaled by `scale`:
 // out = scale i kappa_a u_hat_b on the half spectrum, the Nyquist
-// wavenumber of the derivative direction set to zero (as deriv_kernel).
+// wavenumber of the derivative direction set to zero.
 __global__ __launch_bounds__(256) void gradient_kernel(const hipfftDoubleComplex *__restrict__ uhb,
                                                        hipfftDoubleComplex *__restrict__ out, int n, int64_t nhalf,
                                                        int a, double scale) {
@@ -163,9 +153,8 @@ __global__ __launch_bounds__(256) void gradient_kernel(const hipfftDoubleComplex
   if (m >= nhalf) return;
   const int nxh = n / 2 + 1;
   const int64_t r = m / nxh;
-  int k = a == 0 ? (int)(m % nxh) : (a == 1 ? signed_k((int)(r % n), n) : signed_k((int)(r / n), n));
-  if ((n % 2 == 0) && (2 * k == n || 2 * k == -n)) k = 0;
-  const double kap = 2.0 * M_PI / n * k * scale;
+  const int k = a == 0 ? (int)(m % nxh) : (a == 1 ? signed_k((int)(r % n), n) : signed_k((int)(r / n), n));
+  const double kap = 2.0 * M_PI / n * derivative_k(k, n) * scale;
   const hipfftDoubleComplex v = uhb[m];
   hipfftDoubleComplex o;
   o.x = -kap * v.y;
@@ -202,9 +191,8 @@ __global__ __launch_bounds__(256) void pressure_source_kernel(const hipfftDouble
   if (m >= nhalf) return;
   const int nxh = n / 2 + 1;
   const int64_t r = m / nxh;
-  int k[3] = {(int)(m % nxh), signed_k((int)(r % n), n), signed_k((int)(r / n), n)};
-  for (int i = 0; i < 3; ++i)
-    if ((n % 2 == 0) && (2 * k[i] == n || 2 * k[i] == -n)) k[i] = 0;
+  const int k[3] = {derivative_k((int)(m % nxh), n), derivative_k(signed_k((int)(r % n), n), n),
+                    derivative_k(signed_k((int)(r / n), n), n)};
   double re = 0.0, im = 0.0;
   for (int c = 0; c < 3; ++c) {
     const double w = set == 0 ? (double)k[c] * k[c] : 2.0 * (double)k[c] * k[(c + 1) % 3];
@@ -235,10 +223,12 @@ __global__ __launch_bounds__(256) void inverse_laplacian_kernel(hipfftDoubleComp
   acc[m].y *= f;
 }
 
-// Sums of d^2, d^3, d^4 of a real field scaled by `scale`.
+// Sums of d^2, d^3, d^4 of three real fields scaled by `scale` (field
+// blockIdx.y): partials [3][5][gridDim.x].
 __global__ __launch_bounds__(kBlock) void power_sums_kernel(const double *__restrict__ d, int64_t ncell, double scale,
                                                             double *__restrict__ partials) {
   double v[kNumSums] = {0, 0, 0, 0, 0};
+  d += (int64_t)blockIdx.y * ncell;
   for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < ncell; i += (int64_t)gridDim.x * kBlock) {
     const double x = d[i] * scale;
     const double x2 = x * x;
@@ -246,50 +236,95 @@ __global__ __launch_bounds__(kBlock) void power_sums_kernel(const double *__rest
     v[1] += x2 * x;
     v[2] += x2 * x2;
   }
-  write_block_partials(v, partials, gridDim.x, blockIdx.x);
+  write_block_partials(v, partials + (int64_t)blockIdx.y * kNumSums * gridDim.x, gridDim.x, blockIdx.x);
+}
+// Adds them up: block a the partials of field a, into out[a][5].
+__global__ __launch_bounds__(kBlock) void power_totals_kernel(const double *__restrict__ partials, int nblocks,
+                                                              double *__restrict__ out) {
+  __shared__ double smem[kWaves][kNumSums];
+  double v[kNumSums] = {0, 0, 0, 0, 0};
+  const double *p = partials + (int64_t)blockIdx.x * kNumSums * nblocks;
+  for (int b = threadIdx.x; b < nblocks; b += kBlock)
+    static_for<kNumSums>([&](auto i) { v[i] += p[(int64_t)i * nblocks + b]; });
+  const double t = block_sum5<kWaves>(v, smem);
+  if (threadIdx.x < kNumSums) out[blockIdx.x * kNumSums + threadIdx.x] = t;
+}
+
+// Words of SpectrumWork::result.
+static size_t shell_words(int nshell) { return 2 * kShellParts * (size_t)nshell; }
+static size_t result_words(int nshell) { return shell_words(nshell) + 15 + 1; }
+
+static hipfftResult plan_of(hipfftHandle *h, int n, bool forward, int batch) {
+  int dims[3] = {n, n, n};
+  const int ncell = n * n * n, nhalf = n * n * (n / 2 + 1);
+  return forward ? hipfftPlanMany(h, 3, dims, nullptr, 1, ncell, nullptr, 1, nhalf, HIPFFT_D2Z, batch)
+                 : hipfftPlanMany(h, 3, dims, nullptr, 1, nhalf, nullptr, 1, ncell, HIPFFT_Z2D, batch);
 }
 
 static void ensure_work(dhit_box &b) {
-  if (b.spec) return;
-  SpectrumWork *w = new SpectrumWork();
-  b.spec = w;
-  const int n = b.n;
-  w->n = n;
-  w->nhalf = (int64_t)n * n * (n / 2 + 1);
-  w->nshell = (int)std::floor(std::sqrt(3.0) * (n / 2 + 1)) + 2;
-  if (hipMalloc(&w->u, 3 * b.ncell * sizeof(double)) != hipSuccess ||
-      hipMalloc(&w->uh, 3 * w->nhalf * sizeof(hipfftDoubleComplex)) != hipSuccess ||
-      hipMalloc(&w->tmp, w->nhalf * sizeof(hipfftDoubleComplex)) != hipSuccess ||
-      hipMalloc(&w->shells, 2 * kShellParts * w->nshell * sizeof(unsigned long long)) != hipSuccess ||
-      hipMalloc(&w->overflow, sizeof(int)) != hipSuccess ||
-      hipMalloc(&w->partials, 5 * 1024 * sizeof(double)) != hipSuccess ||
-      hipMalloc(&w->dstats, 3 * 5 * sizeof(double)) != hipSuccess)
+  if (!b.spec) {
+    SpectrumWork *w = new SpectrumWork();
+    b.spec = w;
+    const int n = b.n;
+    w->n = n;
+    w->nhalf = (int64_t)n * n * (n / 2 + 1);
+    w->nshell = (int)std::floor(std::sqrt(3.0) * (n / 2 + 1)) + 2;
+    if (hipMalloc(&w->u, 3 * b.ncell * sizeof(double)) != hipSuccess ||
+        hipMalloc(&w->uh, 3 * w->nhalf * sizeof(hipfftDoubleComplex)) != hipSuccess ||
+        hipMalloc(&w->result, result_words(w->nshell) * sizeof(unsigned long long)) != hipSuccess ||
+        hipMalloc(&w->partials, 3 * 5 * kPowerBlocks * sizeof(double)) != hipSuccess)
+      throw Error(DHIT_ENOMEM, "cannot allocate spectrum work space");
+    DHIT_FFT(plan_of(&w->fwd, n, true, 3));
+    w->have_fwd = true;
+  }
+  DHIT_FFT(hipfftSetStream(b.spec->fwd, b.stream));
+}
+
+// The inverse transform of three fields.
+static hipfftHandle inverse3(dhit_box &b) {
+  SpectrumWork &w = *b.spec;
+  if (!w.have_inv3) {
+    DHIT_FFT(plan_of(&w.inv3, b.n, false, 3));
+    w.have_inv3 = true;
+  }
+  DHIT_FFT(hipfftSetStream(w.inv3, b.stream));
+  return w.inv3;
+}
+
+// The inverse transform of one field, and the half spectrum it starts from.
+static hipfftHandle inverse1(dhit_box &b) {
+  SpectrumWork &w = *b.spec;
+  if (!w.tmp && hipMalloc(&w.tmp, w.nhalf * sizeof(hipfftDoubleComplex)) != hipSuccess) {
+    w.tmp = nullptr;
     throw Error(DHIT_ENOMEM, "cannot allocate spectrum work space");
-  int dims[3] = {n, n, n};
-  DHIT_FFT(hipfftPlanMany(&w->fwd, 3, dims, nullptr, 1, (int)b.ncell, nullptr, 1, (int)w->nhalf, HIPFFT_D2Z, 3));
-  w->have_fwd = true;
-  DHIT_FFT(hipfftPlanMany(&w->inv, 3, dims, nullptr, 1, (int)w->nhalf, nullptr, 1, (int)b.ncell, HIPFFT_Z2D, 1));
-  w->have_inv = true;
+  }
+  if (!w.have_inv1) {
+    DHIT_FFT(plan_of(&w.inv1, b.n, false, 1));
+    w.have_inv1 = true;
+  }
+  DHIT_FFT(hipfftSetStream(w.inv1, b.stream));
+  return w.inv1;
 }
 
 // Device bytes of the spectrum work space of an n^3 box: the arrays of
-// ensure_work and the work areas of its two hipFFT plans (made here with
-// automatic allocation off, so nothing is allocated).
+// ensure_work and inverse1 and the work areas of its three hipFFT plans (made
+// here with automatic allocation off, so nothing is allocated).
 int64_t spectrum_work_bytes(int n) {
   const int64_t ncell = (int64_t)n * n * n, nhalf = (int64_t)n * n * (n / 2 + 1);
   const int64_t nshell = (int64_t)std::floor(std::sqrt(3.0) * (n / 2 + 1)) + 2;
   int64_t bytes = 3 * ncell * (int64_t)sizeof(double) + 4 * nhalf * (int64_t)sizeof(hipfftDoubleComplex) +
-                  2 * kShellParts * nshell * (int64_t)sizeof(unsigned long long) + (int64_t)sizeof(int) +
-                  5 * 1024 * (int64_t)sizeof(double) + 15 * (int64_t)sizeof(double);
+                  (int64_t)(result_words((int)nshell) * sizeof(unsigned long long)) +
+                  3 * 5 * kPowerBlocks * (int64_t)sizeof(double);
   int dims[3] = {n, n, n};
-  for (int dir = 0; dir < 2; ++dir) {
+  for (int plan = 0; plan < 3; ++plan) {
     hipfftHandle h = 0;
     DHIT_FFT(hipfftCreate(&h));
     size_t work = 0;
     hipfftResult r = hipfftSetAutoAllocation(h, 0);
     if (r == HIPFFT_SUCCESS)
-      r = dir == 0 ? hipfftMakePlanMany(h, 3, dims, nullptr, 1, (int)ncell, nullptr, 1, (int)nhalf, HIPFFT_D2Z, 3, &work)
-                   : hipfftMakePlanMany(h, 3, dims, nullptr, 1, (int)nhalf, nullptr, 1, (int)ncell, HIPFFT_Z2D, 1, &work);
+      r = plan == 0 ? hipfftMakePlanMany(h, 3, dims, nullptr, 1, (int)ncell, nullptr, 1, (int)nhalf, HIPFFT_D2Z, 3, &work)
+                    : hipfftMakePlanMany(h, 3, dims, nullptr, 1, (int)nhalf, nullptr, 1, (int)ncell, HIPFFT_Z2D,
+                                         plan == 1 ? 3 : 1, &work);
     hipfftDestroy(h);
     if (r != HIPFFT_SUCCESS) throw Error(DHIT_EDEVICE, "hipfftMakePlanMany failed, code " + std::to_string((int)r));
     bytes += (int64_t)work;
@@ -301,14 +336,13 @@ void spectrum_free(dhit_box &b) {
   SpectrumWork *w = b.spec;
   if (!w) return;
   if (w->have_fwd) hipfftDestroy(w->fwd);
-  if (w->have_inv) hipfftDestroy(w->inv);
+  if (w->have_inv3) hipfftDestroy(w->inv3);
+  if (w->have_inv1) hipfftDestroy(w->inv1);
   if (w->u) (void)hipFree(w->u);
   if (w->uh) (void)hipFree(w->uh);
   if (w->tmp) (void)hipFree(w->tmp);
-  if (w->shells) (void)hipFree(w->shells);
-  if (w->overflow) (void)hipFree(w->overflow);
+  if (w->result) (void)hipFree(w->result);
   if (w->partials) (void)hipFree(w->partials);
-  if (w->dstats) (void)hipFree(w->dstats);
   delete w;
   b.spec = nullptr;
 }
@@ -317,39 +351,30 @@ void spectrum_compute(dhit_box &b, double *E_host, int kmax, double *stats_host)
   ensure_work(b);
   SpectrumWork &w = *b.spec;
   const int n = b.n;
-  DHIT_FFT(hipfftSetStream(w.fwd, b.stream));
-  DHIT_FFT(hipfftSetStream(w.inv, b.stream));
+  const hipfftHandle inv = inverse3(b);
   launch_velocity(b, b.f[b.cur], w.u);
   DHIT_FFT(hipfftExecD2Z(w.fwd, w.u, w.uh));
-  const size_t shell_words = 2 * kShellParts * (size_t)w.nshell;
-  DHIT_HIP(hipMemsetAsync(w.shells, 0, shell_words * sizeof(unsigned long long), b.stream));
-  DHIT_HIP(hipMemsetAsync(w.overflow, 0, sizeof(int), b.stream));
+  const size_t shells = shell_words(w.nshell), words = result_words(w.nshell);
+  double *dstats = reinterpret_cast<double *>(w.result + shells);
+  DHIT_HIP(hipMemsetAsync(w.result, 0, words * sizeof(unsigned long long), b.stream));
   const double inv_n3 = 1.0 / ((double)n * n * n);
   {
     const int blocks = (int)std::min<int64_t>((w.nhalf + 255) / 256, 2048);
-    hipLaunchKernelGGL(bin_kernel, dim3(blocks), dim3(256), shell_words * sizeof(unsigned long long), b.stream, w.uh,
-                       n, w.nhalf, w.nshell, inv_n3 * inv_n3, w.shells, w.overflow);
+    hipLaunchKernelGGL(bin_kernel, dim3(blocks), dim3(256), shells * sizeof(unsigned long long), b.stream, w.uh, n,
+                       w.nhalf, w.nshell, inv_n3 * inv_n3, w.result, w.result + words - 1);
     DHIT_HIP(hipGetLastError());
   }
-  for (int a = 0; a < 3; ++a) {
-    const int blocks = (int)((w.nhalf + 255) / 256);
-    hipLaunchKernelGGL(deriv_kernel, dim3(blocks), dim3(256), 0, b.stream, w.uh + a * w.nhalf, w.tmp, n, w.nhalf, a);
-    DHIT_HIP(hipGetLastError());
-    DHIT_FFT(hipfftExecZ2D(w.inv, w.tmp, w.u));  // overwrites u[0 .. ncell)
-    const int rb = (int)std::min<int64_t>((b.ncell + kBlock - 1) / kBlock, 1024);
-    hipLaunchKernelGGL(power_sums_kernel, dim3(rb), dim3(kBlock), 0, b.stream, w.u, b.ncell, inv_n3, w.partials);
-    DHIT_HIP(hipGetLastError());
-    launch_finalize_sums(b, w.partials, rb, w.dstats + 5 * a);
-  }
-  std::vector<unsigned long long> dig(shell_words);
-  double ds[15];
-  int over = 0;
-  DHIT_HIP(hipMemcpyAsync(dig.data(), w.shells, shell_words * sizeof(unsigned long long), hipMemcpyDeviceToHost,
-                          b.stream));
-  DHIT_HIP(hipMemcpyAsync(ds, w.dstats, sizeof(ds), hipMemcpyDeviceToHost, b.stream));
-  DHIT_HIP(hipMemcpyAsync(&over, w.overflow, sizeof(int), hipMemcpyDeviceToHost, b.stream));
+  DHIT_FFT(hipfftExecZ2D(inv, w.uh, w.u));
+  const int rb = (int)std::min<int64_t>((b.ncell + kBlock - 1) / kBlock, kPowerBlocks);
+  hipLaunchKernelGGL(power_sums_kernel, dim3(rb, 3), dim3(kBlock), 0, b.stream, w.u, b.ncell, inv_n3, w.partials);
+  hipLaunchKernelGGL(power_totals_kernel, dim3(3), dim3(kBlock), 0, b.stream, w.partials, rb, dstats);
+  DHIT_HIP(hipGetLastError());
+  std::vector<unsigned long long> dig(words);
+  DHIT_HIP(hipMemcpyAsync(dig.data(), w.result, words * sizeof(unsigned long long), hipMemcpyDeviceToHost, b.stream));
   DHIT_HIP(hipStreamSynchronize(b.stream));
-  if (over) throw Error(DHIT_ENONFINITE, "velocity field is not finite (or a spectral term exceeds 2^8)");
+  double ds[15];
+  std::memcpy(ds, dig.data() + shells, sizeof(ds));
+  if (dig[words - 1]) throw Error(DHIT_ENONFINITE, "velocity field is not finite (or a spectral term exceeds 2^8)");
   // join the digits of each shell: sum_j digit_j 2^(34 j), then times 2^-88
   std::vector<double> sh(2 * w.nshell);
   for (int q = 0; q < 2; ++q)
@@ -387,8 +412,7 @@ void pressure_compute(dhit_box &b, const double *u_host, double *drho_host) {
   ensure_work(b);
   SpectrumWork &w = *b.spec;
   const int n = b.n;
-  DHIT_FFT(hipfftSetStream(w.fwd, b.stream));
-  DHIT_FFT(hipfftSetStream(w.inv, b.stream));
+  const hipfftHandle inv = inverse1(b);
   double *du = nullptr;
   if (hipMalloc(&du, 3 * b.ncell * sizeof(double)) != hipSuccess)
     throw Error(DHIT_ENOMEM, "cannot allocate the velocity upload buffer");
@@ -406,7 +430,7 @@ void pressure_compute(dhit_box &b, const double *u_host, double *drho_host) {
     const double scale = -3.0 * b.p.rho0 / ((double)n * n * n);
     hipLaunchKernelGGL(inverse_laplacian_kernel, dim3(mb), dim3(256), 0, b.stream, w.tmp, n, w.nhalf, scale);
     DHIT_HIP(hipGetLastError());
-    DHIT_FFT(hipfftExecZ2D(w.inv, w.tmp, w.u));
+    DHIT_FFT(hipfftExecZ2D(inv, w.tmp, w.u));
     copy_to_host({{drho_host, w.u, b.ncell * sizeof(double)}}, b.stream);
   } catch (...) {
     (void)hipStreamSynchronize(b.stream);
@@ -420,8 +444,7 @@ void gradient_compute(dhit_box &b, const double *d_u, double *d_grad) {
   ensure_work(b);
   SpectrumWork &w = *b.spec;
   const int n = b.n;
-  DHIT_FFT(hipfftSetStream(w.fwd, b.stream));
-  DHIT_FFT(hipfftSetStream(w.inv, b.stream));
+  const hipfftHandle inv = inverse1(b);
   DHIT_HIP(hipMemcpyAsync(w.u, d_u, 3 * b.ncell * sizeof(double), hipMemcpyDeviceToDevice, b.stream));
   DHIT_FFT(hipfftExecD2Z(w.fwd, w.u, w.uh));
   const double inv_n3 = 1.0 / ((double)n * n * n);  // both transforms are unnormalised
@@ -431,7 +454,7 @@ void gradient_compute(dhit_box &b, const double *d_u, double *d_grad) {
       hipLaunchKernelGGL(gradient_kernel, dim3(blocks), dim3(256), 0, b.stream, w.uh + (int64_t)c * w.nhalf, w.tmp, n,
                          w.nhalf, a, inv_n3);
       DHIT_HIP(hipGetLastError());
-      DHIT_FFT(hipfftExecZ2D(w.inv, w.tmp, d_grad + (int64_t)(3 * a + c) * b.ncell));
+      DHIT_FFT(hipfftExecZ2D(inv, w.tmp, d_grad + (int64_t)(3 * a + c) * b.ncell));
     }
 }
 
@@ -439,17 +462,14 @@ void vorticity_compute(dhit_box &b, double *omega_host) {
   ensure_work(b);
   SpectrumWork &w = *b.spec;
   const int n = b.n;
-  DHIT_FFT(hipfftSetStream(w.fwd, b.stream));
-  DHIT_FFT(hipfftSetStream(w.inv, b.stream));
+  const hipfftHandle inv = inverse3(b);
   launch_velocity(b, b.f[b.cur], w.u);
   DHIT_FFT(hipfftExecD2Z(w.fwd, w.u, w.uh));
   const double inv_n3 = 1.0 / ((double)n * n * n);  // both transforms are unnormalised
   const int blocks = (int)((w.nhalf + 255) / 256);
-  for (int a = 0; a < 3; ++a) {
-    hipLaunchKernelGGL(curl_kernel, dim3(blocks), dim3(256), 0, b.stream, w.uh, w.tmp, n, w.nhalf, a, inv_n3);
-    DHIT_HIP(hipGetLastError());
-    DHIT_FFT(hipfftExecZ2D(w.inv, w.tmp, w.u + (int64_t)a * b.ncell));
-  }
+  hipLaunchKernelGGL(curl_kernel, dim3(blocks), dim3(256), 0, b.stream, w.uh, n, w.nhalf, inv_n3);
+  DHIT_HIP(hipGetLastError());
+  DHIT_FFT(hipfftExecZ2D(inv, w.uh, w.u));
   copy_to_host({{omega_host, w.u, 3 * b.ncell * sizeof(double)}}, b.stream);
 }
 
