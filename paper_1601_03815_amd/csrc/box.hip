@@ -510,12 +510,11 @@ int32_t init_consistent(dhit_box *b, const double *u, const double *drho, int32_
           DHIT_HIP(hipMemsetAsync(dprev, 0, bytes, b->stream));
       }
       for (int32_t k = 0; k < iters; ++k) {
+        // the last pass compares drho with that of the pass before it
         const bool last = k == iters - 1;
-        double *slot = b->hist + (k % dhit::kHistoryCap) * 5;
-        dhit::launch_lbe_step(*b, b->f[b->cur], b->f[1 - b->cur], slot);
+        dhit::launch_lbe_hold(*b, b->f[b->cur], b->f[1 - b->cur], du, k == iters - 2 ? dprev : nullptr,
+                              last ? dprev : nullptr, last ? dmax : nullptr);
         b->cur = 1 - b->cur;
-        dhit::launch_hold_velocity(*b, b->f[b->cur], du, last ? nullptr : dprev, last ? dprev : nullptr,
-                                   last ? dmax : nullptr);
       }
       double res = 0.0;
       if (iters > 0) {

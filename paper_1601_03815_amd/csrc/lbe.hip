@@ -88,20 +88,17 @@ __device__ __forceinline__ Run<Real, C> load_run(const global_t<Real> *row, int 
   return r;
 }
 
-// Update of the C cells starting at `cell` (same row); adds their moments
-// to the block's sums v.
-template <int K, int C, typename Real>
-__device__ __forceinline__ void lbe_run(const global_t<Real> *__restrict__ src, global_t<Real> *__restrict__ dst,
-                                        const StepParams &p, int cell, double (&v)[kNumSums]) {
-  const int n = p.n;
-  const int64_t stride = p.stride;
+// Pull of the C cells starting at `cell` (same row): f[k][q] = the value that
+// streams into cell + k along xi_q.
+template <int C, typename Real>
+__device__ __forceinline__ void pull(const global_t<Real> *__restrict__ src, int n, int64_t stride, int cell,
+                                     Real (&f)[C][kQ]) {
   const int x = cell % n;
   const int t = cell / n;
   const int y = t % n;
   const int z = t / n;
   const int row = cell - x;
   const AxisOff oy = axis_offsets(y, n, n), oz = axis_offsets(z, n, n * n);
-  Real f[C][kQ];
   static_for<kQ>([&](auto q) {
     // source row of the cells - xi_q
     int off = row;
@@ -113,6 +110,15 @@ __device__ __forceinline__ void lbe_run(const global_t<Real> *__restrict__ src, 
 #pragma unroll
     for (int k = 0; k < C; ++k) f[k][q] = r.v[k];
   });
+}
+
+// Update of the C cells starting at `cell` (same row); adds their moments
+// to the block's sums v.
+template <int K, int C, typename Real>
+__device__ __forceinline__ void lbe_run(const global_t<Real> *__restrict__ src, global_t<Real> *__restrict__ dst,
+                                        const StepParams &p, int cell, double (&v)[kNumSums]) {
+  Real f[C][kQ];
+  pull<C, Real>(src, p.n, p.stride, cell, f);
 #pragma unroll
   for (int k = 0; k < C; ++k) {
     Real drho, jx, jy, jz;
@@ -122,7 +128,7 @@ __device__ __forceinline__ void lbe_run(const global_t<Real> *__restrict__ src, 
   }
   // the new state is read only by the next step: stream it past the caches
   static_for<kQ>([&](auto q) {
-    global_t<Real> *d = dst + (int64_t)q * stride + cell;
+    global_t<Real> *d = dst + (int64_t)q * p.stride + cell;
     if constexpr (C == 1) {
       __builtin_nontemporal_store(f[0][q], d);
     } else {
@@ -133,6 +139,91 @@ __device__ __forceinline__ void lbe_run(const global_t<Real> *__restrict__ src, 
       __builtin_nontemporal_store(w, reinterpret_cast<global_t<Vec> *>(d));
     }
   });
+}
+
+// One pass of the initial-state iteration of an LBE box (Sec. IV.A: the
+// kinetic schemes start from the density fluctuation and non-equilibrium
+// part that belong to the initial velocity, found by running the scheme
+// with the velocity held at its initial value): a time step from src, then
+// every cell's momentum put back to rho0 u while its density and its
+// non-equilibrium part are kept, f += E(drho, rho0 u) - E(drho, j), with E
+// the state init_kernel builds, into dst.  Both collisions conserve drho and j
+// and relax only f - E, so the update gives the same result on the
+// post-collision state as on the pre-collision one.
+// drho_out (optional) receives drho; with drho_prev and block_max given,
+// block b stores the largest |drho - drho_prev| of its cells in block_max[b].
+// Bound by memory: one pass reads and writes the state once (as a step and a
+// pass of its own, with the sums nobody asked for, 34 us at 64^3 in FP64;
+// now 17).
+template <int K, typename Real>
+__global__ __launch_bounds__(kBlock) void lbe_hold_kernel(const Real *__restrict__ src, Real *__restrict__ dst,
+                                                          const double *__restrict__ u, double *__restrict__ drho_out,
+                                                          const double *__restrict__ drho_prev,
+                                                          double *__restrict__ block_max, StepParams p, int ncell) {
+  __shared__ double wave_max[kWaves];
+  const int cell = blockIdx.x * kBlock + threadIdx.x;
+  double dev = 0.0;
+  if (cell < ncell) {
+    Real g[1][kQ];
+    pull<1, Real>(to_global(src), p.n, p.stride, cell, g);
+    Real (&f)[kQ] = g[0];
+    Real r, jx, jy, jz;
+    cell_moments<Real>(f, r, jx, jy, jz);
+    collide<K, Real>(f, r, jx, jy, jz, p);
+    cell_moments<Real>(f, r, jx, jy, jz);
+    const Real hx = Real(p.rho0 * u[cell]);
+    const Real hy = Real(p.rho0 * u[(int64_t)ncell + cell]);
+    const Real hz = Real(p.rho0 * u[2 * (int64_t)ncell + cell]);
+    Real held[kQ], now[kQ];
+    if constexpr (K == kMRT) {
+      mrt_equilibrium_populations<Real>(r, hx, hy, hz, p, held);
+      mrt_equilibrium_populations<Real>(r, jx, jy, jz, p, now);
+    } else {
+      equilibrium<Real>(r, hx, hy, hz, Real(p.rho0), Real(p.inv_rho0), held);
+      equilibrium<Real>(r, jx, jy, jz, Real(p.rho0), Real(p.inv_rho0), now);
+    }
+    static_for<kQ>([&](auto q) {
+      __builtin_nontemporal_store(f[q] + (held[q] - now[q]), to_global(dst) + (int64_t)q * p.stride + cell);
+    });
+    if (drho_out) drho_out[cell] = (double)r;
+    if (drho_prev) {
+      dev = fabs((double)r - drho_prev[cell]);
+      if (!(dev < INFINITY)) dev = INFINITY;  // a NaN must survive the fmax reduction
+    }
+  }
+  if (!block_max) return;
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) dev = fmax(dev, __shfl_down(dev, off, 64));
+  if ((threadIdx.x & 63) == 0) wave_max[threadIdx.x >> 6] = dev;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double m = wave_max[0];
+    for (int w = 1; w < kWaves; ++w) m = fmax(m, wave_max[w]);
+    block_max[blockIdx.x] = m;
+  }
+}
+
+template <typename Real>
+static void hold_launch(dhit_box &b, const void *src, void *dst, const double *d_u, double *d_drho_out,
+                        const double *d_drho_prev, double *d_block_max) {
+  const Real *s = static_cast<const Real *>(src);
+  Real *d = static_cast<Real *>(dst);
+  const int blocks = cell_blocks(b.ncell), n = (int)b.ncell;
+  if (b.p.method == DHIT_LBE_MRT)
+    hipLaunchKernelGGL((lbe_hold_kernel<kMRT, Real>), dim3(blocks), dim3(kBlock), 0, b.stream, s, d, d_u, d_drho_out,
+                       d_drho_prev, d_block_max, b.sp, n);
+  else
+    hipLaunchKernelGGL((lbe_hold_kernel<kBGK, Real>), dim3(blocks), dim3(kBlock), 0, b.stream, s, d, d_u, d_drho_out,
+                       d_drho_prev, d_block_max, b.sp, n);
+}
+
+void launch_lbe_hold(dhit_box &b, const void *src, void *dst, const double *d_u, double *d_drho_out,
+                     const double *d_drho_prev, double *d_block_max) {
+  if (b.p.precision == DHIT_FP64)
+    hold_launch<double>(b, src, dst, d_u, d_drho_out, d_drho_prev, d_block_max);
+  else
+    hold_launch<float>(b, src, dst, d_u, d_drho_out, d_drho_prev, d_block_max);
+  DHIT_HIP(hipGetLastError());
 }
 
 // One launch advances one or many boxes: work item = a run of B * C cells of
