@@ -64,10 +64,15 @@ int32_t guarded(F &&f) {
 // shift suits each kernel's access pattern (measured at 256^3): 3 KiB for the
 // LBE, whose 19 streams advance together (in sweeps of 0.5 to 9 KiB the FP64
 // step was fastest at 3 KiB: 1% faster than at 1 KiB, 4% than at 4 KiB;
-// FP32 alike within 1%), 16 KiB for the DUGKS march (1 KiB made it 4% slower).
+// FP32 alike within 1%); 2.25 KiB for the DUGKS march, whose tiles read 19
+// populations x 8 rows of 256 bytes per plane: with odd multiples of 256 bytes
+// the populations of a row segment fall on different channels (FP64 256^3
+// 1.72 ms, 128^3 226 us; multiples of 1 KiB, 16 KiB among them, 1.75-1.81 ms
+// and 232 us; FP32 256^3 0.875 against 0.89 ms; odd multiples from 0.25 to
+// 33 KiB alike within 2%).
 int64_t padded_stride(int64_t ncell, size_t elem, int method) {
   const int64_t align = 256 / (int64_t)elem;
-  const int64_t shift = (method == DHIT_DUGKS ? 16384 : 3072) / (int64_t)elem;
+  const int64_t shift = (method == DHIT_DUGKS ? 2304 : 3072) / (int64_t)elem;
   return ((ncell + align - 1) / align) * align + shift;
 }
 
