@@ -146,17 +146,34 @@ struct Unit {
   static constexpr int x = T == 0, y = T == 1, z = T == 2;
 };
 
-// Value of the previous lane of the wavefront (lane 0 gets 0): a DPP
-// whole-wavefront shift right by one lane, one move per 32 bits.
-__device__ __forceinline__ int from_previous_lane(int v) { return __builtin_amdgcn_update_dpp(0, v, 0x138, 0xf, 0xf, false); }
-__device__ __forceinline__ float from_previous_lane(float v) {
-  return __builtin_bit_cast(float, from_previous_lane(__builtin_bit_cast(int, v)));
+// Value of the previous / next lane of the wavefront (lane 0 / 63 gets 0): a
+// DPP whole-wavefront shift by one lane, one move per 32 bits.
+template <int Ctrl>
+__device__ __forceinline__ int lane_shift(int v) { return __builtin_amdgcn_update_dpp(0, v, Ctrl, 0xf, 0xf, true); }
+template <int Ctrl>
+__device__ __forceinline__ float lane_shift(float v) {
+  return __builtin_bit_cast(float, lane_shift<Ctrl>(__builtin_bit_cast(int, v)));
 }
-__device__ __forceinline__ double from_previous_lane(double v) {
+template <int Ctrl>
+__device__ __forceinline__ double lane_shift(double v) {
   const long long b = __builtin_bit_cast(long long, v);
-  const int lo = from_previous_lane((int)b), hi = from_previous_lane((int)(b >> 32));
+  const int lo = lane_shift<Ctrl>((int)b), hi = lane_shift<Ctrl>((int)(b >> 32));
   return __builtin_bit_cast(double, ((long long)hi << 32) | (long long)(unsigned)lo);
 }
+template <typename T>
+__device__ __forceinline__ T from_previous_lane(T v) { return lane_shift<0x138>(v); }
+template <typename T>
+__device__ __forceinline__ T from_next_lane(T v) { return lane_shift<0x130>(v); }
+// Whether the corner neighbours (x+-1, y+-1) of an in-plane diagonal population
+// come as lane shifts of the (x, y+-1) values (a tile row is consecutive
+// lanes) instead of LDS reads.  FP64: a plane's LDS traffic and its vector work
+// take about as long as each other and add up, and a shift costs two of a
+// SIMD's moves against a 512-byte read of the LDS all four SIMDs share; with
+// the trimmed exchanges of the split march 256^3 1.72 -> 1.70 ms, 128^3
+// 224 us either way, 64^3 43.6 -> 41.9 us.  FP32 is bound by vector issue:
+// 1-3% slower with the shifts.
+template <typename Real>
+constexpr bool kLaneCorners = sizeof(Real) == 8;
 
 // Reads of one plane: populations from P, in-plane moment fields from Q,
 // z-differentiated fields from Z (each offset to the thread's column; a
@@ -736,9 +753,17 @@ struct InPlaneCoef<Real, W, true> {
     constexpr int i = kCx[Q] > 0 ? 0 : 1, j = kCy[Q] > 0 ? 0 : 1;
     const Real p1 = g.template at<Q, 1, 0>(), m1 = g.template at<Q, -1, 0>();
     const Real p2 = g.template at<Q, 0, 1>(), m2 = g.template at<Q, 0, -1>();
-    const Real pp = g.template at<Q, 1, 1>(), pm = g.template at<Q, 1, -1>();
-    const Real mp = g.template at<Q, -1, 1>(), mm = g.template at<Q, -1, -1>();
     const Real b0 = g.template at<Q, 0, 0>();
+    Real pp, pm, mp, mm;
+    if constexpr (kLaneCorners<Real>) {
+      if constexpr (G::use) {
+        pp = from_next_lane(p2), pm = from_next_lane(m2);
+        mp = from_previous_lane(p2), mm = from_previous_lane(m2);
+      }
+    } else {
+      pp = g.template at<Q, 1, 1>(), pm = g.template at<Q, 1, -1>();
+      mp = g.template at<Q, -1, 1>(), mm = g.template at<Q, -1, -1>();
+    }
     if constexpr (G::use) {
       const Real y0 = p2 - m2, x0 = p1 - m1;
       const Real mix = hs[1] * (a[0] * ((pp - pm) - y0) + e[0] * (y0 - (mp - mm))) +
@@ -1186,24 +1211,30 @@ constexpr int local_of(int q) {
     if (kPopsB[i] == q) return i;
   return -1;
 }
+// The partial moments the groups exchange (indices of pair_moments): B needs
+// A's part of drho, j, Pi_xx and Pi_yy (A's populations have no Pi_xy), A needs
+// B's part of drho, jx and jy (B's have no jz, Pi_zz, Pi_xz, Pi_yz).
+constexpr int kToB = 6, kToA = 3;
+constexpr int kForB[kToB] = {0, 1, 2, 3, 4, 5};
+constexpr int kForA[kToA] = {0, 1, 2};
 // LDS per column after the plane buffers:
-//   RA [12]: A's partial moments (read by B after the first barrier of an
-//            iteration), then the z-face moments [8..12), formed by B (read
-//            by A after the third);
-//   RB [10]: B's partial moments, then the x-face moments [0..8) formed by A;
-//   SA [4]:  A's part of the sums of its last stored cell (read by B in the
-//            next iteration);
-//   RY [4]:  the moments of the y-face between the column and the next row,
-//            formed by B in the third phase and read after the third barrier
-//            by both threads of the column above (its lower y-face).
-// RA, RB and SA of a column are used only by the two threads of that
-// column, so every reuse is separated from the previous reads by a barrier
-// or by program order within one thread.  RY is read by another column,
-// at the end of an iteration, without a barrier before that column's next
-// partial moments are written: it has slots of its own, next written after
-// the second barrier of the next iteration.
-constexpr int kRA = kNPop + 2 * kNQ + 3 * kNZ, kRB = kRA + 12, kSA = kRB + 10, kRY = kSA + 4;
-constexpr int kSplitValues = kRY + 4;
+//   RA [6]:  A's partial moments (read by B after the first barrier of an
+//            iteration);
+//   RB [3]:  B's partial moments;
+//   RZ [4]:  the moments of the z-face below plane p, formed by B in the third
+//            phase, read by A after the third barrier;
+//   FX [4]:  those of the x-face between the column and the next one, formed by
+//            A, read by B of both columns;
+//   RY [4]:  those of the y-face between the column and the next row, formed
+//            by B, read by A of both columns and B of the upper one;
+//   SA [3]:  A's part of the momentum of its last stored cell (read by B in the
+//            next iteration).
+// RA, RB and SA are written in the first or last phase of an iteration and
+// read after the barrier that follows; RZ, FX and RY are written in the third
+// phase, and next written after the second barrier of the next iteration.
+constexpr int kRA = kNPop + 2 * kNQ + 3 * kNZ, kRB = kRA + kToB, kRZ = kRB + kToA, kFX = kRZ + 4, kRY = kFX + 4,
+              kSA = kRY + 4;
+constexpr int kSplitValues = kSA + 3;
 
 // Loads of the group's populations of the column's cell in plane `plane`.
 template <typename Real, int G, bool O32>
@@ -1279,7 +1310,8 @@ __device__ __forceinline__ void split_tile(const global_t<Real> *__restrict__ ft
   gy = gy < 0 ? gy + n : (gy >= n ? gy % n : gy);
   const int col = gy * n + gx;
   const bool inner = tx >= 1 && tx <= TX - 2 && ty >= 1 && ty <= TY - 2 && (x0 + tx - 1) < n && (y0 + ty - 1) < n;
-  const bool xface = tx <= TX - 2 && ty >= 1 && ty <= TY - 2;  // A: forms an x+ face
+  const bool rows = ty >= 1 && ty <= TY - 2;  // interior rows, halo columns too
+  const bool xface = tx <= TX - 2 && rows;                     // A: forms an x+ face
   const bool yface = tx >= 1 && tx <= TX - 2 && ty <= TY - 2;  // B: forms a y+ face
   const Real h = Real(p.h), dt = Real(p.dt);
   const Real dtal = dt * Real(p.alpha), dtbe = dt * Real(p.beta);
@@ -1289,8 +1321,10 @@ __device__ __forceinline__ void split_tile(const global_t<Real> *__restrict__ ft
   Real *const LZ = L + (kNPop + 2 * kNQ) * NT + c;
   Real *const RA = L + kRA * NT + c;
   Real *const RB = L + kRB * NT + c;
-  Real *const SA = L + kSA * NT + c;
+  Real *const RZ = L + kRZ * NT + c;
+  Real *const FX = L + kFX * NT + c;
   Real *const RY = L + kRY * NT + c;
+  Real *const SA = L + kSA * NT + c;
   MeshMarch<Real, W> mc{};
   const constant_t<double> *wz = nullptr;
   double wxy = 1.0;
@@ -1301,14 +1335,14 @@ __device__ __forceinline__ void split_tile(const global_t<Real> *__restrict__ ft
     wz = (const constant_t<double> *)(width + 2 * n);
     wxy = to_global(width)[gx] * to_global(width)[n + gy];
   }
-  // adds B's own sums (r, x, y, z) of a stored cell, or A's part with the
-  // cell's kinetic energy, weighted by the cell volume on the mesh
-  auto add_sums = [&](int plane, double r, double x, double y, double z, double ke) {
+  // adds the group's part of a stored cell's sums, weighted by the cell volume
+  // on the mesh
+  auto add_sums = [&](int plane, double r, double x, double y, double z) {
     if constexpr (Mesh) {
       const double vol = wxy * wz[plane];
-      v[0] += vol * r; v[1] += vol * x; v[2] += vol * y; v[3] += vol * z; v[4] += vol * ke;
+      v[0] += vol * r; v[1] += vol * x; v[2] += vol * y; v[3] += vol * z;
     } else {
-      v[0] += r; v[1] += x; v[2] += y; v[3] += z; v[4] += ke;
+      v[0] += r; v[1] += x; v[2] += y; v[3] += z;
     }
   };
 
@@ -1319,6 +1353,15 @@ __device__ __forceinline__ void split_tile(const global_t<Real> *__restrict__ ft
   Real zl[4];             // B: lower half of the z-face above the previous plane (mesh: its w, and nf in zn)
   Real zn[4];
   double jb[3] = {0, 0, 0};  // B: its part of the momentum of the last stored cell
+  // B: the kinetic energy of the last stored cell, in plane `plane`
+  auto add_energy = [&](int plane) {
+    const double x = jb[0] + (double)SA[0], y = jb[1] + (double)SA[NT], z = jb[2] + (double)SA[2 * NT];
+    const double ke = 0.5 * (x * x + y * y + z * z) * ir * ir;
+    if constexpr (Mesh)
+      v[4] += wxy * wz[plane] * ke;
+    else
+      v[4] += ke;
+  };
   static_for<NG>([&](auto i) { acc_p[i] = Real(0); });
   static_for<10>([&](auto i) { nxt[i] = Real(0); });
   static_for<4>([&](auto i) { zl[i] = Real(0); zn[i] = Real(0); });
@@ -1338,14 +1381,18 @@ __device__ __forceinline__ void split_tile(const global_t<Real> *__restrict__ ft
     // partial moments of this group's populations, exchanged with the other group
     Real m[10];
     partial_moments<Real, G>(pf, m);
-    static_for<10>([&](auto k) { (G == 0 ? RA : RB)[k * NT] = m[k]; });
+    if constexpr (G == 0)
+      static_for<kToB>([&](auto k) { RA[k * NT] = m[kForB[k]]; });
+    else
+      static_for<kToA>([&](auto k) { RB[k * NT] = m[kForA[k]]; });
     __syncthreads();
-    static_for<10>([&](auto k) { m[k] = G == 0 ? m[k] + RB[k * NT] : RA[k * NT] + m[k]; });
+    if constexpr (G == 0)
+      static_for<kToA>([&](auto k) { m[kForA[k]] = m[kForA[k]] + RB[k * NT]; });
+    else
+      static_for<kToB>([&](auto k) { m[kForB[k]] = RA[k * NT] + m[kForB[k]]; });
     if constexpr (G == 1) {
       if (inner && stored_last) {
-        const double ra = (double)SA[0], xa = (double)SA[NT], ya = (double)SA[2 * NT], za = (double)SA[3 * NT];
-        const double x = jb[0] + xa, y = jb[1] + ya, z = jb[2] + za;
-        add_sums(p_ - 2, ra, xa, ya, za, 0.5 * (x * x + y * y + z * z) * ir * ir);
+        add_energy(p_ - 2);
       }
     }
     // own-column pieces of plane p (see fused_tile)
@@ -1407,58 +1454,61 @@ __device__ __forceinline__ void split_tile(const global_t<Real> *__restrict__ ft
             zface_half<1>(g, h, lo);
           }
           if constexpr (std::decay_t<decltype(g)>::use) {
-            static_for<4>([&](auto i) { RA[(8 + i) * NT] = Mesh ? mm[i] : mm[i] + zl[i]; });
+            static_for<4>([&](auto i) { RZ[i * NT] = Mesh ? mm[i] : mm[i] + zl[i]; });
             if constexpr (!Mesh) static_for<4>([&](auto i) { zl[i] = lo[i]; });
           }
         });
-        if (has_cur) {
-          const InPlaneCoef<Real, W, Mesh> xy(mc);
-          gathered<Real, W>(pc, pc, [&](const auto &g, const auto &) {
-            static_for<5>([&](auto q) {
-              if constexpr (q >= 1 && Mesh) {
-                xy.template axis<q>(g, acc_p[local_of(q)]);
-              } else if constexpr (q >= 1) {
-                constexpr int d = kCx[q] != 0 ? 0 : 1, s = kCx[q] + kCy[q];
-                const Real bp_ = g.template at<q, Unit<d>::x, Unit<d>::y>();
-                const Real bm_ = g.template at<q, -Unit<d>::x, -Unit<d>::y>();
-                if constexpr (std::decay_t<decltype(g)>::use)
-                  acc_p[local_of(q)] -= dtal * (Real(0.5 * s) * (bp_ - bm_) - h * (bp_ + bm_));
-              }
-            });
-          });
-          auto diag_xy = [&](auto q, const auto &g) {
-            if constexpr (Mesh) {
-              xy.template diag<q>(g, acc_p[local_of(q)]);
-              return;
+      }
+    }
+    if constexpr (G == 1) {
+      // (every lane of an interior row: the corners come from the lanes beside)
+      if (rows && has_cur) {
+        const InPlaneCoef<Real, W, Mesh> xy(mc);
+        gathered<Real, W>(pc, pc, [&](const auto &g, const auto &) {
+          static_for<5>([&](auto q) {
+            if constexpr (q >= 1 && Mesh) {
+              xy.template axis<q>(g, acc_p[local_of(q)]);
+            } else if constexpr (q >= 1) {
+              constexpr int d = kCx[q] != 0 ? 0 : 1, s = kCx[q] + kCy[q];
+              const Real bp_ = g.template at<q, Unit<d>::x, Unit<d>::y>();
+              const Real bm_ = g.template at<q, -Unit<d>::x, -Unit<d>::y>();
+              if constexpr (std::decay_t<decltype(g)>::use)
+                acc_p[local_of(q)] -= dtal * (Real(0.5 * s) * (bp_ - bm_) - h * (bp_ + bm_));
             }
-            constexpr int sx = kCx[q], sy = kCy[q];
-            const Real p1 = g.template at<q, 1, 0>(), m1 = g.template at<q, -1, 0>();
-            const Real p2 = g.template at<q, 0, 1>(), m2 = g.template at<q, 0, -1>();
-            const Real pp = g.template at<q, sx, sy>(), pm = g.template at<q, sx, -sy>();
-            const Real mp = g.template at<q, -sx, sy>(), mm = g.template at<q, -sx, -sy>();
-            if constexpr (std::decay_t<decltype(g)>::use) {
-              const Real a1 = sx > 0 ? (p1 - m1) : (m1 - p1);
-              const Real a2 = sy > 0 ? (p2 - m2) : (m2 - p2);
-              acc_p[local_of(q)] -= dtal * ((Real(0.5) * a1 + Real(0.5) * a2) - h * ((p1 + m1) + (p2 + m2)) -
-                                            Real(0.5) * h * (((pp - pm) - mp) + mm));
-            }
-          };
-          gathered<Real, W>(pc, pc, [&](const auto &g, const auto &) {
-            diag_xy(std::integral_constant<int, 7>{}, g);
-            diag_xy(std::integral_constant<int, 8>{}, g);
           });
-          gathered<Real, W>(pc, pc, [&](const auto &g, const auto &) {
-            diag_xy(std::integral_constant<int, 9>{}, g);
-            diag_xy(std::integral_constant<int, 10>{}, g);
-          });
-        }
+        });
+        auto diag_xy = [&](auto q, const auto &g) {
+          if constexpr (Mesh) {
+            xy.template diag<q>(g, acc_p[local_of(q)]);
+            return;
+          }
+          constexpr int sx = kCx[q], sy = kCy[q];
+          const Real p1 = g.template at<q, 1, 0>(), m1 = g.template at<q, -1, 0>();
+          const Real p2 = g.template at<q, 0, 1>(), m2 = g.template at<q, 0, -1>();
+          if constexpr (std::decay_t<decltype(g)>::use) {
+            // the corners' mixed difference: the y-differences of the next and
+            // the previous column, which are the lanes beside this one
+            const Real gx = p1 - m1, gy = p2 - m2;
+            const Real mix = from_next_lane(gy) - from_previous_lane(gy);
+            constexpr Real hx = Real(0.5 * sx), hy = Real(0.5 * sy), hm = Real(0.5 * sx * sy);
+            acc_p[local_of(q)] -= dtal * ((hx * gx + hy * gy) - h * ((p1 + m1) + (p2 + m2)) - hm * (h * mix));
+          }
+        };
+        gathered<Real, W>(pc, pc, [&](const auto &g, const auto &) {
+          diag_xy(std::integral_constant<int, 7>{}, g);
+          diag_xy(std::integral_constant<int, 8>{}, g);
+        });
+        gathered<Real, W>(pc, pc, [&](const auto &g, const auto &) {
+          diag_xy(std::integral_constant<int, 9>{}, g);
+          diag_xy(std::integral_constant<int, 10>{}, g);
+        });
       }
     }
     if (has_prev) {
       {
         // the group's two faces of centre p-1: in-plane part from plane
         // p-1, z-tangential gradients -h/4 [(M_L + M_R)(p) - (M_L + M_R)(p-2)];
-        // written for the other group (A's into RB, B's into RA)
+        // written for the other group (A's into FX, B's into RY)
         constexpr int D = G == 0 ? 0 : 1;
         const Real hq = Real(0.25) * h;
         auto face = [&](auto LX, auto LY, Real (&fm)[4]) {
@@ -1488,6 +1538,7 @@ __device__ __forceinline__ void split_tile(const global_t<Real> *__restrict__ ft
           static_for<4>([&](auto i) {
             fx[0][i] = xp[i];
             fx[1][i] = from_previous_lane(xp[i]);
+            FX[i * NT] = xp[i];
           });
         } else {
           // y+ faces only, by every interior column of every row but the
@@ -1496,9 +1547,6 @@ __device__ __forceinline__ void split_tile(const global_t<Real> *__restrict__ ft
             face(I0{}, I0{}, fx[0]);
             static_for<4>([&](auto i) { RY[i * NT] = fx[0][i]; });
           }
-        }
-        if constexpr (G == 0) {
-          if (inner) static_for<2>([&](auto f) { static_for<4>([&](auto i) { RB[(f * 4 + i) * NT] = fx[f][i]; }); });
         }
       }
     }
@@ -1526,7 +1574,7 @@ __device__ __forceinline__ void split_tile(const global_t<Real> *__restrict__ ft
         if constexpr (G == 0) {
           // the z-face between p-1 and p: upper face of centre p-1, lower of centre p
           Real zf[4];
-          static_for<4>([&](auto i) { zf[i] = RA[(8 + i) * NT]; });
+          static_for<4>([&](auto i) { zf[i] = RZ[i * NT]; });
           Real iwc = Real(1), iwp = Real(1);
           if constexpr (Mesh) {
             iwc = mc.z(kMarchIw, p_ - 1);
@@ -1549,7 +1597,7 @@ __device__ __forceinline__ void split_tile(const global_t<Real> *__restrict__ ft
           if constexpr (G == 0) {
             static_for<4>([&](auto i) { fo[0][i] = RY[i * NT]; fo[1][i] = RY[i * NT - W]; });
           } else {
-            static_for<2>([&](auto f) { static_for<4>([&](auto i) { fo[f][i] = RB[(f * 4 + i) * NT]; }); });
+            static_for<4>([&](auto i) { fo[0][i] = FX[i * NT]; fo[1][i] = FX[i * NT - 1]; });
             static_for<4>([&](auto i) { fx[1][i] = RY[i * NT - W]; });
           }
           using Ip = std::integral_constant<int, 1>;
@@ -1572,10 +1620,10 @@ __device__ __forceinline__ void split_tile(const global_t<Real> *__restrict__ ft
             if constexpr (kCy[q] != 0) ay += kCy[q] * x;
             if constexpr (kCz[q] != 0) az += kCz[q] * x;
           });
+          add_sums(p_ - 1, r, ax, ay, az);
           if constexpr (G == 0) {
-            SA[0] = Real(r); SA[NT] = Real(ax); SA[2 * NT] = Real(ay); SA[3 * NT] = Real(az);
+            SA[0] = Real(ax); SA[NT] = Real(ay); SA[2 * NT] = Real(az);
           } else {
-            add_sums(p_ - 1, r, ax, ay, az, 0.0);
             jb[0] = ax; jb[1] = ay; jb[2] = az;
           }
         }
@@ -1588,9 +1636,7 @@ __device__ __forceinline__ void split_tile(const global_t<Real> *__restrict__ ft
   __syncthreads();
   if constexpr (G == 1) {
     if (inner) {
-      const double ra = (double)SA[0], xa = (double)SA[NT], ya = (double)SA[2 * NT], za = (double)SA[3 * NT];
-      const double x = jb[0] + xa, y = jb[1] + ya, z = jb[2] + za;
-      add_sums(z1 - 1, ra, xa, ya, za, 0.5 * (x * x + y * y + z * z) * ir * ir);
+      add_energy(z1 - 1);
     }
   }
   __syncthreads();
