@@ -777,6 +777,62 @@ struct InPlaneCoef<Real, W, true> {
   }
 };
 
+// A cell's halves of the moments of its two D-faces (D = 0 or 1) at centre
+// plane p-1 (planes p, p-1, p-2): with w the value less the tangential
+// gradients and n the normal-flux field, the face between L and R has
+//   unit cells: (w_L/2 + h n_L) + (w_R/2 - h n_R),
+//   mesh:       ((1 - lam_L) w_L + hg_L n_L) + (lam_L w_R - hg_L n_R),
+// so a cell forms up (as L of its upper face) and dn (as R of its lower one)
+// from its own column's fields and their differences across D, and a face
+// takes one half from each side: 23 field values instead of the 46 of the two
+// cells' reads, and each gradient is formed once.
+template <int D, bool Mesh, typename Real, int W>
+__device__ __forceinline__ void face_halves(const MeshMarch<Real, W> &mc, int p, Real h, const Plane<Real, W> &c,
+                                            const Plane<Real, W> &c1, const Plane<Real, W> &c2, Real (&up)[4],
+                                            Real (&dn)[4]) {
+  constexpr int t = 1 - D;
+  using std::integral_constant;
+  Real lam = Real(0), hg = Real(0), lam_m = Real(0), hg_m = Real(0), hst = Real(0.25) * h, hsz = hst;
+  if constexpr (Mesh) {
+    lam = mc.template col<D>(kMarchLam), hg = mc.template col<D>(kMarchHg);
+    // of the lower face: the cell below's (column 0 of the tile, whose lower
+    // half nobody reads, gets another entry of the table)
+    lam_m = D == 0 ? mc.X[kMarchLam * W - 1] : mc.Y[kMarchLam * 8 - 1];
+    hg_m = D == 0 ? mc.X[kMarchHg * W - 1] : mc.Y[kMarchHg * 8 - 1];
+    hst = mc.template col<t>(kMarchHs), hsz = mc.z(kMarchHs, p - 1);
+  }
+  Real zd[4];
+  gathered<Real, W>(c, c2, [&](const auto &g, const auto &g2) {
+    constexpr int ids[4] = {kJz, kPxz, kPyz, kPzz};
+    static_for<4>([&](auto i) {
+      const Real a = g.template at<ids[i], 0, 0>(), b = g2.template at<ids[i], 0, 0>();
+      if constexpr (std::decay_t<decltype(g)>::use) zd[i] = a - b;
+    });
+  });
+  gathered<Real, W>(c1, c1, [&](const auto &g, const auto &) {
+    auto half = [&](auto i, auto V, auto N, auto T) {
+      const Real v = g.template at<V, 0, 0>(), nf = g.template at<N, 0, 0>(), d = dif<T, t, 0, 0>(g);
+      if constexpr (std::decay_t<decltype(g)>::use) {
+        if constexpr (Mesh) {
+          const Real w = v - (hst * d + hsz * zd[i]);
+          up[i] = (w - lam * w) + hg * nf;
+          dn[i] = lam_m * w - hg_m * nf;
+        } else {
+          const Real w = Real(0.5) * v - hst * (d + zd[i]);
+          up[i] = w + h * nf;
+          dn[i] = w - h * nf;
+        }
+      }
+    };
+    half(integral_constant<int, 0>{}, integral_constant<int, kR0>{}, integral_constant<int, jid(D)>{},
+         integral_constant<int, jid(t)>{});
+    static_for<3>([&](auto a) {
+      half(integral_constant<int, 1 + a>{}, integral_constant<int, jid(a)>{}, integral_constant<int, pid(a, D)>{},
+           integral_constant<int, pid(a, t)>{});
+    });
+  });
+}
+
 // Moments of the D-face (D = 0 or 1) between the column and its upper
 // neighbour at centre plane p-1, on the mesh (planes p, p-1, p-2).
 template <int D, typename Real, int W>
@@ -820,7 +876,7 @@ __device__ __forceinline__ void fused_tile(const global_t<Real> *__restrict__ ft
   gy = gy < 0 ? gy + n : (gy >= n ? gy % n : gy);
   const int col = gy * n + gx;
   const bool inner = tx >= 1 && tx <= TX - 2 && ty >= 1 && ty <= TY - 2 && (x0 + tx - 1) < n && (y0 + ty - 1) < n;
-  const bool xface = tx <= TX - 2 && ty >= 1 && ty <= TY - 2;  // forms the x+ face (see below)
+  const bool rows = ty >= 1 && ty <= TY - 2;                   // interior rows, halo columns too
   const bool yface = tx >= 1 && tx <= TX - 2 && ty <= TY - 2;  // forms the y+ face
   const Real h = Real(p.h), dt = Real(p.dt);
   const Real dtal = dt * Real(p.alpha), dtbe = dt * Real(p.beta);
@@ -1005,7 +1061,11 @@ __device__ __forceinline__ void fused_tile(const global_t<Real> *__restrict__ ft
       // column before it, the previous lane (a tile row is 32 consecutive
       // lanes of one wavefront).  The lane shift runs with every lane active.
       Real mxp[4] = {Real(0), Real(0), Real(0), Real(0)};
-      if (xface) face_moments(I0{}, I0{}, I0{}, mxp);
+      if (rows) {
+        Real up[4], dn[4];
+        face_halves<0, Mesh>(mc, p_, h, c, c1, c2, up, dn);
+        static_for<4>([&](auto i) { mxp[i] = up[i] + from_next_lane(dn[i]); });
+      }
       Real fxp[10], fxm[10];
       face_terms<0>(mxp, p, dtbe, fxp);
       static_for<10>([&](auto k) { fxm[k] = from_previous_lane(fxp[k]); });
@@ -1225,15 +1285,16 @@ constexpr int kForA[kToA] = {0, 1, 2};
 //            phase, read by A after the third barrier;
 //   FX [4]:  those of the x-face between the column and the next one, formed by
 //            A, read by B of both columns;
-//   RY [4]:  those of the y-face between the column and the next row, formed
-//            by B, read by A of both columns and B of the upper one;
+//   RU, RD [4]: the column's halves of the moments of its upper and lower
+//            y-faces (face_halves), formed by B, read by A of the column and by
+//            both threads of the columns above and below;
 //   SA [3]:  A's part of the momentum of its last stored cell (read by B in the
 //            next iteration).
 // RA, RB and SA are written in the first or last phase of an iteration and
-// read after the barrier that follows; RZ, FX and RY are written in the third
+// read after the barrier that follows; RZ, FX, RU, RD are written in the third
 // phase, and next written after the second barrier of the next iteration.
-constexpr int kRA = kNPop + 2 * kNQ + 3 * kNZ, kRB = kRA + kToB, kRZ = kRB + kToA, kFX = kRZ + 4, kRY = kFX + 4,
-              kSA = kRY + 4;
+constexpr int kRA = kNPop + 2 * kNQ + 3 * kNZ, kRB = kRA + kToB, kRZ = kRB + kToA, kFX = kRZ + 4, kRU = kFX + 4,
+              kRD = kRU + 4, kSA = kRD + 4;
 constexpr int kSplitValues = kSA + 3;
 
 // Loads of the group's populations of the column's cell in plane `plane`.
@@ -1311,8 +1372,6 @@ __device__ __forceinline__ void split_tile(const global_t<Real> *__restrict__ ft
   const int col = gy * n + gx;
   const bool inner = tx >= 1 && tx <= TX - 2 && ty >= 1 && ty <= TY - 2 && (x0 + tx - 1) < n && (y0 + ty - 1) < n;
   const bool rows = ty >= 1 && ty <= TY - 2;  // interior rows, halo columns too
-  const bool xface = tx <= TX - 2 && rows;                     // A: forms an x+ face
-  const bool yface = tx >= 1 && tx <= TX - 2 && ty <= TY - 2;  // B: forms a y+ face
   const Real h = Real(p.h), dt = Real(p.dt);
   const Real dtal = dt * Real(p.alpha), dtbe = dt * Real(p.beta);
   const double ir = p.inv_rho0;
@@ -1323,7 +1382,8 @@ __device__ __forceinline__ void split_tile(const global_t<Real> *__restrict__ ft
   Real *const RB = L + kRB * NT + c;
   Real *const RZ = L + kRZ * NT + c;
   Real *const FX = L + kFX * NT + c;
-  Real *const RY = L + kRY * NT + c;
+  Real *const RU = L + kRU * NT + c;
+  Real *const RD = L + kRD * NT + c;
   Real *const SA = L + kSA * NT + c;
   MeshMarch<Real, W> mc{};
   const constant_t<double> *wz = nullptr;
@@ -1414,7 +1474,7 @@ __device__ __forceinline__ void split_tile(const global_t<Real> *__restrict__ ft
     });
     __syncthreads();
 
-    Real fx[2][4];  // the faces this group forms: A x+ and x-, B y+ and y-
+    Real fx[2][4];  // A: the x+ and x- faces; B: its halves of the y+ and y- faces, then the faces
     if (inner) {
       if constexpr (G == 0) {
         // diagonal z-moving populations: in-plane differences D = B(+d1) -
@@ -1505,49 +1565,22 @@ __device__ __forceinline__ void split_tile(const global_t<Real> *__restrict__ ft
       }
     }
     if (has_prev) {
-      {
-        // the group's two faces of centre p-1: in-plane part from plane
-        // p-1, z-tangential gradients -h/4 [(M_L + M_R)(p) - (M_L + M_R)(p-2)];
-        // written for the other group (A's into FX, B's into RY)
-        constexpr int D = G == 0 ? 0 : 1;
-        const Real hq = Real(0.25) * h;
-        auto face = [&](auto LX, auto LY, Real (&fm)[4]) {
-          if constexpr (Mesh) {
-            face_moments_mesh<D>(mc, p_, pc, pc1, pc2, fm);
-            return;
-          }
-          gathered<Real, W>(pc1, pc1, [&](const auto &g, const auto &) {
-            Real t[4];
-            face_inplane<D, LX, LY>(g, h, t);
-            if constexpr (std::decay_t<decltype(g)>::use) static_for<4>([&](auto i) { fm[i] = t[i]; });
-          });
-          gathered<Real, W>(pc, pc2, [&](const auto &g, const auto &g2) {
-            Real s1[4], s0[4];
-            face_zsum<D, LX, LY>(g, s1);
-            face_zsum<D, LX, LY>(g2, s0);
-            if constexpr (std::decay_t<decltype(g)>::use) static_for<4>([&](auto i) { fm[i] -= hq * (s1[i] - s0[i]); });
-          });
-        };
-        using I0 = std::integral_constant<int, 0>;
-        using Im1 = std::integral_constant<int, -1>;
-        if constexpr (G == 0) {
-          // each x-face formed once, as in fused_tile: x+ by every column of
-          // an interior row but the last, x- from the previous lane
-          Real xp[4] = {Real(0), Real(0), Real(0), Real(0)};
-          if (xface) face(I0{}, I0{}, xp);
+      // the group's faces of centre p-1
+      if constexpr (G == 0) {
+        // x-faces: the neighbours' halves come from the lanes beside
+        if (rows) {
+          Real up[4], dn[4];
+          face_halves<0, Mesh>(mc, p_, h, pc, pc1, pc2, up, dn);
           static_for<4>([&](auto i) {
-            fx[0][i] = xp[i];
-            fx[1][i] = from_previous_lane(xp[i]);
-            FX[i * NT] = xp[i];
+            fx[0][i] = up[i] + from_next_lane(dn[i]);
+            fx[1][i] = from_previous_lane(up[i]) + dn[i];
+            FX[i * NT] = fx[0][i];
           });
-        } else {
-          // y+ faces only, by every interior column of every row but the
-          // last (halo row 0 too); the y- face is read back from the row below
-          if (yface) {
-            face(I0{}, I0{}, fx[0]);
-            static_for<4>([&](auto i) { RY[i * NT] = fx[0][i]; });
-          }
         }
+      } else {
+        // y-faces: halves of every row (halo rows too), joined after the barrier
+        face_halves<1, Mesh>(mc, p_, h, pc, pc1, pc2, fx[0], fx[1]);
+        static_for<4>([&](auto i) { RU[i * NT] = fx[0][i]; RD[i * NT] = fx[1][i]; });
       }
     }
     phase();
@@ -1595,10 +1628,16 @@ __device__ __forceinline__ void split_tile(const global_t<Real> *__restrict__ ft
           // group's populations: its own two faces and the other group's
           Real fo[2][4];
           if constexpr (G == 0) {
-            static_for<4>([&](auto i) { fo[0][i] = RY[i * NT]; fo[1][i] = RY[i * NT - W]; });
+            static_for<4>([&](auto i) {
+              fo[0][i] = RU[i * NT] + RD[i * NT + W];
+              fo[1][i] = RU[i * NT - W] + RD[i * NT];
+            });
           } else {
             static_for<4>([&](auto i) { fo[0][i] = FX[i * NT]; fo[1][i] = FX[i * NT - 1]; });
-            static_for<4>([&](auto i) { fx[1][i] = RY[i * NT - W]; });
+            static_for<4>([&](auto i) {
+              fx[0][i] += RD[i * NT + W];
+              fx[1][i] = RU[i * NT - W] + fx[1][i];
+            });
           }
           using Ip = std::integral_constant<int, 1>;
           using Im = std::integral_constant<int, -1>;
