@@ -902,21 +902,19 @@ __device__ __forceinline__ void fused_tile(const global_t<Real> *__restrict__ ft
   // when the centre is stored, so that the result is rounded at the scale of
   // f~ once instead of at every term (in FP32 this more than halves the
   // rounding noise the march adds per step).
-  Real acc_c[kQ];     // terms of centre p-1, completed in this iteration
-  Real acc_p[kQ];     // terms of centre p
-  Real fp_c[kQ];      // f~+ of centre p-1
-  Real fp_p[kQ];      // f~+ of centre p
+  // Two centres at a time: p-1, completed in plane p's iteration, and p.
+  Real acc_0[kQ], fp_0[kQ], acc_1[kQ], fp_1[kQ];
   Real nxt[10];       // z-1 terms of the z-moving populations of centre p+1
   Real zl[4];         // lower half of the z-face above the previous plane (mesh: its w, and nf in zn)
   Real zn[4];
-  static_for<kQ>([&](auto q) { acc_p[q] = Real(0); fp_p[q] = Real(0); });
+  static_for<kQ>([&](auto q) { acc_0[q] = acc_1[q] = fp_0[q] = fp_1[q] = Real(0); });
   static_for<10>([&](auto i) { nxt[i] = Real(0); });
   static_for<4>([&](auto i) { zl[i] = Real(0); zn[i] = Real(0); });
 
-  // Completes centre `plane` (acc_c): its lower y-face, read from the slot
+  // Completes centre `plane` (acc_c, fp_c): its lower y-face, read from the slot
   // of the column W before, the store and the sums.  Runs after the barrier
   // that ends the iteration which formed the faces.
-  auto finish = [&](int plane) {
+  auto finish = [&](int plane, Real (&acc_c)[kQ], const Real (&fp_c)[kQ]) {
     Real fym[10];
     static_for<10>([&](auto k) { fym[k] = LY[k * NT - W]; });
     if constexpr (Mesh)
@@ -944,12 +942,14 @@ __device__ __forceinline__ void fused_tile(const global_t<Real> *__restrict__ ft
 
   load_raw<Real, O32>(ft, stride, n, col, z0 - 1, pf);
   int q2 = 0, q3 = 0;  // Q slot and Z slot of plane p
-  // One iteration past the chunk's end only finishes its last centre, so
-  // that every centre is completed by the same code (and rounds the same
-  // whatever the chunk length).
-  for (int p_ = z0 - 1; p_ <= z1 + 1; ++p_) {
-    if (p_ - 1 > z0 && inner) finish(p_ - 2);  // the centre the last iteration formed
-    if (p_ > z1) break;
+  // Plane p_ of the march: acc_c, fp_c hold centre p-1; acc_p, fp_p hold the
+  // centre the last iteration formed (p-2, finished here) and then centre p.
+  // One iteration past the chunk's end only finishes its last centre (and
+  // returns false), so that every centre is completed by the same code (and
+  // rounds the same whatever the chunk length).
+  auto iteration = [&](int p_, Real (&acc_c)[kQ], const Real (&fp_c)[kQ], Real (&acc_p)[kQ], Real (&fp_p)[kQ]) {
+    if (p_ - 1 > z0 && inner) finish(p_ - 2, acc_p, fp_p);
+    if (p_ > z1) return false;
     const bool has_prev = p_ > z0;          // centre p-1 is in the chunk
     const bool has_cur = p_ >= z0 && p_ < z1;
     const int q2m = q2 ^ 1, q3m = q3 == 0 ? 2 : q3 - 1, q3mm = q3 == 2 ? 0 : q3 + 1;
@@ -957,8 +957,6 @@ __device__ __forceinline__ void fused_tile(const global_t<Real> *__restrict__ ft
     const Plane<Real, W> c1{nullptr, LQ + q2m * (kNQ * NT), LZ + q3m * (kNZ * NT)};  // plane p-1
     const Plane<Real, W> c2{nullptr, nullptr, LZ + q3mm * (kNZ * NT)};              // plane p-2
 
-    // centre p-1 becomes the completed centre
-    static_for<kQ>([&](auto q) { acc_c[q] = acc_p[q]; fp_c[q] = fp_p[q]; });
     // own-column pieces of plane p: z+1 terms of centre p-1, the centre
     // terms and initial value of centre p, z-1 terms of centre p+1 (formed
     // by halo columns too, which never store them)
@@ -1152,6 +1150,14 @@ __device__ __forceinline__ void fused_tile(const global_t<Real> *__restrict__ ft
     q2 ^= 1;
     q3 = q3 == 2 ? 0 : q3 + 1;
     __syncthreads();
+    return true;
+  };
+  // two planes per turn, the two centres' arrays changing places: as one
+  // iteration with a copy from one to the other, 38 of its ~1200 vector
+  // instructions were that copy
+  for (int p_ = z0 - 1;; p_ += 2) {
+    if (!iteration(p_, acc_0, fp_0, acc_1, fp_1)) break;
+    if (!iteration(p_ + 1, acc_1, fp_1, acc_0, fp_0)) break;
   }
 }
 
