@@ -1361,7 +1361,17 @@ __device__ __forceinline__ void publish_group(const Real (&f)[Group<G>::N], cons
 // The z-march of group G of a tile over the planes [z0, z1) (see above).
 // L: the block's LDS, kSplitValues values per column.
 // Mesh: as in fused_tile.
-template <typename Real, int W, int G, bool O32, bool Mesh>
+// Halo: the code of the wavefront of a group that holds the two halo rows of a
+// 32-wide tile.  It has no centres of its own; A's forms the x-faces of the
+// group's three interior wavefronts (lane l takes the columns of lane l of
+// each in turn).  A's is its group's last wavefront and B's its first: the
+// wavefronts of a block go to the compute unit's four SIMDs in turn, so the
+// halo wavefronts are on different SIMDs, each beside an interior one, where
+// together on one they left it idle while the others worked.  256^3 1.665 ms
+// with both last, 1.610 ms apart, 1.535 ms with the x-faces handed over
+// (128^3 217, 216, 214 us; 64^3 40.9, 39.3, 39.8 us); the z-faces handed to B's
+// halo wavefront 1.55 ms at 256^3 but 220 us at 128^3.
+template <typename Real, int W, int G, bool O32, bool Mesh, bool Halo>
 __device__ __forceinline__ void split_tile(const global_t<Real> *__restrict__ ft, global_t<Real> *__restrict__ out, const StepParams &p,
                                            int bx, int by, int z0, int z1, Real *L, double (&v)[kNumSums],
                                            const Real *coef, const double *width) {
@@ -1369,15 +1379,20 @@ __device__ __forceinline__ void split_tile(const global_t<Real> *__restrict__ ft
   constexpr int NG = Group<G>::N;
   const int n = p.n;
   const int64_t stride = p.stride;
-  const int c = tile_column<W>(threadIdx.x - G * NT);  // column of the tile
+  // column of the tile; B's wavefronts of a 32-wide tile are rotated by one, its
+  // halo wavefront first
+  const int c = tile_column<W>(G == 0 ? threadIdx.x : (threadIdx.x - (W == 32 ? 64 : 0)) % NT);
   const int tx = c % TX, ty = c / TX;
   const int x0 = bx * IX, y0 = by * IY;
   int gx = x0 - 1 + tx, gy = y0 - 1 + ty;
   gx = gx < 0 ? gx + n : (gx >= n ? gx % n : gx);
   gy = gy < 0 ? gy + n : (gy >= n ? gy % n : gy);
   const int col = gy * n + gx;
-  const bool inner = tx >= 1 && tx <= TX - 2 && ty >= 1 && ty <= TY - 2 && (x0 + tx - 1) < n && (y0 + ty - 1) < n;
-  const bool rows = ty >= 1 && ty <= TY - 2;  // interior rows, halo columns too
+  constexpr bool kHelp = W == 32;  // the halo rows have a wavefront of their own
+  const bool rows = kHelp ? !Halo : ty >= 1 && ty <= TY - 2;  // interior rows, halo columns too
+  const bool inner = rows && tx >= 1 && tx <= TX - 2 && (x0 + tx - 1) < n && (y0 + ty - 1) < n;
+  // Halo: distance (columns, rows) to the columns of interior wavefront j
+  auto helped = [&](int j) { return tile_column<W>(j * 64 + (threadIdx.x & 63)) - c; };
   const Real h = Real(p.h), dt = Real(p.dt);
   const Real dtal = dt * Real(p.alpha), dtbe = dt * Real(p.beta);
   const double ir = p.inv_rho0;
@@ -1416,8 +1431,8 @@ __device__ __forceinline__ void split_tile(const global_t<Real> *__restrict__ ft
   Real acc_c[NG];         // centre p-1
   Real acc_p[NG];         // centre p
   Real nxt[10];           // A: z-1 terms of centre p+1 (all of A's populations move in z)
-  Real zl[4];             // B: lower half of the z-face above the previous plane (mesh: its w, and nf in zn)
-  Real zn[4];
+  // B: lower half of the z-face above the previous plane (mesh: its w, and nf in zn)
+  Real zl[4], zn[4];
   double jb[3] = {0, 0, 0};  // B: its part of the momentum of the last stored cell
   // B: the kinetic energy of the last stored cell, in plane `plane`
   auto add_energy = [&](int plane) {
@@ -1481,6 +1496,28 @@ __device__ __forceinline__ void split_tile(const global_t<Real> *__restrict__ ft
     __syncthreads();
 
     Real fx[2][4];  // A: the x+ and x- faces; B: its halves of the y+ and y- faces, then the faces
+    // A: x-faces of a column: its halves and those of the lanes beside
+    auto x_faces = [&](const Plane<Real, W> &a, const Plane<Real, W> &b, const Plane<Real, W> &e,
+                       const MeshMarch<Real, W> &m, Real *f, Real (&xp)[4], Real (&xm)[4]) {
+      Real up[4], dn[4];
+      face_halves<0, Mesh>(m, p_, h, a, b, e, up, dn);
+      static_for<4>([&](auto i) {
+        xp[i] = up[i] + from_next_lane(dn[i]);
+        xm[i] = from_previous_lane(up[i]) + dn[i];
+        f[i * NT] = xp[i];
+      });
+    };
+    if constexpr (Halo && G == 0) {
+      if (has_prev)
+        static_for<3>([&](auto j) {
+          const int d = helped(j);
+          MeshMarch<Real, W> m = mc;
+          if constexpr (Mesh) m.Y += d / W;  // the same x, d / W rows further
+          const Plane<Real, W> a{nullptr, nullptr, pc.Z + d}, b{nullptr, pc1.Q + d, pc1.Z + d}, e{nullptr, nullptr, pc2.Z + d};
+          Real xp[4], xm[4];
+          x_faces(a, b, e, m, FX + d, xp, xm);
+        });
+    }
     if (inner) {
       if constexpr (G == 0) {
         // diagonal z-moving populations: in-plane differences D = B(+d1) -
@@ -1573,15 +1610,8 @@ __device__ __forceinline__ void split_tile(const global_t<Real> *__restrict__ ft
     if (has_prev) {
       // the group's faces of centre p-1
       if constexpr (G == 0) {
-        // x-faces: the neighbours' halves come from the lanes beside
-        if (rows) {
-          Real up[4], dn[4];
-          face_halves<0, Mesh>(mc, p_, h, pc, pc1, pc2, up, dn);
-          static_for<4>([&](auto i) {
-            fx[0][i] = up[i] + from_next_lane(dn[i]);
-            fx[1][i] = from_previous_lane(up[i]) + dn[i];
-            FX[i * NT] = fx[0][i];
-          });
+        if constexpr (!kHelp) {
+          if (rows) x_faces(pc, pc1, pc2, mc, FX, fx[0], fx[1]);
         }
       } else {
         // y-faces: halves of every row (halo rows too), joined after the barrier
@@ -1638,6 +1668,7 @@ __device__ __forceinline__ void split_tile(const global_t<Real> *__restrict__ ft
               fo[0][i] = RU[i * NT] + RD[i * NT + W];
               fo[1][i] = RU[i * NT - W] + RD[i * NT];
             });
+            if constexpr (kHelp) static_for<4>([&](auto i) { fx[0][i] = FX[i * NT]; fx[1][i] = FX[i * NT - 1]; });
           } else {
             static_for<4>([&](auto i) { fo[0][i] = FX[i * NT]; fo[1][i] = FX[i * NT - 1]; });
             static_for<4>([&](auto i) {
@@ -1705,12 +1736,27 @@ __global__ __launch_bounds__(2 * Tile<W>::NT) void dugks_split_kernel(const Batc
     const ItemPlanes ip(d, local);
     if (ip.left > 0) {
       const int bx = ip.tile % d.tiles_x, by = ip.tile / d.tiles_x, z1 = ip.z0 + ip.left;
-      if (threadIdx.x < Tile<W>::NT)
-        split_tile<Real, W, 0, O32, Mesh>(src, dst, d.sp, bx, by, ip.z0, z1, L, v,
-                                          static_cast<const Real *>(d.mesh_coef), d.mesh_width);
-      else
-        split_tile<Real, W, 1, O32, Mesh>(src, dst, d.sp, bx, by, ip.z0, z1, L, v,
-                                          static_cast<const Real *>(d.mesh_coef), d.mesh_width);
+      const Real *coef = static_cast<const Real *>(d.mesh_coef);
+      auto march = [&](auto G, auto halo) {
+        split_tile<Real, W, G, O32, Mesh, halo>(src, dst, d.sp, bx, by, ip.z0, z1, L, v, coef, d.mesh_width);
+      };
+      using std::integral_constant;
+      constexpr int NT = Tile<W>::NT;
+      const int t = threadIdx.x;
+      if constexpr (W == 32) {  // see split_tile: A's halo wavefront is its last, B's its first
+        if (t < NT - 64)
+          march(integral_constant<int, 0>{}, std::false_type{});
+        else if (t < NT)
+          march(integral_constant<int, 0>{}, std::true_type{});
+        else if (t < NT + 64)
+          march(integral_constant<int, 1>{}, std::true_type{});
+        else
+          march(integral_constant<int, 1>{}, std::false_type{});
+      } else if (t < NT) {
+        march(integral_constant<int, 0>{}, std::false_type{});
+      } else {
+        march(integral_constant<int, 1>{}, std::false_type{});
+      }
     }
     write_block_partials<2 * Tile<W>::NT / 64>(v, d.partials, d.items, local, reinterpret_cast<double (*)[kNumSums]>(L));
     __syncthreads();
