@@ -1496,6 +1496,24 @@ __device__ __forceinline__ void split_tile(const global_t<Real> *__restrict__ ft
     __syncthreads();
 
     Real fx[2][4];  // A: the x+ and x- faces; B: its halves of the y+ and y- faces, then the faces
+    // B: face between p-1 and p (upper half from plane p, lower half carried
+    // from plane p-1) for A, and the lower half of the next one
+    auto face_below = [&]() {
+      const ZFaceCoef<Real, W, Mesh> zf(mc, p_);
+      gathered<Real, W>(pc, pc, [&](const auto &g, const auto &) {
+        Real mm[4], lo[4];
+        if constexpr (Mesh) {
+          zf.face(g, zl, zn, mm);
+        } else {
+          zface_half<-1>(g, h, mm);
+          zface_half<1>(g, h, lo);
+        }
+        if constexpr (std::decay_t<decltype(g)>::use) {
+          static_for<4>([&](auto i) { RZ[i * NT] = Mesh ? mm[i] : mm[i] + zl[i]; });
+          if constexpr (!Mesh) static_for<4>([&](auto i) { zl[i] = lo[i]; });
+        }
+      });
+    };
     // A: x-faces of a column: its halves and those of the lanes beside
     auto x_faces = [&](const Plane<Real, W> &a, const Plane<Real, W> &b, const Plane<Real, W> &e,
                        const MeshMarch<Real, W> &m, Real *f, Real (&xp)[4], Real (&xm)[4]) {
@@ -1545,22 +1563,7 @@ __device__ __forceinline__ void split_tile(const global_t<Real> *__restrict__ ft
           });
         });
       } else {
-        // face between p-1 and p (upper half from plane p, lower half
-        // carried from plane p-1) for A, and the lower half of the next one
-        const ZFaceCoef<Real, W, Mesh> zf(mc, p_);
-        gathered<Real, W>(pc, pc, [&](const auto &g, const auto &) {
-          Real mm[4], lo[4];
-          if constexpr (Mesh) {
-            zf.face(g, zl, zn, mm);
-          } else {
-            zface_half<-1>(g, h, mm);
-            zface_half<1>(g, h, lo);
-          }
-          if constexpr (std::decay_t<decltype(g)>::use) {
-            static_for<4>([&](auto i) { RZ[i * NT] = Mesh ? mm[i] : mm[i] + zl[i]; });
-            if constexpr (!Mesh) static_for<4>([&](auto i) { zl[i] = lo[i]; });
-          }
-        });
+        face_below();
       }
     }
     if constexpr (G == 1) {
@@ -1743,19 +1746,16 @@ __global__ __launch_bounds__(2 * Tile<W>::NT) void dugks_split_kernel(const Batc
       using std::integral_constant;
       constexpr int NT = Tile<W>::NT;
       const int t = threadIdx.x;
-      if constexpr (W == 32) {  // see split_tile: A's halo wavefront is its last, B's its first
-        if (t < NT - 64)
-          march(integral_constant<int, 0>{}, std::false_type{});
-        else if (t < NT)
-          march(integral_constant<int, 0>{}, std::true_type{});
-        else if (t < NT + 64)
-          march(integral_constant<int, 1>{}, std::true_type{});
-        else
-          march(integral_constant<int, 1>{}, std::false_type{});
-      } else if (t < NT) {
+      const int halo_from = W == 32 ? NT - 64 : NT;
+      if (t < halo_from)
         march(integral_constant<int, 0>{}, std::false_type{});
-      } else {
+      else if (W == 32 ? t >= NT + 64 : t >= NT)
         march(integral_constant<int, 1>{}, std::false_type{});
+      else if constexpr (W == 32) {
+        if (t < NT)
+          march(integral_constant<int, 0>{}, std::true_type{});
+        else
+          march(integral_constant<int, 1>{}, std::true_type{});
       }
     }
     write_block_partials<2 * Tile<W>::NT / 64>(v, d.partials, d.items, local, reinterpret_cast<double (*)[kNumSums]>(L));
