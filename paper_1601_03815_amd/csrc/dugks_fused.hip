@@ -45,10 +45,10 @@
 // Pxz, Pyz, Pzz) of planes p-2, p-1 and p: 16 + 12 + 12 values per column.
 //
 // Two marches implement this.  fused_tile (FP32): one thread per column,
-// 44 values of LDS per column (44 KB for a 32 x 8 tile, two blocks per
+// 58 values of LDS per column (59 KB for a 32 x 8 tile, two blocks per
 // compute unit).  split_tile (FP64): two threads per column, one in each of
 // two groups that hold about half of the populations each (see below), so
-// that a thread's registers fit two waves per SIMD; 70 values per column.
+// that a thread's registers fit two waves per SIMD; 68 values per column.
 // LDS reads are gathered (see gathered()) so that each chunk of work waits
 // for LDS once.
 //
@@ -85,8 +85,9 @@ constexpr int kNPop = 16, kNQ = 6, kNZ = 4;
 constexpr int kLdsValues = kNPop + 2 * kNQ + 3 * kNZ;  // per column
 // The one-thread march adds the ten face-equilibrium terms of the y-face
 // between each column and the next row (read back by the column above as
-// its lower y-face).
-constexpr int kFusedValues = kLdsValues + 10;
+// its lower y-face), and the moments of the column's x+ face and of the
+// z-face below the plane (formed by the halo rows' wavefront).
+constexpr int kFusedValues = kLdsValues + 18;
 constexpr int pop_index(int id) { return (id >= 1 && id <= 4) ? id - 1 : ((id >= 7 && id <= 18) ? id - 3 : -1); }
 constexpr int q_index(int id) {
   switch (id) {
@@ -855,28 +856,47 @@ __device__ __forceinline__ void face_moments_mesh(const MeshMarch<Real, W> &mc, 
   static_for<4>([&](auto i) { m[i] = vl[i] + (m[i] - hsz * s1[i]); });
 }
 
+// Thread number of the one-thread march: a 32-wide tile's wavefronts rotated so
+// that the one with the halo rows is the first of its block, or the third in
+// blocks whose number has an odd multiple of 256 (8 XCDs x 32 compute units: the
+// two blocks a unit starts with).  A block's wavefronts go to the unit's four
+// SIMDs in turn, so the halo wavefronts of its two blocks fall on different
+// SIMDs, where as the last of every block both shared one.  FP32 160^3
+// 228 -> 222 us, 256^3 0.846 -> 0.832 ms.
+template <int W>
+__device__ __forceinline__ int fused_thread() {
+  return W == 32 ? (threadIdx.x + ((blockIdx.x >> 8) & 1 ? 64 : 192)) & 255 : threadIdx.x;
+}
+
 // The z-march of one tile (bx, by) over the planes [z0, z1) of a box; adds
 // the moments of the updated cells to v.  L is the block's LDS, kFusedValues
 // values per column: P [kNPop][NT], Q [2][kNQ][NT], Z [3][kNZ][NT].
 // Mesh: on a stretched mesh with the tables coef (x, y, z rows of
 // MarchCoef) and width (the cell widths, the weights of the sums); the x/y
 // coefficients follow the plane data in L (kMeshValues).
-template <typename Real, int W, bool O32, bool Mesh>
+// Halo: the code of the wavefront that holds the two halo rows of a 32-wide
+// tile (tile_column).  It has no centres of its own and forms the moments of
+// the interior wavefronts' x- and z-faces for them (lane l takes the columns of
+// lane l of each in turn): the march is bound by the interior wavefronts'
+// vector issue, and this one had a third of their work.  128^3 129.5 -> 124.2
+// us, 256^3 0.868 -> 0.846 ms.
+template <typename Real, int W, bool O32, bool Mesh, bool Halo>
 __device__ __forceinline__ void fused_tile(const global_t<Real> *__restrict__ ft, global_t<Real> *__restrict__ out, const StepParams &p,
                                            int bx, int by, int z0, int z1, Real *L, double (&v)[kNumSums],
                                            const Real *coef, const double *width) {
   constexpr int TX = Tile<W>::TX, TY = Tile<W>::TY, IX = Tile<W>::IX, IY = Tile<W>::IY, NT = Tile<W>::NT;
   const int n = p.n;
   const int64_t stride = p.stride;
-  const int tid = tile_column<W>(threadIdx.x);  // column of the tile
+  const int tid = tile_column<W>(fused_thread<W>());  // column of the tile
   const int tx = tid % TX, ty = tid / TX;
   const int x0 = bx * IX, y0 = by * IY;
   int gx = x0 - 1 + tx, gy = y0 - 1 + ty;
   gx = gx < 0 ? gx + n : (gx >= n ? gx % n : gx);
   gy = gy < 0 ? gy + n : (gy >= n ? gy % n : gy);
   const int col = gy * n + gx;
-  const bool inner = tx >= 1 && tx <= TX - 2 && ty >= 1 && ty <= TY - 2 && (x0 + tx - 1) < n && (y0 + ty - 1) < n;
-  const bool rows = ty >= 1 && ty <= TY - 2;                   // interior rows, halo columns too
+  constexpr bool kHelp = W == 32;                              // the halo rows have a wavefront of their own
+  const bool rows = kHelp ? !Halo : ty >= 1 && ty <= TY - 2;   // interior rows, halo columns too
+  const bool inner = rows && tx >= 1 && tx <= TX - 2 && (x0 + tx - 1) < n && (y0 + ty - 1) < n;
   const bool yface = tx >= 1 && tx <= TX - 2 && ty <= TY - 2;  // forms the y+ face
   const Real h = Real(p.h), dt = Real(p.dt);
   const Real dtal = dt * Real(p.alpha), dtbe = dt * Real(p.beta);
@@ -884,6 +904,8 @@ __device__ __forceinline__ void fused_tile(const global_t<Real> *__restrict__ ft
   Real *const LQ = L + kNPop * NT + tid;
   Real *const LZ = L + (kNPop + 2 * kNQ) * NT + tid;
   Real *const LY = L + kLdsValues * NT + tid;
+  Real *const FX = L + (kLdsValues + 10) * NT + tid;
+  Real *const RZ = L + (kLdsValues + 14) * NT + tid;
   MeshMarch<Real, W> mc{};
   const constant_t<double> *wz = nullptr;
   double wxy = 1.0;
@@ -905,22 +927,54 @@ __device__ __forceinline__ void fused_tile(const global_t<Real> *__restrict__ ft
   // Two centres at a time: p-1, completed in plane p's iteration, and p.
   Real acc_0[kQ], fp_0[kQ], acc_1[kQ], fp_1[kQ];
   Real nxt[10];       // z-1 terms of the z-moving populations of centre p+1
-  Real zl[4];         // lower half of the z-face above the previous plane (mesh: its w, and nf in zn)
-  Real zn[4];
+  // lower half of the z-face above the previous plane (mesh: its w, and nf in
+  // zn), of the own column or of each helped one
+  constexpr int kZ = kHelp ? 3 : 1;
+  Real zl[kZ][4], zn[kZ][4];
   static_for<kQ>([&](auto q) { acc_0[q] = acc_1[q] = fp_0[q] = fp_1[q] = Real(0); });
   static_for<10>([&](auto i) { nxt[i] = Real(0); });
-  static_for<4>([&](auto i) { zl[i] = Real(0); zn[i] = Real(0); });
+  static_for<kZ>([&](auto j) { static_for<4>([&](auto i) { zl[j][i] = Real(0); zn[j][i] = Real(0); }); });
 
-  // Completes centre `plane` (acc_c, fp_c): its lower y-face, read from the slot
-  // of the column W before, the store and the sums.  Runs after the barrier
-  // that ends the iteration which formed the faces.
-  auto finish = [&](int plane, Real (&acc_c)[kQ], const Real (&fp_c)[kQ]) {
+  // With the faces formed at plane P: the z-face between P-1 and P to the
+  // centres P-1 (acc_c, fp_c) and P (acc_p), then the x-faces and the lower
+  // y-face (from the slot of the column W before) of centre P-1, its store and
+  // its sums.  Runs after the barrier that ends plane P's iteration, in every
+  // lane of an interior row (the x- terms are the previous lane's x+ terms).
+  auto finish = [&](int P, Real (&acc_c)[kQ], const Real (&fp_c)[kQ], Real (&acc_p)[kQ]) {
+    const int plane = P - 1;
+    if (inner) {
+      Real m[4];
+      static_for<4>([&](auto i) { m[i] = RZ[i * NT]; });
+      Real iw_c = Real(1), iw_p = Real(1);
+      if constexpr (Mesh) iw_c = mc.z(kMarchIw, P - 1), iw_p = mc.z(kMarchIw, P);
+      face_equilibrium<2, Real>(m, p, dtbe, [&](auto q, Real val) {
+        if constexpr (Mesh) {
+          acc_c[q] -= iw_c * val;
+          acc_p[q] += iw_p * val;
+        } else {
+          acc_c[q] -= val;
+          acc_p[q] += val;
+        }
+      });
+    }
+    if (P <= z0) return;
+    Real mx[4], fxp[10], fxm[10];
+    static_for<4>([&](auto i) { mx[i] = FX[i * NT]; });
+    face_terms<0>(mx, p, dtbe, fxp);
+    static_for<10>([&](auto k) { fxm[k] = from_previous_lane(fxp[k]); });
+    if (!inner) return;
     Real fym[10];
     static_for<10>([&](auto k) { fym[k] = LY[k * NT - W]; });
-    if constexpr (Mesh)
+    if constexpr (Mesh) {
+      const Real iw = mc.template col<0>(kMarchIw);
+      apply_terms<0, 1>(fxp, iw, acc_c);
+      apply_terms<0, -1>(fxm, iw, acc_c);
       apply_terms<1, -1>(fym, mc.template col<1>(kMarchIw), acc_c);
-    else
+    } else {
+      apply_terms<0, 1>(fxp, acc_c);
+      apply_terms<0, -1>(fxm, acc_c);
       apply_terms<1, -1>(fym, acc_c);
+    }
     const int cell = plane * n * n + col;
     // plain (L2-allocating) stores: a tile row's 30 updated cells do not
     // fill whole 128-byte lines, and L2 merges them with the neighbouring
@@ -948,7 +1002,7 @@ __device__ __forceinline__ void fused_tile(const global_t<Real> *__restrict__ ft
   // returns false), so that every centre is completed by the same code (and
   // rounds the same whatever the chunk length).
   auto iteration = [&](int p_, Real (&acc_c)[kQ], const Real (&fp_c)[kQ], Real (&acc_p)[kQ], Real (&fp_p)[kQ]) {
-    if (p_ - 1 > z0 && inner) finish(p_ - 2, acc_p, fp_p);
+    if (p_ > z0 && rows) finish(p_ - 1, acc_p, fp_p, acc_c);
     if (p_ > z1) return false;
     const bool has_prev = p_ > z0;          // centre p-1 is in the chunk
     const bool has_cur = p_ >= z0 && p_ < z1;
@@ -979,11 +1033,11 @@ __device__ __forceinline__ void fused_tile(const global_t<Real> *__restrict__ ft
     });
     __syncthreads();
 
-    if (inner) {
-      // face between p-1 and p (upper half from plane p, lower half carried
-      // from plane p-1) and the lower half of the face between p and p+1
-      const ZFaceCoef<Real, W, Mesh> zf(mc, p_);
-      gathered<Real, W>(c, c, [&](const auto &g, const auto &) {
+    // face between p-1 and p of a column (upper half from plane p, lower half
+    // carried from plane p-1), and the lower half of the next one
+    auto face_below = [&](const Plane<Real, W> &pl, const MeshMarch<Real, W> &cf, Real *rz, Real (&zl)[4], Real (&zn)[4]) {
+      const ZFaceCoef<Real, W, Mesh> zf(cf, p_);
+      gathered<Real, W>(pl, pl, [&](const auto &g, const auto &) {
         Real m[4], lo[4];
         if constexpr (Mesh) {
           zf.face(g, zl, zn, m);
@@ -992,19 +1046,32 @@ __device__ __forceinline__ void fused_tile(const global_t<Real> *__restrict__ ft
           zface_half<1>(g, h, lo);
         }
         if constexpr (std::decay_t<decltype(g)>::use) {
-          if constexpr (!Mesh) static_for<4>([&](auto i) { m[i] += zl[i]; });
-          face_equilibrium<2, Real>(m, p, dtbe, [&](auto q, Real val) {
-            if constexpr (Mesh) {
-              acc_c[q] -= zf.iw_c * val;
-              acc_p[q] += zf.iw_p * val;
-            } else {
-              acc_c[q] -= val;   // upper face of centre p-1
-              acc_p[q] += val;   // lower face of centre p
-            }
-          });
+          static_for<4>([&](auto i) { rz[i * NT] = Mesh ? m[i] : m[i] + zl[i]; });
           if constexpr (!Mesh) static_for<4>([&](auto i) { zl[i] = lo[i]; });
         }
       });
+    };
+    // x+ face of a column: its upper half and the next lane's lower one
+    auto face_right = [&](const Plane<Real, W> &a, const Plane<Real, W> &b, const Plane<Real, W> &e,
+                          const MeshMarch<Real, W> &cf, Real *f) {
+      Real up[4], dn[4];
+      face_halves<0, Mesh>(cf, p_, h, a, b, e, up, dn);
+      static_for<4>([&](auto i) { f[i * NT] = up[i] + from_next_lane(dn[i]); });
+    };
+    if constexpr (Halo) {
+      static_for<3>([&](auto j) {
+        const int d = tile_column<W>(j * 64 + (threadIdx.x & 63)) - tid;
+        MeshMarch<Real, W> cf = mc;
+        if constexpr (Mesh) cf.Y += d / W;  // the same x, d / W rows further
+        const Plane<Real, W> a{nullptr, c.Q + d, c.Z + d}, b{nullptr, c1.Q + d, c1.Z + d}, e{nullptr, nullptr, c2.Z + d};
+        face_below(a, cf, RZ + d, zl[j], zn[j]);
+        if (has_prev) face_right(a, b, e, cf, FX + d);
+      });
+    } else if constexpr (!kHelp) {
+      if (inner) face_below(c, mc, RZ, zl[0], zn[0]);
+      if (has_prev && rows) face_right(c, c1, c2, mc, FX);
+    }
+    if (inner) {
       // diagonal z-moving populations: the in-plane differences D = B(+d1)
       // - B(-d1) and sums S = B(+d1) + B(-d1) of plane p enter centre p-1
       // (z+1 mixed term), centre p (in-plane terms) and centre p+1 (z-1
@@ -1030,8 +1097,8 @@ __device__ __forceinline__ void fused_tile(const global_t<Real> *__restrict__ ft
       });
     }
     if (has_prev) {
-      // x- and y-faces of centre p-1: in-plane part from plane p-1, the
-      // z-tangential gradients -h/4 [(M_L + M_R)(p) - (M_L + M_R)(p-2)]
+      // y-faces of centre p-1: in-plane part from plane p-1, the z-tangential
+      // gradients -h/4 [(M_L + M_R)(p) - (M_L + M_R)(p-2)]
       const Real hq = Real(0.25) * h;
       auto face_moments = [&](auto D, auto LX, auto LY, Real (&m)[4]) {
         if constexpr (Mesh) {
@@ -1052,26 +1119,10 @@ __device__ __forceinline__ void fused_tile(const global_t<Real> *__restrict__ ft
       };
       using I0 = std::integral_constant<int, 0>;
       using I1 = std::integral_constant<int, 1>;
-      using Im1 = std::integral_constant<int, -1>;
-      // Each x-face is formed once: every column of an interior row but the
-      // last (the halo column 0 too) forms its x+ face and that face's ten
-      // equilibrium terms, and a column's x- terms are the x+ terms of the
-      // column before it, the previous lane (a tile row is 32 consecutive
-      // lanes of one wavefront).  The lane shift runs with every lane active.
-      Real mxp[4] = {Real(0), Real(0), Real(0), Real(0)};
-      if (rows) {
-        Real up[4], dn[4];
-        face_halves<0, Mesh>(mc, p_, h, c, c1, c2, up, dn);
-        static_for<4>([&](auto i) { mxp[i] = up[i] + from_next_lane(dn[i]); });
-      }
-      Real fxp[10], fxm[10];
-      face_terms<0>(mxp, p, dtbe, fxp);
-      static_for<10>([&](auto k) { fxm[k] = from_previous_lane(fxp[k]); });
-      // The y-face between the column and the next row is formed once too,
-      // by every interior column of every row but the last (halo row 0
-      // too); its ten terms are left in LY for the column above, which
-      // applies them as its lower face in finish() after the barrier that
-      // ends this iteration.
+      // The y-face between the column and the next row is formed once, by
+      // every interior column of every row but the last (halo row 0 too); its
+      // ten terms are left in LY for the column above, which applies them as
+      // its lower face in finish().
       if (yface) {
         Real my[4], fy[10];
         face_moments(I1{}, I0{}, I0{}, my);
@@ -1082,16 +1133,6 @@ __device__ __forceinline__ void fused_tile(const global_t<Real> *__restrict__ ft
             apply_terms<1, 1>(fy, mc.template col<1>(kMarchIw), acc_c);
           else
             apply_terms<1, 1>(fy, acc_c);    // y+
-        }
-      }
-      if (inner) {
-        if constexpr (Mesh) {
-          const Real iw = mc.template col<0>(kMarchIw);
-          apply_terms<0, 1>(fxp, iw, acc_c);
-          apply_terms<0, -1>(fxm, iw, acc_c);
-        } else {
-          apply_terms<0, 1>(fxp, acc_c);   // x+
-          apply_terms<0, -1>(fxm, acc_c);  // x-
         }
       }
     }
@@ -1242,9 +1283,16 @@ __global__ __launch_bounds__(Tile<W>::NT, kWavesPerSimd<Real>) void dugks_fused_
     global_t<Real> *dst = to_global(static_cast<Real *>(d.f[d.cur ^ 1]));
     const ItemPlanes ip(d, local);
     // the march ends with a barrier: L is free for the block reduction
-    if (ip.left > 0)
-      fused_tile<Real, W, O32, Mesh>(src, dst, d.sp, ip.tile % d.tiles_x, ip.tile / d.tiles_x, ip.z0, ip.z0 + ip.left, L,
-                                     v, static_cast<const Real *>(d.mesh_coef), d.mesh_width);
+    if (ip.left > 0) {
+      auto march = [&](auto halo) {
+        fused_tile<Real, W, O32, Mesh, halo>(src, dst, d.sp, ip.tile % d.tiles_x, ip.tile / d.tiles_x, ip.z0,
+                                             ip.z0 + ip.left, L, v, static_cast<const Real *>(d.mesh_coef), d.mesh_width);
+      };
+      if (W != 32 || fused_thread<W>() < Tile<W>::NT - 64)
+        march(std::false_type{});
+      else if constexpr (W == 32)
+        march(std::true_type{});
+    }
     write_block_partials<Tile<W>::NT / 64>(v, d.partials, d.items, local, reinterpret_cast<double (*)[kNumSums]>(L));
     __syncthreads();
   }
@@ -1775,8 +1823,8 @@ __global__ void store_table_kernel(BatchBox e0, BatchBox e1, BatchBox *__restric
 }  // namespace fused
 
 // Default tile: 32 x 8 columns in both precisions (rows of 256 B in FP64).
-// FP64 (split march, 512 threads): 140 KB of LDS, one block per compute
-// unit; FP32 (256 threads): 51 KB of LDS, two blocks per compute unit
+// FP64 (split march, 512 threads): 136 KB of LDS, one block per compute
+// unit; FP32 (256 threads): 59 KB of LDS, two blocks per compute unit
 // (two waves per SIMD).
 constexpr int fused_tile_width(int) { return 32; }
 
