@@ -219,10 +219,10 @@ void enqueue_step(dhit_batch &bt, int commit) {
   const int nbox = (int)bt.boxes.size();
   if (bt.method == DHIT_DUGKS)
     dhit::launch_dugks_batch(bt.stream, bt.precision, bt.tile, bt.max_n, bt.d_boxes, nbox, bt.total_items, bt.grid,
-                             false);
+                             false, {});
   else
     dhit::launch_lbe_batch(bt.stream, bt.method, bt.precision, {bt.cells_per_thread, dhit::kBlock}, bt.d_boxes, nbox,
-                           bt.total_items, bt.grid);
+                           bt.total_items, bt.grid, {});
   dhit::launch_finalize_batch(bt.stream, bt.d_boxes, nbox, commit);
 }
 

@@ -246,7 +246,7 @@ int64_t population_buffer_bytes(const dhit_params *p) {
 int64_t box_bytes(const dhit_params *p) {
   int64_t pop = population_buffer_bytes(p);
   if (pop < 0) return pop;
-  return 2 * pop + (reduction_blocks(*p) * 5 + dhit::kFinalizeDoubles) * 8 + dhit::kHistoryCap * 5 * 8 +
+  return 2 * pop + (reduction_blocks(*p) * 2 * 5 + dhit::kFinalizeDoubles) * 8 + dhit::kHistoryCap * 5 * 8 +
          scratch_bytes_of(*p, pop) +
          step_table_bytes(*p);
 }
@@ -293,15 +293,15 @@ int32_t create_box(const dhit_params *pp, dhit_box **out) {
           fail(DHIT_ENOMEM, "cannot allocate population buffers");
       }
       b->max_blocks = (int)reduction_blocks(b->p);
-      // block partials, then the wide finalisation's level sums and counter
-      if (hipMalloc(&b->partials, ((size_t)b->max_blocks * 5 + dhit::kFinalizeDoubles) * sizeof(double)) != hipSuccess ||
+      // two sets of block partials, then the wide finalisation's level sums and counter
+      if (hipMalloc(&b->partials, ((size_t)b->max_blocks * 2 * 5 + dhit::kFinalizeDoubles) * sizeof(double)) != hipSuccess ||
           hipMalloc(&b->hist, (size_t)dhit::kHistoryCap * 5 * sizeof(double)) != hipSuccess)
         fail(DHIT_ENOMEM, "cannot allocate reduction buffers");
       if (scratch_bytes_of(*pp, pop) > 0) {
         if (hipMalloc(&b->scratch, scratch_bytes_of(*pp, pop)) != hipSuccess)
           fail(DHIT_ENOMEM, "cannot allocate DUGKS scratch field");
       }
-      b->reduce_level = b->partials + (size_t)b->max_blocks * 5;
+      b->reduce_level = b->partials + (size_t)b->max_blocks * 2 * 5;
       DHIT_HIP(hipMemsetAsync(b->reduce_level, 0, dhit::kFinalizeDoubles * sizeof(double), b->stream));
       derive_step_params(*b);
       if (step_table_bytes(b->p) > 0) {
@@ -548,14 +548,16 @@ static int32_t step_common(dhit_box *b, int32_t nsteps, bool lbe) {
     if (nsteps < 0) fail(DHIT_EINVAL, "nsteps must be >= 0");
     const bool is_lbe = b->p.method != DHIT_DUGKS;
     if (is_lbe != lbe) fail(DHIT_EMETHOD, lbe ? "step_lbe called on a DUGKS box" : "step_dugks called on an LBE box");
+    dhit::PendingSums pend{};
     for (int32_t s = 0; s < nsteps; ++s) {
+      const bool defer = s + 1 < nsteps;
       double *slot = b->hist + (b->steps % dhit::kHistoryCap) * 5;
       const void *src = b->f[b->cur];
       void *dst = b->f[1 - b->cur];
       if (lbe)
-        dhit::launch_lbe_step(*b, src, dst, slot);
+        dhit::launch_lbe_step(*b, src, dst, slot, defer, &pend);
       else
-        dhit::launch_dugks_step(*b, src, dst, slot);
+        dhit::launch_dugks_step(*b, src, dst, slot, defer, &pend);
       b->cur = 1 - b->cur;
       b->steps++;
     }
@@ -746,9 +748,9 @@ int32_t step_noalloc(const dhit_params *pp, const void *src, void *dst, double *
     b.step_table = reinterpret_cast<dhit::BatchBox *>(ws + kNoallocTable);
     dhit::launch_store_table(b.stream, e, b.step_table);
     if (p.method == DHIT_DUGKS)
-      dhit::launch_dugks_step(b, src, dst, out);
+      dhit::launch_dugks_step(b, src, dst, out, false, nullptr);
     else
-      dhit::launch_lbe_step(b, src, dst, out);
+      dhit::launch_lbe_step(b, src, dst, out, false, nullptr);
     return DHIT_OK;
   });
 }

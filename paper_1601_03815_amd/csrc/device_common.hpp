@@ -6,6 +6,7 @@
 #include <cstdint>
 
 #include "lattice.hpp"
+#include "runtime.hpp"
 
 namespace dhit {
 
@@ -220,6 +221,33 @@ __device__ __forceinline__ void write_block_partials(double (&v)[kNumSums], doub
                                                      int block) {
   __shared__ double smem[NW][kNumSums];
   write_block_partials<NW>(v, partials, nblocks, block, smem);
+}
+
+// Adds up the partials of the step before (at most kPendingMax), by one block
+// of NW wavefronts in the order of a 1024-thread finalisation launch: its
+// wavefronts' trees in turn, then their totals in order.  smem: 16 rows.
+template <int NW>
+__device__ __forceinline__ void add_pending(const double *partials, int nblocks, double *out, double (*smem)[kNumSums]) {
+  constexpr int kTurns = kPendingMax / 64 / NW;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = (nblocks + 63) / 64;
+  double v[kTurns][kNumSums];  // all turns' loads in flight together
+  static_for<kTurns>([&](auto k) {
+    const int b = (k * NW + wave) * 64 + lane;
+    static_for<kNumSums>([&](auto i) { v[k][i] = b < nblocks ? to_global(partials)[i * nblocks + b] : 0.0; });
+  });
+  static_for<kTurns>([&](auto k) {
+    if (k * NW + wave < waves)
+      static_for<kNumSums>([&](auto i) {
+        const double t = wave_sum(v[k][i]);
+        if (lane == 0) smem[k * NW + wave][i] = t;
+      });
+  });
+  __syncthreads();
+  if (threadIdx.x < kNumSums) {
+    double t = smem[0][threadIdx.x];
+    for (int w = 1; w < waves; ++w) t += smem[w][threadIdx.x];
+    to_global(out)[threadIdx.x] = t;
+  }
 }
 
 // Flat-index offsets of the +-1 neighbours along one axis with periodic

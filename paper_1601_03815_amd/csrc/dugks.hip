@@ -184,9 +184,9 @@ static void dugks_two_pass(dhit_box &b, const void *src, void *dst, double *sums
   launch_finalize_sums(b, b.partials, blocks, sums_out);
 }
 
-void launch_dugks_step(dhit_box &b, const void *src, void *dst, double *sums_out) {
+void launch_dugks_step(dhit_box &b, const void *src, void *dst, double *sums_out, bool defer, PendingSums *pend) {
   if (b.mesh || b.p.variant == DHIT_VARIANT_DEFAULT) {  // a stretched mesh runs the fused march whatever the variant
-    launch_dugks_fused(b, src, dst, sums_out);
+    launch_dugks_fused(b, src, dst, sums_out, defer, pend);
     return;
   }
   if (b.p.precision == DHIT_FP64)

@@ -1269,11 +1269,17 @@ __device__ __forceinline__ int xcd_tile(int b, int padded) { return (b & 7) * (p
 // a batch run the same machine code and give the same bits.
 template <typename Real, int W, bool O32, bool Mesh>
 __global__ __launch_bounds__(Tile<W>::NT, kWavesPerSimd<Real>) void dugks_fused_kernel(const BatchBox *__restrict__ boxes, int nbox,
-                                                                  int total_items) {
+                                                                  int total_items, PendingSums prev) {
   __shared__ Real L[kFusedValues * Tile<W>::NT + (Mesh ? kMeshValues<W> : 0)];
-  const int G = gridDim.x;
+  // the extra block (see launch_lbe_step) is the first; the others keep their
+  // distribution over the XCDs, one further on
+  const int extra = prev.nblocks > 0, G = gridDim.x - extra, block = blockIdx.x - extra;
+  if (block < 0) {
+    add_pending<Tile<W>::NT / 64>(prev.partials, prev.nblocks, prev.out, reinterpret_cast<double (*)[kNumSums]>(L));
+    return;
+  }
   for (int base = 0; base < total_items; base += G) {
-    const int it = base + xcd_tile(blockIdx.x, G);
+    const int it = base + xcd_tile(block, G);
     if (it >= total_items) continue;
     const int b = find_batch_box(boxes, nbox, it);
     const BatchBox &d = boxes[b];
@@ -1772,11 +1778,17 @@ __device__ __forceinline__ void split_tile(const global_t<Real> *__restrict__ ft
 // Work-list kernel of the split march (see dugks_fused_kernel).
 template <typename Real, int W, bool O32, bool Mesh>
 __global__ __launch_bounds__(2 * Tile<W>::NT) void dugks_split_kernel(const BatchBox *__restrict__ boxes, int nbox,
-                                                                      int total_items) {
+                                                                      int total_items, PendingSums prev) {
   __shared__ Real L[kSplitValues * Tile<W>::NT + (Mesh ? kMeshValues<W> : 0)];
-  const int G = gridDim.x;
+  // the extra block (see launch_lbe_step) is the first; the others keep their
+  // distribution over the XCDs, one further on
+  const int extra = prev.nblocks > 0, G = gridDim.x - extra, block = blockIdx.x - extra;
+  if (block < 0) {
+    add_pending<2 * Tile<W>::NT / 64>(prev.partials, prev.nblocks, prev.out, reinterpret_cast<double (*)[kNumSums]>(L));
+    return;
+  }
   for (int base = 0; base < total_items; base += G) {
-    const int it = base + xcd_tile(blockIdx.x, G);
+    const int it = base + xcd_tile(block, G);
     if (it >= total_items) continue;
     const int b = find_batch_box(boxes, nbox, it);
     const BatchBox &d = boxes[b];
@@ -1927,14 +1939,15 @@ template <typename Real>
 constexpr bool kSplit = sizeof(Real) == 8;
 
 template <typename Real, int W, bool O32, bool Mesh>
-static void list_launch(hipStream_t s, const BatchBox *d_boxes, int nbox, int total_items, int grid) {
+static void list_launch(hipStream_t s, const BatchBox *d_boxes, int nbox, int total_items, int grid,
+                        const PendingSums &prev) {
   grid = (grid + 7) / 8 * 8;  // the XCD numbering of work items needs a multiple of 8
   if constexpr (kSplit<Real>)
-    hipLaunchKernelGGL((fused::dugks_split_kernel<Real, W, O32, Mesh>), dim3(grid), dim3(2 * fused::Tile<W>::NT), 0, s,
-                       d_boxes, nbox, total_items);
+    hipLaunchKernelGGL((fused::dugks_split_kernel<Real, W, O32, Mesh>), dim3(grid + (prev.nblocks > 0)), dim3(2 * fused::Tile<W>::NT), 0, s,
+                       d_boxes, nbox, total_items, prev);
   else
-    hipLaunchKernelGGL((fused::dugks_fused_kernel<Real, W, O32, Mesh>), dim3(grid), dim3(fused::Tile<W>::NT), 0, s,
-                       d_boxes, nbox, total_items);
+    hipLaunchKernelGGL((fused::dugks_fused_kernel<Real, W, O32, Mesh>), dim3(grid + (prev.nblocks > 0)), dim3(fused::Tile<W>::NT), 0, s,
+                       d_boxes, nbox, total_items, prev);
 }
 
 // Whether 32-bit byte offsets reach every cell of one population array of
@@ -1945,25 +1958,26 @@ static bool offsets32(int max_n, int precision) {
 }
 
 template <typename Real, bool Mesh>
-static void list_launch(hipStream_t s, int w, bool o32, const BatchBox *d_boxes, int nbox, int total_items, int grid) {
+static void list_launch(hipStream_t s, int w, bool o32, const BatchBox *d_boxes, int nbox, int total_items, int grid,
+                        const PendingSums &prev) {
   if (w == 16)
-    o32 ? list_launch<Real, 16, true, Mesh>(s, d_boxes, nbox, total_items, grid)
-        : list_launch<Real, 16, false, Mesh>(s, d_boxes, nbox, total_items, grid);
+    o32 ? list_launch<Real, 16, true, Mesh>(s, d_boxes, nbox, total_items, grid, prev)
+        : list_launch<Real, 16, false, Mesh>(s, d_boxes, nbox, total_items, grid, prev);
   else
-    o32 ? list_launch<Real, 32, true, Mesh>(s, d_boxes, nbox, total_items, grid)
-        : list_launch<Real, 32, false, Mesh>(s, d_boxes, nbox, total_items, grid);
+    o32 ? list_launch<Real, 32, true, Mesh>(s, d_boxes, nbox, total_items, grid, prev)
+        : list_launch<Real, 32, false, Mesh>(s, d_boxes, nbox, total_items, grid, prev);
 }
 
 void launch_dugks_batch(hipStream_t s, int precision, int w, int max_n, const BatchBox *d_boxes, int nbox,
-                        int total_items, int grid, bool mesh) {
+                        int total_items, int grid, bool mesh, const PendingSums &prev) {
   if (w != 16 && w != 32) throw Error(DHIT_EINVAL, "fused DUGKS tile width must be 16 or 32");
   const bool o32 = offsets32(max_n, precision);
   if (precision == DHIT_FP64)
-    mesh ? list_launch<double, true>(s, w, o32, d_boxes, nbox, total_items, grid)
-         : list_launch<double, false>(s, w, o32, d_boxes, nbox, total_items, grid);
+    mesh ? list_launch<double, true>(s, w, o32, d_boxes, nbox, total_items, grid, prev)
+         : list_launch<double, false>(s, w, o32, d_boxes, nbox, total_items, grid, prev);
   else
-    mesh ? list_launch<float, true>(s, w, o32, d_boxes, nbox, total_items, grid)
-         : list_launch<float, false>(s, w, o32, d_boxes, nbox, total_items, grid);
+    mesh ? list_launch<float, true>(s, w, o32, d_boxes, nbox, total_items, grid, prev)
+         : list_launch<float, false>(s, w, o32, d_boxes, nbox, total_items, grid, prev);
   DHIT_HIP(hipGetLastError());
 }
 
@@ -1983,7 +1997,7 @@ void fused_table_entries(const dhit_box &b, BatchBox (&e)[2]) {
     e[c].nz_chunk = f.chunk;
     e[c].tail_from = f.tail_from;
     e[c].tail_split = f.tail_split;
-    e[c].partials = b.partials;
+    e[c].partials = b.partials + (size_t)c * 5 * b.max_blocks;
     e[c].hist = b.hist;
     e[c].cur = c;
     e[c].mesh_width = b.mesh;
@@ -1996,7 +2010,7 @@ void launch_store_table(hipStream_t s, const BatchBox (&e)[2], BatchBox *dst) {
   DHIT_HIP(hipGetLastError());
 }
 
-static void fused_step(dhit_box &b, const void *src, void *dst, double *sums_out) {
+static void fused_step(dhit_box &b, const void *src, void *dst, double *sums_out, bool defer, PendingSums *pend) {
   if (!b.step_table) throw Error(DHIT_EINVAL, "box has no fused-step table");
   int entry;
   if (src == b.f[0] && dst == b.f[1]) entry = 0;
@@ -2006,10 +2020,10 @@ static void fused_step(dhit_box &b, const void *src, void *dst, double *sums_out
   {
     TimedLaunch t(b, DHIT_K_DUGKS_FUSED);
     launch_dugks_batch(b.stream, b.p.precision, f.width, b.n, b.step_table + entry, 1, f.items, f.grid,
-                       b.mesh != nullptr);
+                       b.mesh != nullptr, pend ? *pend : PendingSums{});
     t.done();
   }
-  launch_finalize_sums(b, b.partials, f.items, sums_out);
+  finish_step(b, b.partials + (size_t)entry * 5 * b.max_blocks, f.items, sums_out, defer, pend);
 }
 
 int fused_tile_width_of(int precision) { return fused_tile_width(precision); }
@@ -2107,6 +2121,8 @@ int fused_auto_chunk(const dhit_params &p) {
   return fused_balanced_chunk(p.n, f.tiles_x * f.tiles_y, fused_slots(p.precision, f.width));
 }
 
-void launch_dugks_fused(dhit_box &b, const void *src, void *dst, double *sums_out) { fused_step(b, src, dst, sums_out); }
+void launch_dugks_fused(dhit_box &b, const void *src, void *dst, double *sums_out, bool defer, PendingSums *pend) {
+  fused_step(b, src, dst, sums_out, defer, pend);
+}
 
 }  // namespace dhit

@@ -207,6 +207,15 @@ void launch_finalize_sums(dhit_box &b, const double *partials, int nblocks, doub
   t.done();
 }
 
+void finish_step(dhit_box &b, const double *partials, int nblocks, double *sums_out, bool defer, PendingSums *pend) {
+  if (defer && pend && nblocks <= kPendingMax && !(b.timer && b.timer->enabled)) {
+    *pend = {partials, nblocks, sums_out};
+    return;
+  }
+  if (pend) *pend = {nullptr, 0, nullptr};
+  launch_finalize_sums(b, partials, nblocks, sums_out);
+}
+
 void launch_init_equilibrium(dhit_box &b, const double *d_u, const double *d_drho, void *dst) {
   const int blocks = cell_blocks(b.ncell);
   const bool mrt = b.p.method == DHIT_LBE_MRT;

@@ -230,11 +230,20 @@ void launch_lbe_hold(dhit_box &b, const void *src, void *dst, const double *d_u,
 // one box of the device table `boxes` (sorted by item_begin), where C, 1 or
 // kRunCells<Real>, and the block size B are the same for the whole launch.  A
 // single box is a table of one entry.  The per-item partial sums are laid out
-// as a block launch's would be.
+// as a block launch's would be.  With prev the launch has one more block, which
+// adds up the partials of the step before (see launch_lbe_step).
 template <int K, typename Real, int C, int B>
-__global__ __launch_bounds__(B) void lbe_kernel(const BatchBox *__restrict__ boxes, int nbox, int total_items) {
-  __shared__ double smem[B / 64][kNumSums];
-  for (int it = blockIdx.x; it < total_items; it += gridDim.x) {
+__global__ __launch_bounds__(B) void lbe_kernel(const BatchBox *__restrict__ boxes, int nbox, int total_items,
+                                                PendingSums prev) {
+  __shared__ double smem[kPendingMax / 64][kNumSums];
+  // the extra block is the first: it starts with the others and has ended
+  // before they do
+  const int extra = prev.nblocks > 0, G = gridDim.x - extra, block = blockIdx.x - extra;
+  if (block < 0) {
+    add_pending<B / 64>(prev.partials, prev.nblocks, prev.out, smem);
+    return;
+  }
+  for (int it = block; it < total_items; it += G) {
     const int b = find_batch_box(boxes, nbox, it);
     const BatchBox &d = boxes[b];
     const int local = it - d.item_begin;
@@ -266,32 +275,35 @@ int lbe_items(int64_t ncell, const LbeSplit &s) {
 }
 
 template <typename Real, int C, int B>
-static void lbe_launch_typed(hipStream_t s, int method, const BatchBox *d_boxes, int nbox, int total_items, int grid) {
+static void lbe_launch_typed(hipStream_t s, int method, const BatchBox *d_boxes, int nbox, int total_items, int grid,
+                             const PendingSums &prev) {
   if (method == DHIT_LBE_BGK)
-    hipLaunchKernelGGL((lbe_kernel<kBGK, Real, C, B>), dim3(grid), dim3(B), 0, s, d_boxes, nbox, total_items);
+    hipLaunchKernelGGL((lbe_kernel<kBGK, Real, C, B>), dim3(grid + (prev.nblocks > 0)), dim3(B), 0, s, d_boxes, nbox,
+                       total_items, prev);
   else
-    hipLaunchKernelGGL((lbe_kernel<kMRT, Real, C, B>), dim3(grid), dim3(B), 0, s, d_boxes, nbox, total_items);
+    hipLaunchKernelGGL((lbe_kernel<kMRT, Real, C, B>), dim3(grid + (prev.nblocks > 0)), dim3(B), 0, s, d_boxes, nbox,
+                       total_items, prev);
 }
 
 template <typename Real>
 static void lbe_launch_split(hipStream_t s, int method, const LbeSplit &w, const BatchBox *d_boxes, int nbox,
-                             int total_items, int grid) {
+                             int total_items, int grid, const PendingSums &prev) {
   if (w.threads == kSmallBlock && w.cells == 1)
-    lbe_launch_typed<Real, 1, kSmallBlock>(s, method, d_boxes, nbox, total_items, grid);
+    lbe_launch_typed<Real, 1, kSmallBlock>(s, method, d_boxes, nbox, total_items, grid, prev);
   else if (w.threads == kBlock && w.cells == kRunCells<Real>)
-    lbe_launch_typed<Real, kRunCells<Real>, kBlock>(s, method, d_boxes, nbox, total_items, grid);
+    lbe_launch_typed<Real, kRunCells<Real>, kBlock>(s, method, d_boxes, nbox, total_items, grid, prev);
   else if (w.threads == kBlock && w.cells == 1)
-    lbe_launch_typed<Real, 1, kBlock>(s, method, d_boxes, nbox, total_items, grid);
+    lbe_launch_typed<Real, 1, kBlock>(s, method, d_boxes, nbox, total_items, grid, prev);
   else
     throw Error(DHIT_EINVAL, "no LBE kernel for this work split");
 }
 
 void launch_lbe_batch(hipStream_t s, int method, int precision, const LbeSplit &w, const BatchBox *d_boxes, int nbox,
-                      int total_items, int grid) {
+                      int total_items, int grid, const PendingSums &prev) {
   if (precision == DHIT_FP64)
-    lbe_launch_split<double>(s, method, w, d_boxes, nbox, total_items, grid);
+    lbe_launch_split<double>(s, method, w, d_boxes, nbox, total_items, grid, prev);
   else
-    lbe_launch_split<float>(s, method, w, d_boxes, nbox, total_items, grid);
+    lbe_launch_split<float>(s, method, w, d_boxes, nbox, total_items, grid, prev);
   DHIT_HIP(hipGetLastError());
 }
 
@@ -306,13 +318,13 @@ void lbe_table_entries(const dhit_box &b, BatchBox (&e)[2]) {
     e[c].ncell = (int)b.ncell;
     e[c].item_begin = 0;
     e[c].items = lbe_items(b.ncell, w);
-    e[c].partials = b.partials;
+    e[c].partials = b.partials + (size_t)c * 5 * b.max_blocks;
     e[c].hist = b.hist;
     e[c].cur = c;
   }
 }
 
-void launch_lbe_step(dhit_box &b, const void *src, void *dst, double *sums_out) {
+void launch_lbe_step(dhit_box &b, const void *src, void *dst, double *sums_out, bool defer, PendingSums *pend) {
   if (!b.step_table) throw Error(DHIT_EINVAL, "box has no step table");
   int entry;
   if (src == b.f[0] && dst == b.f[1]) entry = 0;
@@ -322,10 +334,11 @@ void launch_lbe_step(dhit_box &b, const void *src, void *dst, double *sums_out) 
   const int items = lbe_items(b.ncell, w);
   {
     TimedLaunch t(b, DHIT_K_LBE);
-    launch_lbe_batch(b.stream, b.p.method, b.p.precision, w, b.step_table + entry, 1, items, items);
+    launch_lbe_batch(b.stream, b.p.method, b.p.precision, w, b.step_table + entry, 1, items, items,
+                     pend ? *pend : PendingSums{});
     t.done();
   }
-  launch_finalize_sums(b, b.partials, items, sums_out);
+  finish_step(b, b.partials + (size_t)entry * 5 * b.max_blocks, items, sums_out, defer, pend);
 }
 
 }  // namespace dhit

@@ -88,6 +88,16 @@ struct BatchBox {
   int64_t step;
 };
 
+// Block partials [5][nblocks] of a step whose sums go to out; nblocks = 0: none.
+struct PendingSums {
+  const double *partials;
+  int nblocks;
+  double *out;
+};
+// Partials that a step kernel's extra block adds up at most (one per thread of
+// the finalisation launch it stands for).
+constexpr int kPendingMax = 1024;
+
 // Box of work item `it`: the last box whose first item is <= it.
 __device__ __forceinline__ int find_batch_box(const BatchBox *boxes, int nbox, int it) {
   int lo = 0, hi = nbox - 1;
@@ -124,7 +134,7 @@ struct dhit_box {
   int cur = 0;               // f[cur] holds the state
   hipStream_t stream = nullptr;
   bool own_stream = false;
-  double *partials = nullptr;  // [5][max_blocks]
+  double *partials = nullptr;  // [2][5][max_blocks]: one set per buffer phase (see launch_lbe_step)
   double *reduce_level = nullptr;  // work space of the wide finalisation (kFinalizeDoubles), NULL: one block
   int max_blocks = 0;
   double *hist = nullptr;      // [kHistoryCap][5]
@@ -156,9 +166,16 @@ void box_gone();
 void set_last_error(const std::string &m);
 
 // Launchers (each enqueues on b.stream; src/dst are population buffers).
-void launch_lbe_step(dhit_box &b, const void *src, void *dst, double *sums_out);
-void launch_dugks_step(dhit_box &b, const void *src, void *dst, double *sums_out);
-void launch_dugks_fused(dhit_box &b, const void *src, void *dst, double *sums_out);
+// A step's sums go to sums_out.  In a run of steps the launch that adds a
+// step's partials up would take as long as a small box's step itself; so with
+// defer the step leaves them in *pend, and the next step's launch, given that
+// pend, adds them up with one block of its own (the two steps' partials are in
+// the sets of the two buffer phases).  Same additions in the same order as the
+// finalisation launch, same bits.  The last step of a run does not defer.
+// Steps of more than kPendingMax blocks, and timed ones, never do.
+void launch_lbe_step(dhit_box &b, const void *src, void *dst, double *sums_out, bool defer, PendingSums *pend);
+void launch_dugks_step(dhit_box &b, const void *src, void *dst, double *sums_out, bool defer, PendingSums *pend);
+void launch_dugks_fused(dhit_box &b, const void *src, void *dst, double *sums_out, bool defer, PendingSums *pend);
 // Blocks of the fused DUGKS launch for an n^3 box (and its tiling).
 int fused_dugks_blocks(const dhit_params &p, int *width, int *tiles_x, int *tiles_y, int *nz_chunk);
 // Work split of a box's fused DUGKS launch: tile width, tiling, z-chunk,
@@ -193,7 +210,7 @@ struct LbeSplit {
   int cells, threads;  // cells per thread, threads per block
 };
 void launch_lbe_batch(hipStream_t s, int method, int precision, const LbeSplit &w, const BatchBox *d_boxes, int nbox,
-                      int total_items, int grid);
+                      int total_items, int grid, const PendingSums &prev);
 int lbe_cells_per_thread(int n, int method, int precision);
 LbeSplit lbe_split(int n, int method, int precision);
 int lbe_items(int64_t ncell, const LbeSplit &s);
@@ -203,7 +220,7 @@ void lbe_table_entries(const dhit_box &b, BatchBox (&e)[2]);
 // stretched meshes, else all on unit cells); a single box is a table of one
 // entry.
 void launch_dugks_batch(hipStream_t s, int precision, int w, int max_n, const BatchBox *d_boxes, int nbox,
-                        int total_items, int grid, bool mesh);
+                        int total_items, int grid, bool mesh, const PendingSums &prev);
 // The two one-entry tables of a box (entry c steps from f[c] to f[1 - c]),
 // and a launch that writes two entries given by value to device memory.
 void fused_table_entries(const dhit_box &b, BatchBox (&e)[2]);
@@ -231,6 +248,10 @@ void gradient_compute(dhit_box &b, const double *d_u, double *d_grad);
 // the first-order Chapman-Enskog part f1 of the velocity gradient (device
 // fields: u [3][ncell], drho [ncell] or NULL, grad [9][ncell]).
 void launch_ce_init(dhit_box &b, const double *d_u, const double *d_drho, const double *d_grad, void *dst);
+
+// Ends a step of `nblocks` partials: in *pend for the next launch, or added up
+// by a launch of its own (see launch_lbe_step).
+void finish_step(dhit_box &b, const double *partials, int nblocks, double *sums_out, bool defer, PendingSums *pend);
 
 // Event bracket around one kernel launch when timing is enabled:
 //   TimedLaunch t(b, DHIT_K_LBE); hipLaunchKernelGGL(...); t.done();
