@@ -320,10 +320,10 @@ __device__ __forceinline__ void zface_half(const P &c, Real h, Real (&m)[4]) {
 //
 // Like the march on unit cells it is bound by the latency its two waves per
 // SIMD cannot cover (FP64) and by vector issue (FP32): 15-20% more
-// instructions than there (1,840 and 1,700 per plane and wave pair).  It took
+// instructions than there.  It took
 // the place of a transform pass and a face pass that rebuilt six faces of 19
-// populations per cell from some 700 cached loads: 128^3 FP64 1.04 -> 0.272 ms
-// a step, 97^3 FP32 0.132 -> 0.083 ms.
+// populations per cell from some 700 cached loads: 128^3 FP64 1.04 -> 0.237 ms
+// a step, 97^3 FP32 0.132 -> 0.069 ms (unit cells: 0.215 ms at 128^3).
 template <typename T>
 using constant_t = __attribute__((address_space(4))) T;
 template <typename Real, int W>
@@ -2083,7 +2083,7 @@ static int fused_slots(int precision, int w) {
 // planes; its launch lasts as long as one block's march, so the shorter
 // chunks whose items still fit one round are taken into the choice: at 32^3
 // (12 column tiles) FP64 chunks of 2 planes (192 items) ran 22.6 us a step
-// against 44.6 with 8 planes (48 items), at 48^3 3 planes (256 items) 26.9
+// (13.8 with the march's later changes) against 44.6 with 8 planes (48 items), at 48^3 3 planes (256 items) 26.9
 // against 42.6, at 64^3 in FP32 (512 slots) 6 planes 37.0 against 42.9.  Two
 // rounds of the shortest chunks lose again (32^3, 1 plane, 384 items: 30.7).
 int fused_balanced_chunk(int n, int tiles_xy, int slots) {

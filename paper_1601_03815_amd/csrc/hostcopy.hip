@@ -6,8 +6,9 @@
 // 128^3 box, where the link gives 56 GB/s.  Here several threads take chunks
 // in turn: a chunk goes over the link to the thread's pinned buffer while the
 // other threads copy theirs on: the moments of that box 6.0 -> 2.5 ms, its
-// vorticity 5.0 -> 1.8 ms (8 and 14 threads, and 4 MiB chunks, the same).  (Uploads stay plain copies: their source is
-// resident, they already run at 26 GB/s, and the same scheme gave no more.)
+// vorticity 5.0 -> 1.8 ms (8 and 14 threads, and 4 MiB chunks, the same).
+// (Uploads stay plain copies: their source is resident, they already run at
+// 26 GB/s, and the same scheme gave no more.)
 #include <algorithm>
 #include <atomic>
 #include <cstring>

@@ -40,10 +40,11 @@ constexpr int64_t kBgkRunMaxCells = 512000;
 // A small box stepped alone runs one cell per thread in blocks of
 // kSmallBlock threads, up to kSmallCells<Real> cells: its launch lasts as long
 // as one thread's chain of loads, collision and stores, and two cells in a
-// row, or fewer and larger blocks, only lengthen it.  Step of a 32^3 box, us,
-// against kRunCells in blocks of kBlock: FP64 MRT 6.8 (11.8), 48^3 12.6
-// (15.1), 52^3 14.8 (16.2), but 56^3 17.4 (16.6); FP32 7.0 (7.3), 36^3 8.1
-// (7.9).  Blocks of 64 threads: 32^3 7.0, 48^3 12.7, 52^3 15.7.
+// row, or fewer and larger blocks, only lengthen it.  Step of a 32^3 box, us
+// (with its finalisation launch), against kRunCells in blocks of kBlock:
+// FP64 MRT 6.8 (11.8), 48^3 12.6 (15.1), 52^3 14.8 (16.2), but 56^3 17.4
+// (16.6); FP32 7.0 (7.3), 36^3 8.1 (7.9).  Blocks of 64 threads: 32^3 7.0,
+// 48^3 12.7, 52^3 15.7.
 constexpr int kSmallBlock = 128;
 template <typename Real>
 constexpr int64_t kSmallCells = sizeof(Real) == 8 ? 150000 : 32768;
