@@ -880,6 +880,11 @@ __device__ __forceinline__ int fused_thread() {
 // lane l of each in turn): the march is bound by the interior wavefronts'
 // vector issue, and this one had a third of their work.  128^3 129.5 -> 124.2
 // us, 256^3 0.868 -> 0.846 ms.
+// In the second phase of a plane, after the barrier that follows the
+// publishing, the interior wavefronts issue before a halo one on the same SIMD,
+// which has less to do; up to that barrier, which all wait for, all are alike
+// (and above another block's second phase).  256^3 0.843 -> 0.818 ms, 160^3
+// 225 -> 219 us, 128^3 121.7 -> 119.8 us; the halo ones first, 0.832 ms.
 template <typename Real, int W, bool O32, bool Mesh, bool Halo>
 __device__ __forceinline__ void fused_tile(const global_t<Real> *__restrict__ ft, global_t<Real> *__restrict__ out, const StepParams &p,
                                            int bx, int by, int z0, int z1, Real *L, double (&v)[kNumSums],
@@ -1032,6 +1037,7 @@ __device__ __forceinline__ void fused_tile(const global_t<Real> *__restrict__ ft
       if constexpr (kCz[q] != 0) nxt[zslot(q)] = -(dtal * ((Real(-0.5 * kCz[q]) - h) * bq));
     });
     __syncthreads();
+    __builtin_amdgcn_s_setprio(Halo ? 0 : 2);
 
     // face between p-1 and p of a column (upper half from plane p, lower half
     // carried from plane p-1), and the lower half of the next one
@@ -1191,6 +1197,7 @@ __device__ __forceinline__ void fused_tile(const global_t<Real> *__restrict__ ft
     q2 ^= 1;
     q3 = q3 == 2 ? 0 : q3 + 1;
     __syncthreads();
+    __builtin_amdgcn_s_setprio(3);
     return true;
   };
   // two planes per turn, the two centres' arrays changing places: as one
@@ -1425,6 +1432,9 @@ __device__ __forceinline__ void publish_group(const Real (&f)[Group<G>::N], cons
 // with both last, 1.610 ms apart, 1.535 ms with the x-faces handed over
 // (128^3 217, 216, 214 us; 64^3 40.9, 39.3, 39.8 us); the z-faces handed to B's
 // halo wavefront 1.55 ms at 256^3 but 220 us at 128^3.
+// The interior wavefronts issue before a halo one on the same SIMD: 256^3 1.541
+// -> 1.515 ms, 64^3 37.6 -> 37.2 us (the halo ones first 1.590 ms; group B before
+// A 1.648 ms, A before B as without).
 template <typename Real, int W, int G, bool O32, bool Mesh, bool Halo>
 __device__ __forceinline__ void split_tile(const global_t<Real> *__restrict__ ft, global_t<Real> *__restrict__ out, const StepParams &p,
                                            int bx, int by, int z0, int z1, Real *L, double (&v)[kNumSums],
@@ -1436,6 +1446,7 @@ __device__ __forceinline__ void split_tile(const global_t<Real> *__restrict__ ft
   // column of the tile; B's wavefronts of a 32-wide tile are rotated by one, its
   // halo wavefront first
   const int c = tile_column<W>(G == 0 ? threadIdx.x : (threadIdx.x - (W == 32 ? 64 : 0)) % NT);
+  __builtin_amdgcn_s_setprio(Halo ? 0 : 2);
   const int tx = c % TX, ty = c / TX;
   const int x0 = bx * IX, y0 = by * IY;
   int gx = x0 - 1 + tx, gy = y0 - 1 + ty;
