@@ -143,11 +143,13 @@ __device__ __forceinline__ double wave_sum(double v) {
 
 // Sums of five doubles over a block of NW wavefronts: thread i < 5 returns
 // the total of v[i].  Deterministic: a fixed tree inside each wavefront, then
-// the wavefront totals in wavefront order (five lanes side by side).
+// the wavefront totals in the order of `wave`, the wavefront's place in the sum
+// (a kernel that gives its wavefronts changing roles passes the role, so that
+// the order does not change with them).
 template <int NW>
-__device__ __forceinline__ double block_sum5(double (&v)[kNumSums], double (*smem)[kNumSums]) {
+__device__ __forceinline__ double block_sum5(double (&v)[kNumSums], double (*smem)[kNumSums], int wave) {
   static_for<kNumSums>([&](auto i) { v[i] = wave_sum(v[i]); });
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63;
   if (lane == 0) {
     static_for<kNumSums>([&](auto i) { smem[wave][i] = v[i]; });
   }
@@ -159,6 +161,10 @@ __device__ __forceinline__ double block_sum5(double (&v)[kNumSums], double (*sme
     for (int w = 1; w < NW; ++w) s += smem[w][threadIdx.x];
   }
   return s;
+}
+template <int NW>
+__device__ __forceinline__ double block_sum5(double (&v)[kNumSums], double (*smem)[kNumSums]) {
+  return block_sum5<NW>(v, smem, threadIdx.x >> 6);
 }
 
 // Per-cell contributions to the five global sums, accumulated in FP64 from
@@ -209,12 +215,17 @@ __device__ __forceinline__ global_t<T> *to_global(T *p) {
 
 // Writes the block's five sums to partials laid out [5][nblocks], using
 // smem (at least one row of five doubles per wavefront of the block) for
-// the reduction.
+// the reduction (wave as in block_sum5).
+template <int NW>
+__device__ __forceinline__ void write_block_partials(double (&v)[kNumSums], double *partials, int nblocks, int block,
+                                                     double (*smem)[kNumSums], int wave) {
+  const double t = block_sum5<NW>(v, smem, wave);
+  if (threadIdx.x < kNumSums) to_global(partials)[(int64_t)threadIdx.x * nblocks + block] = t;
+}
 template <int NW>
 __device__ __forceinline__ void write_block_partials(double (&v)[kNumSums], double *partials, int nblocks, int block,
                                                      double (*smem)[kNumSums]) {
-  const double t = block_sum5<NW>(v, smem);
-  if (threadIdx.x < kNumSums) to_global(partials)[(int64_t)threadIdx.x * nblocks + block] = t;
+  write_block_partials<NW>(v, partials, nblocks, block, smem, threadIdx.x >> 6);
 }
 template <int NW = kWaves>
 __device__ __forceinline__ void write_block_partials(double (&v)[kNumSums], double *partials, int nblocks,

@@ -1306,7 +1306,10 @@ __global__ __launch_bounds__(Tile<W>::NT, kWavesPerSimd<Real>) void dugks_fused_
       else if constexpr (W == 32)
         march(std::true_type{});
     }
-    write_block_partials<Tile<W>::NT / 64>(v, d.partials, d.items, local, reinterpret_cast<double (*)[kNumSums]>(L));
+    // summed in the order of the wavefronts' rows: which wavefront has which rows
+    // depends on the block's number, which the extra block shifts
+    write_block_partials<Tile<W>::NT / 64>(v, d.partials, d.items, local, reinterpret_cast<double (*)[kNumSums]>(L),
+                                           fused_thread<W>() >> 6);
     __syncthreads();
   }
 }
