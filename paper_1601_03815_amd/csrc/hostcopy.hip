@@ -12,8 +12,10 @@
 #include <algorithm>
 #include <atomic>
 #include <cstring>
+#include <map>
 #include <memory>
 #include <mutex>
+#include <new>
 #include <system_error>
 #include <thread>
 #include <vector>
@@ -32,43 +34,66 @@ constexpr size_t kChunk = size_t(2) << 20;
 constexpr size_t kPlainBytes = size_t(4) << 20;
 
 struct Staging {
+  const int dev;        // the events belong to it: only its streams take them
   void *buf = nullptr;  // kCopyThreads chunks of pinned memory
   hipEvent_t done[kCopyThreads] = {};
+  explicit Staging(int d) : dev(d) {}
   ~Staging() {
     for (hipEvent_t e : done)
       if (e) (void)hipEventDestroy(e);
     if (buf) (void)hipHostFree(buf);
   }
+  bool allocate() {
+    if (hipHostMalloc(&buf, kCopyThreads * kChunk, hipHostMallocPortable) != hipSuccess) {
+      (void)hipGetLastError();
+      buf = nullptr;
+      return false;
+    }
+    // events are made on the current device
+    int was = dev;
+    if (hipGetDevice(&was) != hipSuccess || (was != dev && hipSetDevice(dev) != hipSuccess)) {
+      (void)hipGetLastError();
+      return false;
+    }
+    bool ok = true;
+    for (hipEvent_t &e : done)
+      if (ok && hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) {
+        (void)hipGetLastError();
+        e = nullptr;
+        ok = false;
+      }
+    if (was != dev && hipSetDevice(was) != hipSuccess) ok = false;
+    return ok;
+  }
 };
 
-// One idle set of buffers is kept for the next copy while boxes exist;
-// copies that run at the same time make sets of their own.
+// One idle set of buffers per device is kept for the next copy while boxes
+// exist; copies that run at the same time make sets of their own.
 std::mutex g_mu;
-std::unique_ptr<Staging> g_idle;
+std::map<int, std::unique_ptr<Staging>> g_idle;
 int g_boxes = 0;
 
-std::unique_ptr<Staging> take_staging() {
+std::unique_ptr<Staging> take_staging(int dev) {
   {
     std::lock_guard<std::mutex> lock(g_mu);
-    if (g_idle) return std::move(g_idle);
-  }
-  std::unique_ptr<Staging> s(new Staging());
-  if (hipHostMalloc(&s->buf, kCopyThreads * kChunk, hipHostMallocPortable) != hipSuccess) {
-    (void)hipGetLastError();
-    return nullptr;
-  }
-  for (hipEvent_t &e : s->done)
-    if (hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) {
-      (void)hipGetLastError();
-      e = nullptr;
-      return nullptr;
+    const auto it = g_idle.find(dev);
+    if (it != g_idle.end()) {
+      std::unique_ptr<Staging> s = std::move(it->second);
+      g_idle.erase(it);
+      return s;
     }
-  return s;
+  }
+  std::unique_ptr<Staging> s(new Staging(dev));
+  return s->allocate() ? std::move(s) : nullptr;
 }
 
 void give_staging(std::unique_ptr<Staging> s) {
   std::lock_guard<std::mutex> lock(g_mu);
-  if (g_boxes > 0 && !g_idle) g_idle = std::move(s);
+  try {
+    if (g_boxes > 0 && !g_idle.count(s->dev)) g_idle[s->dev] = std::move(s);
+  } catch (const std::bad_alloc &) {
+    // not kept
+  }
 }
 
 // Whether the host pointer is memory the runtime already has pinned (a plain
@@ -104,8 +129,9 @@ void copy_to_host(std::initializer_list<HostCopy> copies, hipStream_t s) {
   const unsigned cpus = std::thread::hardware_concurrency();
   const int threads = (int)std::min<size_t>(std::min<size_t>(kCopyThreads, cpus ? cpus : 1), chunks.size());
   std::unique_ptr<Staging> st;
-  int dev = 0;
-  if (total <= kPlainBytes || threads < 2 || pinned || hipGetDevice(&dev) != hipSuccess || !(st = take_staging())) {
+  hipDevice_t dev = 0;  // the stream's, which need not be the current one
+  if (total <= kPlainBytes || threads < 2 || pinned || hipStreamGetDevice(s, &dev) != hipSuccess ||
+      !(st = take_staging(dev))) {
     for (const HostCopy &c : copies)
       if (c.bytes) DHIT_HIP(hipMemcpyAsync(c.dst, c.src, c.bytes, hipMemcpyDeviceToHost, s));
     DHIT_HIP(hipStreamSynchronize(s));
@@ -114,7 +140,7 @@ void copy_to_host(std::initializer_list<HostCopy> copies, hipStream_t s) {
   std::atomic<size_t> next{0};
   std::atomic<int> error{(int)hipSuccess};
   auto work = [&](int w) {
-    hipError_t e = hipSetDevice(dev);
+    hipError_t e = w > 0 ? hipSetDevice(dev) : hipSuccess;  // 0 is the caller's thread
     char *buf = static_cast<char *>(st->buf) + w * kChunk;
     while (e == hipSuccess && error.load() == (int)hipSuccess) {
       const size_t k = next.fetch_add(1);
@@ -149,9 +175,9 @@ void box_made() {
 }
 
 void box_gone() {
-  std::unique_ptr<Staging> last;
+  std::map<int, std::unique_ptr<Staging>> last;
   std::lock_guard<std::mutex> lock(g_mu);
-  if (--g_boxes == 0) last = std::move(g_idle);
+  if (--g_boxes == 0) last.swap(g_idle);
 }
 
 }  // namespace dhit

@@ -1,0 +1,60 @@
+// Cases of the library's copies to the host on the stand-in runtime; argv[1]
+// names one.  Exit status 0: as it should be.
+#define FAKE_HIP_MAIN
+#include "fake_hip.hpp"
+
+#include <vector>
+
+#include "../paper_1601_03815_amd/csrc/runtime.hpp"
+
+static std::vector<char> pattern(size_t n, int seed) {
+  std::vector<char> v(n);
+  for (size_t i = 0; i < n; ++i) v[i] = (char)((i * 2654435761u + seed) >> 7);
+  return v;
+}
+
+// Copies n bytes on s and says whether they arrived.
+static bool copy_on(hipStream_t s, size_t n, int seed) {
+  const std::vector<char> src = pattern(n, seed);
+  std::vector<char> dst(n + 64, 0x55);
+  dhit::copy_to_host({{dst.data() + 8, src.data(), n}}, s);
+  for (size_t i = 0; i < dst.size(); ++i)
+    if (dst[i] != (i >= 8 && i < n + 8 ? src[i - 8] : 0x55)) return false;
+  return true;
+}
+
+#define CHECK(x)                                             \
+  do {                                                       \
+    if (!(x)) {                                              \
+      std::fprintf(stderr, "line %d: %s\n", __LINE__, #x);   \
+      return 1;                                              \
+    }                                                        \
+  } while (0)
+
+constexpr size_t kLarge = (size_t(9) << 20) + 40;
+
+// Boxes on two devices of one process, also when the stream's device is not
+// the current one; what is kept goes with the last box.
+static int two_devices() {
+  hipStream_t s[2] = {fake::stream(0), fake::stream(1)};
+  dhit::box_made();
+  dhit::box_made();
+  for (int k = 0; k < 6; ++k) {
+    const int d = (k / 2 + k) % 2;
+    CHECK(hipSetDevice(k < 4 ? d : 1 - d) == hipSuccess);
+    CHECK(copy_on(s[d], kLarge, k));
+    int now = -1;
+    CHECK(hipGetDevice(&now) == hipSuccess && now == (k < 4 ? d : 1 - d));
+  }
+  CHECK(fake::pinned.size() <= 2);
+  dhit::box_gone();
+  dhit::box_gone();
+  CHECK(fake::pinned.empty() && fake::live_events == 0);
+  return 0;
+}
+
+int main(int argc, char **argv) {
+  const std::string c = argc > 1 ? argv[1] : "";
+  if (c == "two_devices") return two_devices();
+  return 2;
+}
