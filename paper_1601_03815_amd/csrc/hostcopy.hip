@@ -96,15 +96,15 @@ void give_staging(std::unique_ptr<Staging> s) {
   }
 }
 
-// Whether the host pointer is memory the runtime already has pinned (a plain
-// copy is then one transfer).
-bool is_pinned(const void *p) {
+// Whether the destination is memory the runtime knows: pinned (a plain copy is
+// then one transfer), managed, or a device's, which the host must not write.
+bool is_known(const void *p) {
   hipPointerAttribute_t a;
   if (hipPointerGetAttributes(&a, p) != hipSuccess) {
     (void)hipGetLastError();
     return false;
   }
-  return a.type == hipMemoryTypeHost || a.type == hipMemoryTypeManaged;
+  return a.type != hipMemoryTypeUnregistered;
 }
 
 }  // namespace
@@ -112,11 +112,11 @@ bool is_pinned(const void *p) {
 void copy_to_host(std::initializer_list<HostCopy> copies, hipStream_t s) {
   std::vector<HostCopy> chunks;
   size_t total = 0;
-  bool pinned = false;
+  bool known = false;
   for (const HostCopy &c : copies) {
     if (c.bytes == 0) continue;
     total += c.bytes;
-    pinned = pinned || is_pinned(c.dst);
+    known = known || is_known(c.dst);
     char *dst = static_cast<char *>(c.dst);
     const char *src = static_cast<const char *>(c.src);
     const size_t lead = reinterpret_cast<uintptr_t>(dst) % kChunk;
@@ -130,7 +130,7 @@ void copy_to_host(std::initializer_list<HostCopy> copies, hipStream_t s) {
   const int threads = (int)std::min<size_t>(std::min<size_t>(kCopyThreads, cpus ? cpus : 1), chunks.size());
   std::unique_ptr<Staging> st;
   hipDevice_t dev = 0;  // the stream's, which need not be the current one
-  if (total <= kPlainBytes || threads < 2 || pinned || hipStreamGetDevice(s, &dev) != hipSuccess ||
+  if (total <= kPlainBytes || threads < 2 || known || hipStreamGetDevice(s, &dev) != hipSuccess ||
       !(st = take_staging(dev))) {
     for (const HostCopy &c : copies)
       if (c.bytes) DHIT_HIP(hipMemcpyAsync(c.dst, c.src, c.bytes, hipMemcpyDeviceToHost, s));

@@ -53,8 +53,26 @@ static int two_devices() {
   return 0;
 }
 
+// Memory the runtime knows is left to the runtime, whatever its kind: device
+// memory, which the host may not touch, among it.
+static int known_destinations() {
+  dhit::box_made();
+  for (hipMemoryType kind : {hipMemoryTypeHost, hipMemoryTypeDevice, hipMemoryTypeManaged, hipMemoryTypeUnified}) {
+    const std::vector<char> src = pattern(kLarge, 3);
+    std::vector<char> dst(kLarge);
+    fake::kinds[dst.data()] = kind;
+    fake::copies = 0;
+    dhit::copy_to_host({{dst.data(), src.data(), kLarge}}, fake::stream(0));
+    CHECK(fake::copies == 1 && dst == src);
+    fake::kinds.clear();
+  }
+  dhit::box_gone();
+  return 0;
+}
+
 int main(int argc, char **argv) {
   const std::string c = argc > 1 ? argv[1] : "";
   if (c == "two_devices") return two_devices();
+  if (c == "known_destinations") return known_destinations();
   return 2;
 }
