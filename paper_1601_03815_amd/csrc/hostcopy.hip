@@ -130,7 +130,8 @@ void copy_to_host(std::initializer_list<HostCopy> copies, hipStream_t s) {
   const int threads = (int)std::min<size_t>(std::min<size_t>(kCopyThreads, cpus ? cpus : 1), chunks.size());
   std::unique_ptr<Staging> st;
   hipDevice_t dev = 0;  // the stream's, which need not be the current one
-  if (total <= kPlainBytes || threads < 2 || known || hipStreamGetDevice(s, &dev) != hipSuccess ||
+  // (hipStreamPerThread would be another stream in each of the threads)
+  if (total <= kPlainBytes || threads < 2 || known || s == hipStreamPerThread || hipStreamGetDevice(s, &dev) != hipSuccess ||
       !(st = take_staging(dev))) {
     for (const HostCopy &c : copies)
       if (c.bytes) DHIT_HIP(hipMemcpyAsync(c.dst, c.src, c.bytes, hipMemcpyDeviceToHost, s));

@@ -70,9 +70,22 @@ static int known_destinations() {
   return 0;
 }
 
+// hipStreamPerThread names another stream in every thread: only the caller's is
+// ordered after the box's work.
+static int per_thread_stream() {
+  dhit::box_made();
+  for (int k = 0; k < 3; ++k) {
+    CHECK(copy_on(hipStreamPerThread, kLarge, k));
+    CHECK(fake::foreign_per_thread == 0);
+  }
+  dhit::box_gone();
+  return 0;
+}
+
 int main(int argc, char **argv) {
   const std::string c = argc > 1 ? argv[1] : "";
   if (c == "two_devices") return two_devices();
   if (c == "known_destinations") return known_destinations();
+  if (c == "per_thread_stream") return per_thread_stream();
   return 2;
 }
