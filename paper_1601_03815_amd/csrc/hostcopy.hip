@@ -16,7 +16,6 @@
 #include <memory>
 #include <mutex>
 #include <new>
-#include <system_error>
 #include <thread>
 #include <vector>
 
@@ -158,8 +157,9 @@ void copy_to_host(std::initializer_list<HostCopy> copies, hipStream_t s) {
   pool.reserve(threads - 1);
   try {
     for (int w = 1; w < threads; ++w) pool.emplace_back(work, w);
-  } catch (const std::system_error &) {
-    // fewer threads: those that started, and this one, take every chunk
+  } catch (...) {
+    // no thread or no memory for one: those that started, and this one, take
+    // every chunk
   }
   work(0);
   for (std::thread &t : pool) t.join();

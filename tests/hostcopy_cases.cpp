@@ -3,9 +3,21 @@
 #define FAKE_HIP_MAIN
 #include "fake_hip.hpp"
 
+#include <new>
 #include <vector>
 
 #include "../paper_1601_03815_amd/csrc/runtime.hpp"
+
+// Allocations of the main thread until one fails (< 0: none does).
+static thread_local int allocations_left = -1;
+void *operator new(size_t n) {
+  if (allocations_left == 0) throw std::bad_alloc();
+  if (allocations_left > 0) --allocations_left;
+  if (void *p = std::malloc(n ? n : 1)) return p;
+  throw std::bad_alloc();
+}
+void operator delete(void *p) noexcept { std::free(p); }
+void operator delete(void *p, size_t) noexcept { std::free(p); }
 
 static std::vector<char> pattern(size_t n, int seed) {
   std::vector<char> v(n);
@@ -82,10 +94,40 @@ static int per_thread_stream() {
   return 0;
 }
 
+// Every allocation of a copy fails once: the copy is whole, or the caller gets
+// the exception; the program goes on.
+static int out_of_memory() {
+  const std::vector<char> src = pattern(kLarge, 5);
+  hipStream_t s = fake::stream(0);
+  dhit::box_made();
+  int thrown = 0, whole = 0;
+  for (int k = 0; whole < 3 && k < 1000; ++k) {
+    std::vector<char> dst(kLarge);
+    bool failed = false;
+    allocations_left = k;
+    try {
+      dhit::copy_to_host({{dst.data(), src.data(), kLarge}}, s);
+    } catch (const std::bad_alloc &) {
+      failed = true;
+    }
+    whole += !failed && allocations_left > 0;  // nothing was left to fail
+    allocations_left = -1;
+    if (failed)
+      ++thrown;
+    else
+      CHECK(dst == src);
+  }
+  CHECK(whole == 3 && thrown > 0);
+  dhit::box_gone();
+  CHECK(fake::pinned.empty() && fake::live_events == 0);
+  return 0;
+}
+
 int main(int argc, char **argv) {
   const std::string c = argc > 1 ? argv[1] : "";
   if (c == "two_devices") return two_devices();
   if (c == "known_destinations") return known_destinations();
   if (c == "per_thread_stream") return per_thread_stream();
+  if (c == "out_of_memory") return out_of_memory();
   return 2;
 }
