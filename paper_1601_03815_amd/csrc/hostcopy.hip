@@ -67,9 +67,11 @@ struct Staging {
 };
 
 // One idle set of buffers per device is kept for the next copy while boxes
-// exist; copies that run at the same time make sets of their own.
+// exist; copies that run at the same time make sets of their own.  A program
+// may end with boxes alive: the map is never destroyed, as the runtime can have
+// ended before the library's static data would be.
 std::mutex g_mu;
-std::map<int, std::unique_ptr<Staging>> g_idle;
+auto &g_idle = *new std::map<int, std::unique_ptr<Staging>>();
 int g_boxes = 0;
 
 std::unique_ptr<Staging> take_staging(int dev) {

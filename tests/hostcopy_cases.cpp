@@ -123,11 +123,21 @@ static int out_of_memory() {
   return 0;
 }
 
+// A program that ends with a box alive: the runtime may have ended before the
+// library's own data does.
+static int box_at_exit() {
+  dhit::box_made();
+  CHECK(copy_on(fake::stream(0), kLarge, 1));
+  std::atexit([] { fake::ended = true; });
+  return 0;
+}
+
 int main(int argc, char **argv) {
   const std::string c = argc > 1 ? argv[1] : "";
   if (c == "two_devices") return two_devices();
   if (c == "known_destinations") return known_destinations();
   if (c == "per_thread_stream") return per_thread_stream();
   if (c == "out_of_memory") return out_of_memory();
+  if (c == "box_at_exit") return box_at_exit();
   return 2;
 }
