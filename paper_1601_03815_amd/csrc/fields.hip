@@ -197,9 +197,9 @@ __global__ __launch_bounds__(kBlock) void finalize_sums_wide_kernel(const double
 
 void launch_finalize_sums(dhit_box &b, const double *partials, int nblocks, double *out) {
   TimedLaunch t(b, DHIT_K_FINALIZE);
-  const int g = (nblocks + kFinalizePer - 1) / kFinalizePer;
-  if (g > 1 && b.reduce_level && g <= kFinalizeLevels)
-    hipLaunchKernelGGL(finalize_sums_wide_kernel, dim3(g), dim3(kBlock), 0, b.stream, partials, nblocks, kFinalizePer,
+  const int per = finalize_per(nblocks), g = (nblocks + per - 1) / per;
+  if (g > 1 && b.reduce_level)
+    hipLaunchKernelGGL(finalize_sums_wide_kernel, dim3(g), dim3(kBlock), 0, b.stream, partials, nblocks, per,
                        b.reduce_level, out);
   else
     hipLaunchKernelGGL(finalize_sums_kernel, dim3(1), dim3(1024), 0, b.stream, partials, nblocks, out);

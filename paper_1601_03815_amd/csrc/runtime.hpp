@@ -44,13 +44,19 @@ struct StepParams {
 };
 
 constexpr int kHistoryCap = 4096;
-// Blocks of the wide finalisation of the per-step sums at most (each sums
-// 4096 block partials); its work space is kFinalizeLevels * 5 doubles and a
-// counter that must be zero before the first launch.
+// Blocks of the wide finalisation of the per-step sums at most; its work space
+// is kFinalizeLevels * 5 doubles and a counter that must be zero before the
+// first launch.
 constexpr int kFinalizeLevels = 64;
-// Partials one block of the wide finalisation sums.
+// Block partials each of them sums at least (a launch of fewer is one block).
 constexpr int kFinalizePer = 4096;
 constexpr int kFinalizeDoubles = kFinalizeLevels * 5 + 8;
+// Partials each of them sums when there are `nblocks`: more than 64 x 4096 (one
+// cell per thread from n = 407 on) make the slices longer; one block alone takes
+// 423 us for the 21 MB of a 512^3 box, the 64 blocks 31 us (640^3: 802 and 49 us).
+constexpr int finalize_per(int nblocks) {
+  return nblocks <= kFinalizeLevels * kFinalizePer ? kFinalizePer : (nblocks + kFinalizeLevels - 1) / kFinalizeLevels;
+}
 
 // Device tables of a stretched DUGKS mesh (set_mesh): the cell widths [3][n]
 // in double (weights of the sums), then the march's coefficients
