@@ -549,17 +549,29 @@ static int32_t step_common(dhit_box *b, int32_t nsteps, bool lbe) {
     const bool is_lbe = b->p.method != DHIT_DUGKS;
     if (is_lbe != lbe) fail(DHIT_EMETHOD, lbe ? "step_lbe called on a DUGKS box" : "step_dugks called on an LBE box");
     dhit::PendingSums pend{};
-    for (int32_t s = 0; s < nsteps; ++s) {
-      const bool defer = s + 1 < nsteps;
-      double *slot = b->hist + (b->steps % dhit::kHistoryCap) * 5;
-      const void *src = b->f[b->cur];
-      void *dst = b->f[1 - b->cur];
-      if (lbe)
-        dhit::launch_lbe_step(*b, src, dst, slot, defer, &pend);
-      else
-        dhit::launch_dugks_step(*b, src, dst, slot, defer, &pend);
-      b->cur = 1 - b->cur;
-      b->steps++;
+    try {
+      for (int32_t s = 0; s < nsteps; ++s) {
+        const bool defer = s + 1 < nsteps;
+        double *slot = b->hist + (b->steps % dhit::kHistoryCap) * 5;
+        const void *src = b->f[b->cur];
+        void *dst = b->f[1 - b->cur];
+        if (lbe)
+          dhit::launch_lbe_step(*b, src, dst, slot, defer, &pend);
+        else
+          dhit::launch_dugks_step(*b, src, dst, slot, defer, &pend);
+        b->cur = 1 - b->cur;
+        b->steps++;
+      }
+    } catch (...) {
+      // the last whole step counts as taken: its sums, which the failed launch
+      // would have added up, belong to the history
+      if (pend.nblocks > 0) {
+        try {
+          dhit::launch_finalize_sums(*b, pend.partials, pend.nblocks, pend.out);
+        } catch (...) {  // the first error is reported
+        }
+      }
+      throw;
     }
     return DHIT_OK;
   });

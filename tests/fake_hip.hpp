@@ -26,6 +26,7 @@ inline std::map<const void *, hipMemoryType> kinds;  // destinations that are no
 inline std::map<void *, int> pinned;                 // live pinned allocations
 inline std::atomic<int> live_events{0}, copies{0}, foreign_per_thread{0}, failing_malloc{0};
 inline std::thread::id owner = std::this_thread::get_id();
+inline int copies_until_failure = -1;                // synchronous copies (< 0: none fails)
 inline bool ended = false;                           // set at exit: no call may follow
 
 inline void alive() {
@@ -94,6 +95,25 @@ hipError_t hipPointerGetAttributes(hipPointerAttribute_t *a, const void *p) {
   std::lock_guard<std::mutex> l(fake::mu);
   const auto it = fake::kinds.find(p);
   a->type = it == fake::kinds.end() ? hipMemoryTypeUnregistered : it->second;
+  return hipSuccess;
+}
+hipError_t hipMalloc(void **p, size_t n) {
+  fake::alive();
+  *p = std::calloc(1, n);
+  return hipSuccess;
+}
+hipError_t hipFree(void *p) {
+  fake::alive();
+  std::free(p);
+  return hipSuccess;
+}
+hipError_t hipMemset(void *p, int v, size_t n) { std::memset(p, v, n); return hipSuccess; }
+hipError_t hipMemsetAsync(void *p, int v, size_t n, hipStream_t) { std::memset(p, v, n); return hipSuccess; }
+hipError_t hipMemcpy(void *dst, const void *src, size_t n, hipMemcpyKind) {
+  fake::alive();
+  if (fake::copies_until_failure == 0) return hipErrorUnknown;
+  if (fake::copies_until_failure > 0) --fake::copies_until_failure;
+  std::memcpy(dst, src, n);
   return hipSuccess;
 }
 hipError_t hipMemcpyAsync(void *dst, const void *src, size_t n, hipMemcpyKind, hipStream_t s) {
