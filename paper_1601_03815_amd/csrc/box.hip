@@ -440,13 +440,25 @@ int32_t set_mesh(dhit_box *b, const double *widths) {
         fail(DHIT_ENOMEM, "cannot allocate the step table");
       b->own_step_table = true;
     }
-    const bool had = b->mesh != nullptr;
-    if (!had && hipMalloc(&b->mesh, img.size()) != hipSuccess) fail(DHIT_ENOMEM, "cannot allocate mesh tables");
-    DHIT_HIP(hipMemcpy(b->mesh, img.data(), img.size(), hipMemcpyHostToDevice));
-    if (!had) {  // the step's tables name the mesh
+    if (b->mesh) {  // the step's tables name it
+      DHIT_HIP(hipMemcpy(b->mesh, img.data(), img.size(), hipMemcpyHostToDevice));
+      return DHIT_OK;
+    }
+    // the box has a mesh (and runs the kernel that reads it) only once its tables
+    // and the step's that name them are whole
+    if (hipMalloc(&b->mesh, img.size()) != hipSuccess) {
+      b->mesh = nullptr;
+      fail(DHIT_ENOMEM, "cannot allocate mesh tables");
+    }
+    try {
+      DHIT_HIP(hipMemcpy(b->mesh, img.data(), img.size(), hipMemcpyHostToDevice));
       dhit::BatchBox e[2];
       dhit::fused_table_entries(*b, e);
       DHIT_HIP(hipMemcpy(b->step_table, e, sizeof(e), hipMemcpyHostToDevice));
+    } catch (...) {
+      (void)hipFree(b->mesh);
+      b->mesh = nullptr;
+      throw;
     }
     return DHIT_OK;
   });

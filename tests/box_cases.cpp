@@ -85,8 +85,43 @@ static int failing_launch() {
   return 0;
 }
 
+// A copy that fails in set_mesh: whatever kernel the box's next step chooses
+// (b->mesh) finds the tables that kernel reads in the step's table.
+static int failing_mesh() {
+  const int n = 8;
+  const std::vector<double> w(3 * n, 1.0), w2(3 * n, 1.25);
+  for (int variant : {DHIT_VARIANT_DEFAULT, DHIT_VARIANT_TWO_PASS})
+    for (bool stretched : {false, true})
+      for (int fails = 0; fails < 3; ++fails) {
+        dhit_params p;
+        CHECK(default_params(n, DHIT_DUGKS, DHIT_FP64, 0.01, &p) == DHIT_OK);
+        p.variant = variant;
+        dhit_box *b = nullptr;
+        CHECK(create_box(&p, &b) == DHIT_OK);
+        if (stretched) CHECK(set_mesh(b, w.data()) == DHIT_OK);
+        auto whole = [&] {
+          if (!b->mesh) return true;
+          for (int e = 0; e < 2; ++e)
+            if (b->step_table[e].mesh_width != b->mesh || b->step_table[e].mesh_coef != b->mesh + 3 * n) return false;
+          return true;
+        };
+        fake::copies_until_failure = fails;
+        const int32_t st = set_mesh(b, w2.data());
+        const bool ran_out = fake::copies_until_failure == 0;
+        fake::copies_until_failure = -1;
+        CHECK(st == DHIT_OK || (st == DHIT_EDEVICE && ran_out));
+        CHECK(whole() && (st == DHIT_OK || (b->mesh != nullptr) == stretched));
+        CHECK(set_mesh(b, w2.data()) == DHIT_OK && b->mesh && whole() && b->mesh[0] == 1.25);
+        CHECK(set_mesh(b, nullptr) == DHIT_OK && !b->mesh);
+        CHECK(set_mesh(b, w.data()) == DHIT_OK && b->mesh && whole());
+        destroy_box(b);
+      }
+  return 0;
+}
+
 int main(int argc, char **argv) {
   const std::string c = argc > 1 ? argv[1] : "";
   if (c == "failing_launch") return failing_launch();
+  if (c == "failing_mesh") return failing_mesh();
   return 2;
 }

@@ -21,7 +21,7 @@ def program(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("case", ["failing_launch"])
+@pytest.mark.parametrize("case", ["failing_launch", "failing_mesh"])
 def test_box_on_errors(program, case):
     r = subprocess.run([program, case], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0, (r.returncode, r.stderr)
