@@ -133,7 +133,7 @@ int64_t box_bytes(const dhit_params *p);
 /* Device bytes of a box's spectrum work space (energy_spectrum,
  * vorticity, initial_pressure, and the DUGKS init_consistent allocate it on
  * their first call and keep it until destroy_box): its arrays plus the work
- * areas of its three hipFFT plans, queried from hipFFT for this n (plans made
+ * area its two hipFFT plans share, queried from hipFFT for this n (plans made
  * without allocation).  For schedulers that admit boxes by HBM budget and
  * take diagnostics before releasing them.  A negative status on error. */
 int64_t spectrum_bytes(const dhit_params *p);

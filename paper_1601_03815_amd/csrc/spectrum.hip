@@ -4,6 +4,7 @@
 //      (exact integer sums, so E(k) is the same bits on every run)
 //   -> spectral derivatives i kappa_a u_hat_a (inverse transforms)
 //   -> <(d_a u_a)^m>, m = 2, 3, 4 -> K, eps, S, F.
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <vector>
@@ -17,19 +18,22 @@ struct SpectrumWork {
   int n = 0;
   int nshell = 0;
   int64_t nhalf = 0;  // modes of one real-to-complex transform, n*n*(n/2+1)
-  double *u = nullptr;                   // three fields
+  double *u = nullptr;                   // three fields (room for three half spectra, see gradient_compute)
   hipfftDoubleComplex *uh = nullptr;     // their transforms
-  hipfftDoubleComplex *tmp = nullptr;    // one more half spectrum (pressure, gradient; made when first needed)
+  hipfftDoubleComplex *tmp = nullptr;    // one more half spectrum (pressure; made when first needed)
   // what energy_spectrum brings to the host, in one piece: the shells' digit
   // sums [2][kShellParts][nshell] of E and kappa^2-weighted E, the power sums
   // of the three derivatives [3][5] (doubles), and a word that is set when a
   // shell term is out of range or not finite
   unsigned long long *result = nullptr;
   double *partials = nullptr;  // [3][5][kPowerBlocks]
-  // real-to-complex of three fields; complex-to-real of three, and of one
-  // (each made when first needed)
-  hipfftHandle fwd = 0, inv3 = 0, inv1 = 0;
-  bool have_fwd = false, have_inv3 = false, have_inv1 = false;
+  // real-to-complex and complex-to-real of three fields, for everything done
+  // here (with a plan of its own for one field, the first spectrum after a
+  // pressure took 2.4 instead of 0.12 ms at 64^3), and the work area they share: a
+  // box's transforms run one after the other (with an area each, and one more
+  // plan, odd sizes took 280 instead of 152 bytes per cell)
+  hipfftHandle fwd = 0, inv = 0;
+  void *area = nullptr;
 };
 constexpr int kPowerBlocks = 1024;
 
@@ -209,8 +213,9 @@ __global__ __launch_bounds__(256) void pressure_source_kernel(const hipfftDouble
   }
 }
 
-// acc <- scale acc / |k|^2 (full integer |k|^2; the k = 0 mode set to 0).
-__global__ __launch_bounds__(256) void inverse_laplacian_kernel(hipfftDoubleComplex *__restrict__ acc, int n,
+// out = scale acc / |k|^2 (full integer |k|^2; the k = 0 mode set to 0).
+__global__ __launch_bounds__(256) void inverse_laplacian_kernel(const hipfftDoubleComplex *__restrict__ acc,
+                                                                hipfftDoubleComplex *__restrict__ out, int n,
                                                                 int64_t nhalf, double scale) {
   const int64_t m = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (m >= nhalf) return;
@@ -219,8 +224,7 @@ __global__ __launch_bounds__(256) void inverse_laplacian_kernel(hipfftDoubleComp
   const int kx = (int)(m % nxh), ky = signed_k((int)(r % n), n), kz = signed_k((int)(r / n), n);
   const int k2 = kx * kx + ky * ky + kz * kz;
   const double f = k2 == 0 ? 0.0 : scale / (double)k2;
-  acc[m].x *= f;
-  acc[m].y *= f;
+  out[m] = make_double2(acc[m].x * f, acc[m].y * f);
 }
 
 // Sums of d^2, d^3, d^4 of three real fields scaled by `scale` (field
@@ -254,96 +258,94 @@ __global__ __launch_bounds__(kBlock) void power_totals_kernel(const double *__re
 static size_t shell_words(int nshell) { return 2 * kShellParts * (size_t)nshell; }
 static size_t result_words(int nshell) { return shell_words(nshell) + 15 + 1; }
 
-static hipfftResult plan_of(hipfftHandle *h, int n, bool forward, int batch) {
+// Makes one of the two plans without a work area; *need = the bytes it needs.
+static void make_plan(hipfftHandle *h, int n, bool forward, size_t *need) {
   int dims[3] = {n, n, n};
   const int ncell = n * n * n, nhalf = n * n * (n / 2 + 1);
-  return forward ? hipfftPlanMany(h, 3, dims, nullptr, 1, ncell, nullptr, 1, nhalf, HIPFFT_D2Z, batch)
-                 : hipfftPlanMany(h, 3, dims, nullptr, 1, nhalf, nullptr, 1, ncell, HIPFFT_Z2D, batch);
+  hipfftHandle p = 0;
+  DHIT_FFT(hipfftCreate(&p));
+  *h = p;
+  DHIT_FFT(hipfftSetAutoAllocation(p, 0));
+  DHIT_FFT(forward ? hipfftMakePlanMany(p, 3, dims, nullptr, 1, ncell, nullptr, 1, nhalf, HIPFFT_D2Z, 3, need)
+                   : hipfftMakePlanMany(p, 3, dims, nullptr, 1, nhalf, nullptr, 1, ncell, HIPFFT_Z2D, 3, need));
 }
 
-static void ensure_work(dhit_box &b) {
-  if (!b.spec) {
-    SpectrumWork *w = new SpectrumWork();
-    b.spec = w;
-    const int n = b.n;
-    w->n = n;
-    w->nhalf = (int64_t)n * n * (n / 2 + 1);
-    w->nshell = (int)std::floor(std::sqrt(3.0) * (n / 2 + 1)) + 2;
-    if (hipMalloc(&w->u, 3 * b.ncell * sizeof(double)) != hipSuccess ||
-        hipMalloc(&w->uh, 3 * w->nhalf * sizeof(hipfftDoubleComplex)) != hipSuccess ||
-        hipMalloc(&w->result, result_words(w->nshell) * sizeof(unsigned long long)) != hipSuccess ||
-        hipMalloc(&w->partials, 3 * 5 * kPowerBlocks * sizeof(double)) != hipSuccess)
-      throw Error(DHIT_ENOMEM, "cannot allocate spectrum work space");
-    DHIT_FFT(plan_of(&w->fwd, n, true, 3));
-    w->have_fwd = true;
-  }
-  DHIT_FFT(hipfftSetStream(b.spec->fwd, b.stream));
-}
-
-// The inverse transform of three fields.
-static hipfftHandle inverse3(dhit_box &b) {
-  SpectrumWork &w = *b.spec;
-  if (!w.have_inv3) {
-    DHIT_FFT(plan_of(&w.inv3, b.n, false, 3));
-    w.have_inv3 = true;
-  }
-  DHIT_FFT(hipfftSetStream(w.inv3, b.stream));
-  return w.inv3;
-}
-
-// The inverse transform of one field, and the half spectrum it starts from.
-static hipfftHandle inverse1(dhit_box &b) {
-  SpectrumWork &w = *b.spec;
-  if (!w.tmp && hipMalloc(&w.tmp, w.nhalf * sizeof(hipfftDoubleComplex)) != hipSuccess) {
-    w.tmp = nullptr;
-    throw Error(DHIT_ENOMEM, "cannot allocate spectrum work space");
-  }
-  if (!w.have_inv1) {
-    DHIT_FFT(plan_of(&w.inv1, b.n, false, 1));
-    w.have_inv1 = true;
-  }
-  DHIT_FFT(hipfftSetStream(w.inv1, b.stream));
-  return w.inv1;
-}
-
-// Device bytes of the spectrum work space of an n^3 box: the arrays of
-// ensure_work and inverse1 and the work areas of its three hipFFT plans (made
-// here with automatic allocation off, so nothing is allocated).
-int64_t spectrum_work_bytes(int n) {
-  const int64_t ncell = (int64_t)n * n * n, nhalf = (int64_t)n * n * (n / 2 + 1);
-  const int64_t nshell = (int64_t)std::floor(std::sqrt(3.0) * (n / 2 + 1)) + 2;
-  int64_t bytes = 3 * ncell * (int64_t)sizeof(double) + 4 * nhalf * (int64_t)sizeof(hipfftDoubleComplex) +
-                  (int64_t)(result_words((int)nshell) * sizeof(unsigned long long)) +
-                  3 * 5 * kPowerBlocks * (int64_t)sizeof(double);
-  int dims[3] = {n, n, n};
-  for (int plan = 0; plan < 3; ++plan) {
-    hipfftHandle h = 0;
-    DHIT_FFT(hipfftCreate(&h));
-    size_t work = 0;
-    hipfftResult r = hipfftSetAutoAllocation(h, 0);
-    if (r == HIPFFT_SUCCESS)
-      r = plan == 0 ? hipfftMakePlanMany(h, 3, dims, nullptr, 1, (int)ncell, nullptr, 1, (int)nhalf, HIPFFT_D2Z, 3, &work)
-                    : hipfftMakePlanMany(h, 3, dims, nullptr, 1, (int)nhalf, nullptr, 1, (int)ncell, HIPFFT_Z2D,
-                                         plan == 1 ? 3 : 1, &work);
-    hipfftDestroy(h);
-    if (r != HIPFFT_SUCCESS) throw Error(DHIT_EDEVICE, "hipfftMakePlanMany failed, code " + std::to_string((int)r));
-    bytes += (int64_t)work;
-  }
-  return bytes;
-}
-
-void spectrum_free(dhit_box &b) {
-  SpectrumWork *w = b.spec;
-  if (!w) return;
-  if (w->have_fwd) hipfftDestroy(w->fwd);
-  if (w->have_inv3) hipfftDestroy(w->inv3);
-  if (w->have_inv1) hipfftDestroy(w->inv1);
+static void work_free(SpectrumWork *w) {
+  if (w->fwd) hipfftDestroy(w->fwd);
+  if (w->inv) hipfftDestroy(w->inv);
+  if (w->area) (void)hipFree(w->area);
   if (w->u) (void)hipFree(w->u);
   if (w->uh) (void)hipFree(w->uh);
   if (w->tmp) (void)hipFree(w->tmp);
   if (w->result) (void)hipFree(w->result);
   if (w->partials) (void)hipFree(w->partials);
   delete w;
+}
+
+template <typename T>
+static void allocate(T **p, size_t bytes) {
+  if (hipMalloc(p, bytes) == hipSuccess) return;
+  *p = nullptr;
+  throw Error(DHIT_ENOMEM, "cannot allocate spectrum work space");
+}
+
+static int shells_of(int n) { return (int)std::floor(std::sqrt(3.0) * (n / 2 + 1)) + 2; }
+
+static void ensure_work(dhit_box &b) {
+  if (!b.spec) {
+    SpectrumWork *w = new SpectrumWork();
+    try {
+      const int n = b.n;
+      w->n = n;
+      w->nhalf = (int64_t)n * n * (n / 2 + 1);
+      w->nshell = shells_of(n);
+      const size_t three = 3 * (size_t)w->nhalf * sizeof(hipfftDoubleComplex);
+      allocate(&w->u, three);
+      allocate(&w->uh, three);
+      allocate(&w->result, result_words(w->nshell) * sizeof(unsigned long long));
+      allocate(&w->partials, 3 * 5 * kPowerBlocks * sizeof(double));
+      size_t need_f = 0, need_i = 0;
+      make_plan(&w->fwd, n, true, &need_f);
+      make_plan(&w->inv, n, false, &need_i);
+      const size_t need = std::max(need_f, need_i);
+      if (need > 0) {
+        allocate(&w->area, need);
+        DHIT_FFT(hipfftSetWorkArea(w->fwd, w->area));
+        DHIT_FFT(hipfftSetWorkArea(w->inv, w->area));
+      }
+    } catch (...) {
+      work_free(w);
+      throw;
+    }
+    b.spec = w;
+  }
+  DHIT_FFT(hipfftSetStream(b.spec->fwd, b.stream));
+  DHIT_FFT(hipfftSetStream(b.spec->inv, b.stream));
+}
+
+// Device bytes of the spectrum work space of an n^3 box: the arrays of
+// ensure_work and pressure_compute and the plans' work area (the plans are made
+// here to ask; nothing is allocated).
+int64_t spectrum_work_bytes(int n) {
+  const int64_t nhalf = (int64_t)n * n * (n / 2 + 1);
+  size_t need[2] = {0, 0};
+  for (int forward = 0; forward < 2; ++forward) {
+    hipfftHandle h = 0;
+    try {
+      make_plan(&h, n, forward != 0, &need[forward]);
+    } catch (...) {
+      if (h) hipfftDestroy(h);
+      throw;
+    }
+    hipfftDestroy(h);
+  }
+  return 7 * nhalf * (int64_t)sizeof(hipfftDoubleComplex) +
+         (int64_t)(result_words(shells_of(n)) * sizeof(unsigned long long)) +
+         3 * 5 * kPowerBlocks * (int64_t)sizeof(double) + (int64_t)std::max(need[0], need[1]);
+}
+
+void spectrum_free(dhit_box &b) {
+  if (b.spec) work_free(b.spec);
   b.spec = nullptr;
 }
 
@@ -351,7 +353,6 @@ void spectrum_compute(dhit_box &b, double *E_host, int kmax, double *stats_host)
   ensure_work(b);
   SpectrumWork &w = *b.spec;
   const int n = b.n;
-  const hipfftHandle inv = inverse3(b);
   launch_velocity(b, b.f[b.cur], w.u);
   DHIT_FFT(hipfftExecD2Z(w.fwd, w.u, w.uh));
   const size_t shells = shell_words(w.nshell), words = result_words(w.nshell);
@@ -364,7 +365,7 @@ void spectrum_compute(dhit_box &b, double *E_host, int kmax, double *stats_host)
                        w.nhalf, w.nshell, inv_n3 * inv_n3, w.result, w.result + words - 1);
     DHIT_HIP(hipGetLastError());
   }
-  DHIT_FFT(hipfftExecZ2D(inv, w.uh, w.u));
+  DHIT_FFT(hipfftExecZ2D(w.inv, w.uh, w.u));
   const int rb = (int)std::min<int64_t>((b.ncell + kBlock - 1) / kBlock, kPowerBlocks);
   hipLaunchKernelGGL(power_sums_kernel, dim3(rb, 3), dim3(kBlock), 0, b.stream, w.u, b.ncell, inv_n3, w.partials);
   hipLaunchKernelGGL(power_totals_kernel, dim3(3), dim3(kBlock), 0, b.stream, w.partials, rb, dstats);
@@ -412,7 +413,7 @@ void pressure_compute(dhit_box &b, const double *u_host, double *drho_host) {
   ensure_work(b);
   SpectrumWork &w = *b.spec;
   const int n = b.n;
-  const hipfftHandle inv = inverse1(b);
+  if (!w.tmp) allocate(&w.tmp, w.nhalf * sizeof(hipfftDoubleComplex));
   double *du = nullptr;
   if (hipMalloc(&du, 3 * b.ncell * sizeof(double)) != hipSuccess)
     throw Error(DHIT_ENOMEM, "cannot allocate the velocity upload buffer");
@@ -428,9 +429,11 @@ void pressure_compute(dhit_box &b, const double *u_host, double *drho_host) {
     }
     // p_hat = -rho0 rhs / |k|^2; drho = 3 p; both transforms are unnormalised
     const double scale = -3.0 * b.p.rho0 / ((double)n * n * n);
-    hipLaunchKernelGGL(inverse_laplacian_kernel, dim3(mb), dim3(256), 0, b.stream, w.tmp, n, w.nhalf, scale);
+    hipLaunchKernelGGL(inverse_laplacian_kernel, dim3(mb), dim3(256), 0, b.stream, w.tmp, w.uh, n, w.nhalf, scale);
     DHIT_HIP(hipGetLastError());
-    DHIT_FFT(hipfftExecZ2D(inv, w.tmp, w.u));
+    // the first of the three fields; the other two are what is left in uh (their
+    // transforms take 1% of the call's time)
+    DHIT_FFT(hipfftExecZ2D(w.inv, w.uh, w.u));
     copy_to_host({{drho_host, w.u, b.ncell * sizeof(double)}}, b.stream);
   } catch (...) {
     (void)hipStreamSynchronize(b.stream);
@@ -444,32 +447,34 @@ void gradient_compute(dhit_box &b, const double *d_u, double *d_grad) {
   ensure_work(b);
   SpectrumWork &w = *b.spec;
   const int n = b.n;
-  const hipfftHandle inv = inverse1(b);
   DHIT_HIP(hipMemcpyAsync(w.u, d_u, 3 * b.ncell * sizeof(double), hipMemcpyDeviceToDevice, b.stream));
   DHIT_FFT(hipfftExecD2Z(w.fwd, w.u, w.uh));
   const double inv_n3 = 1.0 / ((double)n * n * n);  // both transforms are unnormalised
   const int blocks = (int)((w.nhalf + 255) / 256);
-  for (int a = 0; a < 3; ++a)
+  // the three components' derivatives along a at a time: their spectra take the
+  // place of u, which has been transformed
+  hipfftDoubleComplex *du = reinterpret_cast<hipfftDoubleComplex *>(w.u);
+  for (int a = 0; a < 3; ++a) {
     for (int c = 0; c < 3; ++c) {
-      hipLaunchKernelGGL(gradient_kernel, dim3(blocks), dim3(256), 0, b.stream, w.uh + (int64_t)c * w.nhalf, w.tmp, n,
-                         w.nhalf, a, inv_n3);
+      hipLaunchKernelGGL(gradient_kernel, dim3(blocks), dim3(256), 0, b.stream, w.uh + (int64_t)c * w.nhalf,
+                         du + (int64_t)c * w.nhalf, n, w.nhalf, a, inv_n3);
       DHIT_HIP(hipGetLastError());
-      DHIT_FFT(hipfftExecZ2D(inv, w.tmp, d_grad + (int64_t)(3 * a + c) * b.ncell));
     }
+    DHIT_FFT(hipfftExecZ2D(w.inv, du, d_grad + (int64_t)3 * a * b.ncell));
+  }
 }
 
 void vorticity_compute(dhit_box &b, double *omega_host) {
   ensure_work(b);
   SpectrumWork &w = *b.spec;
   const int n = b.n;
-  const hipfftHandle inv = inverse3(b);
   launch_velocity(b, b.f[b.cur], w.u);
   DHIT_FFT(hipfftExecD2Z(w.fwd, w.u, w.uh));
   const double inv_n3 = 1.0 / ((double)n * n * n);  // both transforms are unnormalised
   const int blocks = (int)((w.nhalf + 255) / 256);
   hipLaunchKernelGGL(curl_kernel, dim3(blocks), dim3(256), 0, b.stream, w.uh, n, w.nhalf, inv_n3);
   DHIT_HIP(hipGetLastError());
-  DHIT_FFT(hipfftExecZ2D(inv, w.uh, w.u));
+  DHIT_FFT(hipfftExecZ2D(w.inv, w.uh, w.u));
   copy_to_host({{omega_host, w.u, 3 * b.ncell * sizeof(double)}}, b.stream);
 }
 
