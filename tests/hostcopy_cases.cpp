@@ -3,6 +3,7 @@
 #define FAKE_HIP_MAIN
 #include "fake_hip.hpp"
 
+#include <algorithm>
 #include <new>
 #include <vector>
 
@@ -132,6 +133,29 @@ static int box_at_exit() {
   return 0;
 }
 
+// Every 8-byte phase of a cache line, and destinations that begin and end on
+// both sides of a chunk's end (2 MiB of the host address): each byte once, none
+// beside.
+static int phases() {
+  constexpr size_t chunk = size_t(2) << 20;
+  std::vector<char> mem(kLarge + 3 * chunk);
+  const size_t base = (chunk - reinterpret_cast<uintptr_t>(mem.data()) % chunk) % chunk + chunk;
+  const std::vector<char> src = pattern(kLarge, 9);
+  dhit::box_made();
+  for (size_t bytes : {kLarge, 3 * chunk, 3 * chunk - 8, 3 * chunk + 8})
+    for (int phase = -9; phase <= 9; ++phase) {
+      std::fill(mem.begin(), mem.end(), (char)0x55);
+      char *dst = mem.data() + base + 8 * (ptrdiff_t)phase;
+      const size_t half = bytes / 16 * 8;  // two results of one call
+      dhit::copy_to_host({{dst, src.data(), half}, {dst + half, src.data() + half, bytes - half}}, fake::stream(0));
+      CHECK(std::memcmp(dst, src.data(), bytes) == 0);
+      for (const char *c = mem.data(); c < dst; ++c) CHECK(*c == 0x55);
+      for (const char *c = dst + bytes; c < mem.data() + mem.size(); ++c) CHECK(*c == 0x55);
+    }
+  dhit::box_gone();
+  return 0;
+}
+
 int main(int argc, char **argv) {
   const std::string c = argc > 1 ? argv[1] : "";
   if (c == "two_devices") return two_devices();
@@ -139,5 +163,6 @@ int main(int argc, char **argv) {
   if (c == "per_thread_stream") return per_thread_stream();
   if (c == "out_of_memory") return out_of_memory();
   if (c == "box_at_exit") return box_at_exit();
+  if (c == "phases") return phases();
   return 2;
 }

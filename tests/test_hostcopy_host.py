@@ -19,7 +19,7 @@ def program(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("case", ["two_devices", "known_destinations", "per_thread_stream", "out_of_memory", "box_at_exit"])
+@pytest.mark.parametrize("case", ["two_devices", "known_destinations", "per_thread_stream", "out_of_memory", "box_at_exit", "phases"])
 def test_copies_to_the_host(program, case):
     r = subprocess.run([program, case], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0, (r.returncode, r.stderr)
