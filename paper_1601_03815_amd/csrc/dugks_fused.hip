@@ -34,11 +34,14 @@
 //     populations.
 // The x- and y-faces of centre p-1 are formed in the same iteration from
 // the moment fields of planes p-2, p-1 and p, after which centre p-1 is
-// complete and stored.  Each in-plane face is formed once, by one of its two
-// cells, and handed to the other: across lanes for the x-faces (a tile row
-// is 32 consecutive lanes) and through LDS for the y-faces (in the FP32
-// march the upper cell applies it, and is stored, after the barrier that
-// ends the iteration).  Between planes a thread carries the running
+// complete and stored.  The moments of an x-face are joined from a half of each
+// of its two cells (face_halves), which are neighbouring lanes; in 32-wide tiles
+// the wavefront that holds the two halo rows, and has no centres of its own, does
+// that for the others' columns (and in the FP32 march forms their z-faces'
+// moments too) and leaves the moments in LDS.  A y-face's ten terms are formed by
+// its lower cell and applied by the upper one after the barrier that ends the
+// iteration (FP32), or its moments are joined from the two cells' halves in LDS
+// by every thread that needs them (FP64).  Between planes a thread carries the running
 // results of centres p and p+1 in registers.  LDS holds the populations of
 // plane p only, the in-plane moment fields (R0, Jx, Jy, Pxx, Pxy, Pyy) of
 // planes p-1 and p, and the fields the x/y-faces differentiate in z (Jz,
@@ -253,39 +256,36 @@ __device__ __forceinline__ void gathered(const Plane<Real, W> &c0, const Plane<R
   phase();
 }
 
-// In-plane part of the moments of the D-face (D = 0 or 1) between
-// L = (LX, LY) and R = L + e_D in the current plane: everything but the
-// z-tangential gradients.  Face moment of field pair (value field V,
-// normal-flux field N, in-plane tangential field T):
-//   V_L + (V_R - V_L)/2 - h [(N_R - N_L) + (T(L+e_t) - T(L-e_t) + T(R+e_t) - T(R-e_t))/4]
-template <int D, int LX, int LY, typename Real, class P>
-__device__ __forceinline__ void face_inplane(const P &c, Real h, Real (&m)[4]) {
-  constexpr int t = 1 - D;
-  constexpr int RX = LX + Unit<D>::x, RY = LY + Unit<D>::y;
+// In-plane part of the moments of the y-face between the column (L) and the one
+// above it (R) in the current plane: everything but the z-tangential gradients.
+// Face moment of field pair (value field V, normal-flux field N, in-plane
+// tangential field T):
+//   V_L + (V_R - V_L)/2 - h [(N_R - N_L) + (T(L+e_x) - T(L-e_x) + T(R+e_x) - T(R-e_x))/4]
+template <typename Real, class P>
+__device__ __forceinline__ void yface_inplane(const P &c, Real h, Real (&m)[4]) {
   {
-    const Real tang = dif<jid(t), t, LX, LY>(c) + dif<jid(t), t, RX, RY>(c);
-    const Real vl = c.template at<kR0, LX, LY>(), vr = c.template at<kR0, RX, RY>();
-    const Real nl = c.template at<jid(D), LX, LY>(), nr = c.template at<jid(D), RX, RY>();
+    const Real tang = dif<kJx, 0, 0, 0>(c) + dif<kJx, 0, 0, 1>(c);
+    const Real vl = c.template at<kR0, 0, 0>(), vr = c.template at<kR0, 0, 1>();
+    const Real nl = c.template at<kJy, 0, 0>(), nr = c.template at<kJy, 0, 1>();
     m[0] = (vl + Real(0.5) * (vr - vl)) - h * ((nr - nl) + Real(0.25) * tang);
   }
   static_for<3>([&](auto a) {
-    constexpr int PN = pid(a, D), PT = pid(a, t);
-    const Real tang = dif<PT, t, LX, LY>(c) + dif<PT, t, RX, RY>(c);
-    const Real vl = c.template at<jid(a), LX, LY>(), vr = c.template at<jid(a), RX, RY>();
-    const Real nl = c.template at<PN, LX, LY>(), nr = c.template at<PN, RX, RY>();
+    constexpr int PN = pid(a, 1), PT = pid(a, 0);
+    const Real tang = dif<PT, 0, 0, 0>(c) + dif<PT, 0, 0, 1>(c);
+    const Real vl = c.template at<jid(a), 0, 0>(), vr = c.template at<jid(a), 0, 1>();
+    const Real nl = c.template at<PN, 0, 0>(), nr = c.template at<PN, 0, 1>();
     m[1 + a] = (vl + Real(0.5) * (vr - vl)) - h * ((nr - nl) + Real(0.25) * tang);
   });
 }
 
-// z-tangential part of an x/y-face moment pair sum: for the face between
-// L = (LX, LY) and R, the fields (Jz, Pxz, Pyz, Pzz) summed over L and R.
-template <int D, int LX, int LY, typename Real, class P>
-__device__ __forceinline__ void face_zsum(const P &c, Real (&s)[4]) {
-  constexpr int RX = LX + Unit<D>::x, RY = LY + Unit<D>::y;
-  s[0] = c.template at<kJz, LX, LY>() + c.template at<kJz, RX, RY>();
-  s[1] = c.template at<kPxz, LX, LY>() + c.template at<kPxz, RX, RY>();
-  s[2] = c.template at<kPyz, LX, LY>() + c.template at<kPyz, RX, RY>();
-  s[3] = c.template at<kPzz, LX, LY>() + c.template at<kPzz, RX, RY>();
+// z-tangential part of that face: the fields (Jz, Pxz, Pyz, Pzz) summed over L
+// and R.
+template <typename Real, class P>
+__device__ __forceinline__ void yface_zsum(const P &c, Real (&s)[4]) {
+  s[0] = c.template at<kJz, 0, 0>() + c.template at<kJz, 0, 1>();
+  s[1] = c.template at<kPxz, 0, 0>() + c.template at<kPxz, 0, 1>();
+  s[2] = c.template at<kPyz, 0, 0>() + c.template at<kPyz, 0, 1>();
+  s[3] = c.template at<kPzz, 0, 0>() + c.template at<kPzz, 0, 1>();
 }
 
 // Half of the moments of a z-face that comes from one plane (the cell of
@@ -367,35 +367,32 @@ __device__ __forceinline__ void load_mesh_columns(const Real *coef, int n, int x
   }
 }
 
-// In-plane part of a D-face's moments on the mesh (see face_inplane): the
+// In-plane part of a y-face's moments on the mesh (see yface_inplane): the
 // value v of cell L and the rest m, which is small beside it (added to v once,
 // so that in FP32 a moment is rounded at the scale of v once).
-template <int D, int LX, int LY, typename Real, class P>
-__device__ __forceinline__ void face_inplane_mesh(const P &c, Real lam, Real hg, Real hs, Real (&v)[4], Real (&m)[4]) {
-  constexpr int t = 1 - D;
-  constexpr int RX = LX + Unit<D>::x, RY = LY + Unit<D>::y;
+template <typename Real, class P>
+__device__ __forceinline__ void yface_inplane_mesh(const P &c, Real lam, Real hg, Real hs, Real (&v)[4], Real (&m)[4]) {
   auto moment = [&](auto i, auto V, auto N, auto T) {
-    const Real vl = c.template at<V, LX, LY>(), vr = c.template at<V, RX, RY>();
-    const Real tl = dif<T, t, LX, LY>(c), tr = dif<T, t, RX, RY>(c);
+    const Real vl = c.template at<V, 0, 0>(), vr = c.template at<V, 0, 1>();
+    const Real tl = dif<T, 0, 0, 0>(c), tr = dif<T, 0, 0, 1>(c);
     v[i] = vl;
-    m[i] = lam * ((vr - vl) - hs * (tr - tl)) - (hs * tl + hg * (c.template at<N, RX, RY>() - c.template at<N, LX, LY>()));
+    m[i] = lam * ((vr - vl) - hs * (tr - tl)) - (hs * tl + hg * (c.template at<N, 0, 1>() - c.template at<N, 0, 0>()));
   };
   using std::integral_constant;
-  moment(integral_constant<int, 0>{}, integral_constant<int, kR0>{}, integral_constant<int, jid(D)>{},
-         integral_constant<int, jid(t)>{});
+  moment(integral_constant<int, 0>{}, integral_constant<int, kR0>{}, integral_constant<int, kJy>{},
+         integral_constant<int, kJx>{});
   static_for<3>([&](auto a) {
-    moment(integral_constant<int, 1 + a>{}, integral_constant<int, jid(a)>{}, integral_constant<int, pid(a, D)>{},
-           integral_constant<int, pid(a, t)>{});
+    moment(integral_constant<int, 1 + a>{}, integral_constant<int, jid(a)>{}, integral_constant<int, pid(a, 1)>{},
+           integral_constant<int, pid(a, 0)>{});
   });
 }
 
-// The z-differentiated fields at the D-face (see face_zsum).
-template <int D, int LX, int LY, typename Real, class P>
-__device__ __forceinline__ void face_zvalue_mesh(const P &c, Real lam, Real (&s)[4]) {
-  constexpr int RX = LX + Unit<D>::x, RY = LY + Unit<D>::y;
+// The z-differentiated fields at that face (see yface_zsum).
+template <typename Real, class P>
+__device__ __forceinline__ void yface_zvalue_mesh(const P &c, Real lam, Real (&s)[4]) {
   constexpr int ids[4] = {kJz, kPxz, kPyz, kPzz};
   static_for<4>([&](auto i) {
-    const Real l = c.template at<ids[i], LX, LY>(), r = c.template at<ids[i], RX, RY>();
+    const Real l = c.template at<ids[i], 0, 0>(), r = c.template at<ids[i], 0, 1>();
     s[i] = l + lam * (r - l);
   });
 }
@@ -834,23 +831,23 @@ __device__ __forceinline__ void face_halves(const MeshMarch<Real, W> &mc, int p,
   });
 }
 
-// Moments of the D-face (D = 0 or 1) between the column and its upper
-// neighbour at centre plane p-1, on the mesh (planes p, p-1, p-2).
-template <int D, typename Real, int W>
-__device__ __forceinline__ void face_moments_mesh(const MeshMarch<Real, W> &mc, int p, const Plane<Real, W> &c,
+// Moments of the y-face between the column and its upper neighbour at centre
+// plane p-1, on the mesh (planes p, p-1, p-2).
+template <typename Real, int W>
+__device__ __forceinline__ void yface_moments_mesh(const MeshMarch<Real, W> &mc, int p, const Plane<Real, W> &c,
                                                   const Plane<Real, W> &c1, const Plane<Real, W> &c2, Real (&m)[4]) {
-  const Real lam = mc.template col<D>(kMarchLam), hg = mc.template col<D>(kMarchHg);
-  const Real hs = mc.template col<1 - D>(kMarchHs), hsz = mc.z(kMarchHs, p - 1);
+  const Real lam = mc.template col<1>(kMarchLam), hg = mc.template col<1>(kMarchHg);
+  const Real hs = mc.template col<0>(kMarchHs), hsz = mc.z(kMarchHs, p - 1);
   Real vl[4], s1[4];
   gathered<Real, W>(c1, c1, [&](const auto &g, const auto &) {
     Real v[4], t[4];
-    face_inplane_mesh<D, 0, 0>(g, lam, hg, hs, v, t);
+    yface_inplane_mesh(g, lam, hg, hs, v, t);
     if constexpr (std::decay_t<decltype(g)>::use) static_for<4>([&](auto i) { vl[i] = v[i]; m[i] = t[i]; });
   });
   gathered<Real, W>(c, c2, [&](const auto &g, const auto &g2) {
     Real a[4], b[4];
-    face_zvalue_mesh<D, 0, 0>(g, lam, a);
-    face_zvalue_mesh<D, 0, 0>(g2, lam, b);
+    yface_zvalue_mesh(g, lam, a);
+    yface_zvalue_mesh(g2, lam, b);
     if constexpr (std::decay_t<decltype(g)>::use) static_for<4>([&](auto i) { s1[i] = a[i] - b[i]; });
   });
   static_for<4>([&](auto i) { m[i] = vl[i] + (m[i] - hsz * s1[i]); });
@@ -1106,32 +1103,30 @@ __device__ __forceinline__ void fused_tile(const global_t<Real> *__restrict__ ft
       // y-faces of centre p-1: in-plane part from plane p-1, the z-tangential
       // gradients -h/4 [(M_L + M_R)(p) - (M_L + M_R)(p-2)]
       const Real hq = Real(0.25) * h;
-      auto face_moments = [&](auto D, auto LX, auto LY, Real (&m)[4]) {
+      auto yface_moments = [&](Real (&m)[4]) {
         if constexpr (Mesh) {
-          face_moments_mesh<D>(mc, p_, c, c1, c2, m);
+          yface_moments_mesh(mc, p_, c, c1, c2, m);
           return;
         }
         gathered<Real, W>(c1, c1, [&](const auto &g, const auto &) {
           Real t[4];
-          face_inplane<D, LX, LY>(g, h, t);
+          yface_inplane(g, h, t);
           if constexpr (std::decay_t<decltype(g)>::use) static_for<4>([&](auto i) { m[i] = t[i]; });
         });
         gathered<Real, W>(c, c2, [&](const auto &g, const auto &g2) {
           Real s1[4], s0[4];
-          face_zsum<D, LX, LY>(g, s1);
-          face_zsum<D, LX, LY>(g2, s0);
+          yface_zsum(g, s1);
+          yface_zsum(g2, s0);
           if constexpr (std::decay_t<decltype(g)>::use) static_for<4>([&](auto i) { m[i] -= hq * (s1[i] - s0[i]); });
         });
       };
-      using I0 = std::integral_constant<int, 0>;
-      using I1 = std::integral_constant<int, 1>;
       // The y-face between the column and the next row is formed once, by
       // every interior column of every row but the last (halo row 0 too); its
       // ten terms are left in LY for the column above, which applies them as
       // its lower face in finish().
       if (yface) {
         Real my[4], fy[10];
-        face_moments(I1{}, I0{}, I0{}, my);
+        yface_moments(my);
         face_terms<1>(my, p, dtbe, fy);
         static_for<10>([&](auto k) { LY[k * NT] = fy[k]; });
         if (inner) {
@@ -1296,7 +1291,6 @@ __global__ __launch_bounds__(Tile<W>::NT, kWavesPerSimd<Real>) void dugks_fused_
     const global_t<Real> *src = to_global(static_cast<const Real *>(d.f[d.cur]));
     global_t<Real> *dst = to_global(static_cast<Real *>(d.f[d.cur ^ 1]));
     const ItemPlanes ip(d, local);
-    // the march ends with a barrier: L is free for the block reduction
     if (ip.left > 0) {
       auto march = [&](auto halo) {
         fused_tile<Real, W, O32, Mesh, halo>(src, dst, d.sp, ip.tile % d.tiles_x, ip.tile / d.tiles_x, ip.z0,
@@ -1307,6 +1301,10 @@ __global__ __launch_bounds__(Tile<W>::NT, kWavesPerSimd<Real>) void dugks_fused_
       else if constexpr (W == 32)
         march(std::true_type{});
     }
+    // After the march's last barrier, finish() reads the face terms and moments
+    // and the mesh coefficients; the reduction's rows lie in the populations'
+    // part of L, which it does not read.
+    static_assert(sizeof(double) * kNumSums * (Tile<W>::NT / 64) <= sizeof(Real) * kNPop * Tile<W>::NT);
     // summed in the order of the wavefronts' rows: which wavefront has which rows
     // depends on the block's number, which the extra block shifts
     write_block_partials<Tile<W>::NT / 64>(v, d.partials, d.items, local, reinterpret_cast<double (*)[kNumSums]>(L),
@@ -1899,7 +1897,6 @@ FusedPlan fused_plan_for(const dhit_params &p, int slots) {
   FusedPlan f{};
   const int n = p.n;
   f.width = p.tile_width ? p.tile_width : fused_tile_width(p.precision);
-  // an unresolved setting (0) gets the shortest automatic chunk: an upper
   // an unresolved setting (0) is taken as kMinAutoChunk planes
   f.chunk = p.z_chunk > 0 ? p.z_chunk : (p.z_chunk < 0 ? -p.z_chunk : std::min(n, kMinAutoChunk));
   const int chunks = fused_dugks_items(n, f.width, f.chunk, &f.tiles_x, &f.tiles_y);
