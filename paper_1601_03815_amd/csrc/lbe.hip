@@ -220,11 +220,13 @@ static void hold_launch(dhit_box &b, const void *src, void *dst, const double *d
 
 void launch_lbe_hold(dhit_box &b, const void *src, void *dst, const double *d_u, double *d_drho_out,
                      const double *d_drho_prev, double *d_block_max) {
+  TimedLaunch t(b, DHIT_K_LBE);
   if (b.p.precision == DHIT_FP64)
     hold_launch<double>(b, src, dst, d_u, d_drho_out, d_drho_prev, d_block_max);
   else
     hold_launch<float>(b, src, dst, d_u, d_drho_out, d_drho_prev, d_block_max);
   DHIT_HIP(hipGetLastError());
+  t.done();
 }
 
 // One launch advances one or many boxes: work item = a run of B * C cells of

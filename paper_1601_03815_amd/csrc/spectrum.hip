@@ -368,8 +368,13 @@ void spectrum_compute(dhit_box &b, double *E_host, int kmax, double *stats_host)
   DHIT_FFT(hipfftExecZ2D(w.inv, w.uh, w.u));
   const int rb = (int)std::min<int64_t>((b.ncell + kBlock - 1) / kBlock, kPowerBlocks);
   hipLaunchKernelGGL(power_sums_kernel, dim3(rb, 3), dim3(kBlock), 0, b.stream, w.u, b.ncell, inv_n3, w.partials);
-  hipLaunchKernelGGL(power_totals_kernel, dim3(3), dim3(kBlock), 0, b.stream, w.partials, rb, dstats);
   DHIT_HIP(hipGetLastError());
+  {
+    TimedLaunch t(b, DHIT_K_FINALIZE);
+    hipLaunchKernelGGL(power_totals_kernel, dim3(3), dim3(kBlock), 0, b.stream, w.partials, rb, dstats);
+    DHIT_HIP(hipGetLastError());
+    t.done();
+  }
   std::vector<unsigned long long> dig(words);
   DHIT_HIP(hipMemcpyAsync(dig.data(), w.result, words * sizeof(unsigned long long), hipMemcpyDeviceToHost, b.stream));
   DHIT_HIP(hipStreamSynchronize(b.stream));
