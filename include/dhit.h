@@ -322,9 +322,9 @@ int32_t current_populations(const dhit_box *b, void **ptr, int64_t *stride);
  * 8 steps are replayed from one captured hipGraph.  Results equal
  * single-box steps: populations bit for bit (a single DUGKS box runs the
  * same work-list kernel on a table of one entry, and the march rounds
- * alike whatever the z-chunk; a batch of tile width 16 equals boxes of
- * tile_width 16), global sums to rounding (the chunk decides how the cell
- * sums are grouped).
+ * alike whatever the z-chunk and the tile width), global sums to rounding
+ * (the chunk and the tile width, for LBE the block size, which is smaller for
+ * a small box stepped alone, decide how the cell sums are grouped).
  *
  * create_batch: boxes[nbox] must share method and precision (DUGKS boxes the
  * default variant) and appear once.  With autotune != 0 the grid (one block

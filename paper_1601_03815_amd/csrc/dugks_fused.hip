@@ -1269,7 +1269,8 @@ __device__ __forceinline__ int xcd_tile(int b, int padded) { return (b & 7) * (p
 // the tiles of that box's own launch.  Round r of the grid takes items
 // [r G, (r+1) G), dealt to the XCDs in contiguous eighths.  A single box is
 // a table of one entry, so a box stepped alone and the same box stepped in
-// a batch run the same machine code and give the same bits.
+// a batch of its tile width run the same machine code; other tile widths and
+// offsets round alike too, so the populations are the same bits.
 template <typename Real, int W, bool O32, bool Mesh>
 __global__ __launch_bounds__(Tile<W>::NT, kWavesPerSimd<Real>) void dugks_fused_kernel(const BatchBox *__restrict__ boxes, int nbox,
                                                                   int total_items, PendingSums prev) {
@@ -1855,7 +1856,13 @@ __global__ void store_table_kernel(BatchBox e0, BatchBox e1, BatchBox *__restric
 // Default tile: 32 x 8 columns in both precisions (rows of 256 B in FP64).
 // FP64 (split march, 512 threads): 136 KB of LDS, one block per compute
 // unit; FP32 (256 threads): 59 KB of LDS, two blocks per compute unit
-// (two waves per SIMD).
+// (two waves per SIMD).  The choice does not look at n: 16-wide tiles lose from
+// 80^3 on (us a step, 32- and 16-wide: FP64 128^3 213 and 237, 80^3 49.8 and 50.7;
+// FP32 128^3 120 and 139, 80^3 31.7 and 34.5) and below win at some sizes only (FP64
+// 16^3 9.9 and 8.7, 40^3 17.1 and 14.6, 64^3 37.5 and 32.8, but 32^3 13.9 and 14.0,
+// 48^3 17.4 and 18.0; FP32 40^3 14.9 and 12.2, 64^3 24.7 and 23.5, but 32^3 10.8 and
+// 11.2, 48^3 15.0 and 15.8).  tile_width lets the caller choose; the populations
+// are the same bits.
 constexpr int fused_tile_width(int) { return 32; }
 
 int fused_default_chunk(int n) { return n >= 128 ? 32 : (n >= 32 ? 16 : n); }

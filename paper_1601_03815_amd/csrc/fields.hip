@@ -179,6 +179,8 @@ __global__ __launch_bounds__(kBlock) void finalize_sums_wide_kernel(const double
   }
   const double t = block_sum5<kWaves>(v, smem);
   unsigned *counter = reinterpret_cast<unsigned *>(level + kFinalizeLevels * kNumSums);
+  // (five lanes of one wavefront: its outstanding stores are what thread 0's
+  // release waits for)
   if (threadIdx.x < kNumSums)
     __hip_atomic_store(&level[(int64_t)blockIdx.x * kNumSums + threadIdx.x], t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   if (threadIdx.x == 0) {

@@ -31,8 +31,9 @@ namespace dhit {
 // which does not keep enough accesses in flight once the populations come
 // from HBM (us per step with two cells and with one: 256^3 971 and 930, 128^3
 // 135 and 122, 96^3 62.2 and 57.1; 64^3, in the caches, 19.0 and 19.5).
-// At 256^3 the step runs at the rate of a plain copy of 19 arrays of its
-// layout (0.90-0.96 ms over access widths and block sizes).
+// At 256^3 in FP64 the MRT step takes 0.927 ms; plain copies of 19 arrays of its
+// layout took 0.902 (64-thread blocks) to 0.960 ms over access widths and block
+// sizes.
 template <typename Real>
 constexpr int kRunCells = sizeof(Real) == 8 ? 2 : 1;
 constexpr int64_t kBgkRunMaxCells = 512000;
@@ -44,7 +45,9 @@ constexpr int64_t kBgkRunMaxCells = 512000;
 // (with its finalisation launch), against kRunCells in blocks of kBlock:
 // FP64 MRT 6.8 (11.8), 48^3 12.6 (15.1), 52^3 14.8 (16.2), but 56^3 17.4
 // (16.6); FP32 7.0 (7.3), 36^3 8.1 (7.9).  Blocks of 64 threads: 32^3 7.0,
-// 48^3 12.7, 52^3 15.7.
+// 48^3 12.7, 52^3 15.7.  (Batches keep blocks of kBlock threads: a small box's
+// populations are the same bits there, its step sums are grouped otherwise and
+// agree to rounding.)
 constexpr int kSmallBlock = 128;
 template <typename Real>
 constexpr int64_t kSmallCells = sizeof(Real) == 8 ? 150000 : 32768;
